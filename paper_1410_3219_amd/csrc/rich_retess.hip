@@ -29,8 +29,8 @@
 // clip handles only the cells it leaves.
 //
 // Pipeline (one launch each, all on the caller's stream):
-//   k_rt_begin    clear the result header and the queue counters
-//   k_rt_pack     the new points packed in pairs
+//   k_rt_begin    clear the result header and the queue counters, pack the
+//                 new points in pairs
 //   k_rt_vertex   one thread per cell: the cell from its previous ring, when
 //                 every vertex passes (else queued for the clip)
 //   k_rt_clip     one thread per queued cell: the cell's edges, area, centroid
@@ -38,9 +38,10 @@
 //                 cells left over)
 //   k_rt_classify keep / own each slot by the input stage's rules, check
 //                 each kept edge against the neighbour's slot, count
-//   k_rt_scan_*   prefix sums of the counts into off[] and eoff[]
-//   k_rt_emit     edge records and the CSR entries of both sides of each edge
-//   k_rt_end      fold the flags into the sticky word, count the clipped cells
+//   k_rt_scan_*   prefix sums of the counts (within and over blocks of cells),
+//                 totals, the checks that need every cell, the result header
+//   k_rt_emit     off[], eoff[], edge records and the CSR entries of both
+//                 sides of each edge
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -108,7 +109,7 @@ struct Args {
   int64_t p_n_csr, p_n_edges;
   // new points and output
   const double *x, *y;
-  double2* xy;         // [n] the new points packed in pairs (filled by k_rt_pack)
+  double2* xy;         // [n] the new points packed in pairs (filled by k_rt_begin)
   rich_cell* cells;
   rich_edge* edges;
   int32_t *off, *idx, *eoff;
@@ -120,6 +121,7 @@ struct Args {
   double* s_geo;       // [n][kMaxFan][3] edge length, midpoint x, midpoint y
   uint8_t* s_flag;     // [n][kMaxFan] bit 0 kept, bit 1 owned, bits 2-6 rank among kept
   uint8_t* s_back;     // [n][kMaxFan] owned edge: its slot in the neighbour's row
+  uint32_t* cnt;       // [n] kept | owned << 16 edges of a cell; then of its scan block before it
   int64_t* bsum;       // [2][n_scan_blocks] block totals of kept / owned
   CPart* cpart;        // [cell blocks] classify block sums, reduced by the scan
   int32_t* qcnt;       // [kSeg * kSegStride] queue segment counters (every kSegStride-th)
@@ -202,49 +204,28 @@ __device__ __forceinline__ int prev_neighbour(const Args& a, int k) {
   return (int)((uint32_t)a.p_edges[e].j & kMask);
 }
 
+// Clears the result header and the queue counters (each run's first block)
+// and packs the new points in pairs, so that a candidate's point is one
+// 16-byte load (the kernels gather them by cell index many times over).
 template <bool B>
-__global__ void k_rt_begin(Args one, Batch bt) {
-  const Args& a = B ? bt.descs[blockIdx.x] : one;
-  Hdr* h = a.hdr;
-  for (int t = threadIdx.x; t < kSeg; t += blockDim.x) a.qcnt[t * kSegStride] = 0;
-  if (threadIdx.x == 0) {
-    h->flags = 0;
-    h->n_edges = 0;
-    h->n_csr = 0;
-    h->n_dropped = 0;
-    h->area_sum = 0.0;
-    h->n_wall = 0;
-    h->n_clip = 0;
-  }
-}
-
-// The new points packed in pairs, so that a candidate's point is one 16-byte
-// load (the kernels gather them by cell index many times over).
-template <bool B>
-__global__ __launch_bounds__(kThreads) void k_rt_pack(Args one, Batch bt) {
+__global__ __launch_bounds__(kThreads) void k_rt_begin(Args one, Batch bt) {
   int blk;
   const Args& a = block_run<B>(one, bt.cstart, bt, blk);
-  const int i = blk * kThreads + threadIdx.x;
-  if (i < a.n) a.xy[i] = make_double2(a.x[i], a.y[i]);
-}
-
-template <bool B>
-__global__ void k_rt_end(Args one, Batch bt) {
-  const Args& a = B ? bt.descs[blockIdx.x] : one;
-  Hdr* h = a.hdr;
-  // the cells the vertex check queued for the clip (one wave sums the
-  // segment counters)
-  int c = 0;
-  for (int t = threadIdx.x; t < kSeg; t += blockDim.x) c += a.qcnt[t * kSegStride];
-  for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
-  if (threadIdx.x == 0) {
-    h->n_clip = c;
-    h->sticky |= h->flags;
-    if (B) {
-      bt.hdr_out[blockIdx.x] = *h;
-      bt.flags_out[blockIdx.x] = h->flags;
+  if (blk == 0) {
+    Hdr* h = a.hdr;
+    for (int t = threadIdx.x; t < kSeg; t += kThreads) a.qcnt[t * kSegStride] = 0;
+    if (threadIdx.x == 0) {
+      h->flags = 0;
+      h->n_edges = 0;
+      h->n_csr = 0;
+      h->n_dropped = 0;
+      h->area_sum = 0.0;
+      h->n_wall = 0;
+      h->n_clip = 0;
     }
   }
+  const int i = blk * kThreads + threadIdx.x;
+  if (i < a.n) a.xy[i] = make_double2(a.x[i], a.y[i]);
 }
 
 // ---------------------------------------------------------------------------
@@ -1031,8 +1012,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_rt_classify(Args one, Batch b
   }
   if (i < a.n && l == 0) {
     if (bad) atomicOr(&a.hdr->flags, bad);
-    a.off[i + 1] = n_keep;  // counts; the scan makes them offsets
-    a.eoff[i + 1] = n_own;
+    a.cnt[i] = (uint32_t)n_keep | (uint32_t)n_own << 16;  // the scan makes them offsets
   }
   // block sums of the areas and of the dropped edges
   for (int o = 32; o > 0; o >>= 1) {
@@ -1062,51 +1042,49 @@ __global__ __launch_bounds__(kGroupThreads) void k_rt_classify(Args one, Batch b
 }
 
 // ---------------------------------------------------------------------------
-// prefix sums of the kept / owned counts (in place in off[1..n], eoff[1..n])
+// prefix sums of the kept / owned counts.  Offsets are kept as a cell's
+// prefix within its scan block (cnt, both counts in one word) plus the
+// block's own offset (bsum); emit adds the two and writes off[] and eoff[],
+// which spares a launch and a pass over the cells.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void block_scan2(int& v0, int& v1, int* s0, int* s1, int& tot0,
-                                            int& tot1) {
-  // inclusive scan over the block of two values per thread
+static_assert(kScanThreads * kMaxFan < (1 << 16), "a scan block's counts fit 16 bits");
+
+// Inclusive scan of one value per thread over the block; every thread also
+// gets the total.  s holds a value per wave.
+template <typename T>
+__device__ __forceinline__ T block_scan(T v, T* s, T& total) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  constexpr int NW = kScanThreads / 64;
   for (int o = 1; o < 64; o <<= 1) {
-    const int u0 = __shfl_up(v0, o), u1 = __shfl_up(v1, o);
-    if (lane >= o) { v0 += u0; v1 += u1; }
+    const T u = __shfl_up(v, o);
+    if (lane >= o) v += u;
   }
-  if (lane == 63) { s0[wv] = v0; s1[wv] = v1; }
+  if (lane == 63) s[wv] = v;
   __syncthreads();
-  if (wv == 0) {
-    constexpr int NW = kScanThreads / 64;
-    int w0 = lane < NW ? s0[lane] : 0, w1 = lane < NW ? s1[lane] : 0;
-    for (int o = 1; o < NW; o <<= 1) {
-      const int u0 = __shfl_up(w0, o), u1 = __shfl_up(w1, o);
-      if (lane >= o) { w0 += u0; w1 += u1; }
-    }
-    if (lane < NW) { s0[lane] = w0; s1[lane] = w1; }
+  T before = 0;
+  total = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    const T u = s[w];
+    if (w < wv) before += u;
+    total += u;
   }
-  __syncthreads();
-  if (wv > 0) { v0 += s0[wv - 1]; v1 += s1[wv - 1]; }
-  tot0 = s0[kScanThreads / 64 - 1];
-  tot1 = s1[kScanThreads / 64 - 1];
-  __syncthreads();
+  return v + before;
 }
 
 template <bool B>
 __global__ __launch_bounds__(kScanThreads) void k_rt_scan_local(Args one, Batch bt) {
   int blk;
   const Args& a = block_run<B>(one, bt.sstart, bt, blk);
-  __shared__ int s0[kScanThreads / 64], s1[kScanThreads / 64];
+  __shared__ uint32_t s[kScanThreads / 64];
   const int i = blk * kScanThreads + threadIdx.x;
-  int v0 = i < a.n ? a.off[i + 1] : 0;
-  int v1 = i < a.n ? a.eoff[i + 1] : 0;
-  int t0, t1;
-  block_scan2(v0, v1, s0, s1, t0, t1);
-  if (i < a.n) {
-    a.off[i + 1] = v0;
-    a.eoff[i + 1] = v1;
-  }
+  const uint32_t v = i < a.n ? a.cnt[i] : 0u;
+  uint32_t total;
+  const uint32_t inc = block_scan(v, s, total);
+  if (i < a.n) a.cnt[i] = inc - v;   // (no borrow: both halves grow along the block)
   if (threadIdx.x == 0) {
-    a.bsum[blk] = t0;
-    a.bsum[a.n_scan_blocks + blk] = t1;
+    a.bsum[blk] = total & 0xFFFFu;
+    a.bsum[a.n_scan_blocks + blk] = total >> 16;
   }
   // the sums of the classify blocks of this block's cells, in order, into
   // the first of them (the scan of the block totals reads only those)
@@ -1124,25 +1102,30 @@ __global__ __launch_bounds__(kScanThreads) void k_rt_scan_local(Args one, Batch 
   }
 }
 
-// one block: exclusive scan of the block totals, totals and the checks that
-// need every cell (areas, capacities)
+// One block: exclusive scan of the block totals, totals, the checks that
+// need every cell (areas, capacities) and the finished result header (the
+// flags folded into the sticky word, the cells queued for the clip counted).
+// The totals go through one scan over the block's threads (each thread's
+// run of scan blocks first); a single thread adding 1024 of them took 22 of
+// this kernel's 25 us, the same for every mesh size.
 template <bool B>
 __global__ __launch_bounds__(kScanThreads) void k_rt_scan_blocks(Args one, Batch bt) {
   const Args& a = B ? bt.descs[blockIdx.x] : one;
-  __shared__ long long s0[kScanThreads], s1[kScanThreads];
   constexpr int NW = kScanThreads / 64;
+  __shared__ long long s0[NW], s1[NW];
   __shared__ double s_area[NW];
   __shared__ long long s_drop[NW], s_wall[NW];
+  __shared__ int s_clip;
   // the classify blocks' sums (those of each scan block gathered by
   // k_rt_scan_local): each thread every kScanThreads-th scan block, a fixed
   // xor tree over each wave, then thread 0 over the waves in order (a fixed
   // order throughout, so the area sum is reproducible)
-  const int nb_scan = a.n_scan_blocks;
+  const int nb = a.n_scan_blocks;
   {
     constexpr int CPB = kScanThreads / kThreads;   // classify blocks per scan block
     double ar = 0.0;
     long long dr = 0, wl = 0;
-    for (int c = threadIdx.x; c < nb_scan; c += kScanThreads) {
+    for (int c = threadIdx.x; c < nb; c += kScanThreads) {
       const CPart p = a.cpart[c * CPB];
       ar += p.area;
       dr += p.drop;
@@ -1159,17 +1142,31 @@ __global__ __launch_bounds__(kScanThreads) void k_rt_scan_blocks(Args one, Batch
       s_wall[threadIdx.x >> 6] = wl;
     }
   }
-  const int nb = a.n_scan_blocks;
+  // the cells the vertex check queued for the clip (the first wave sums the
+  // segment counters)
+  if (threadIdx.x < 64) {
+    int c = 0;
+    for (int t = threadIdx.x; t < kSeg; t += 64) c += a.qcnt[t * kSegStride];
+    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
+    if (threadIdx.x == 0) s_clip = c;
+  }
   const int per = (nb + kScanThreads - 1) / kScanThreads;
-  const int b0 = threadIdx.x * per, b1 = min(nb, b0 + per);
+  const int b0 = min(nb, (int)threadIdx.x * per), b1 = min(nb, b0 + per);
   long long c0 = 0, c1 = 0;
   for (int b = b0; b < b1; ++b) {
     c0 += a.bsum[b];
     c1 += a.bsum[nb + b];
   }
-  s0[threadIdx.x] = c0;
-  s1[threadIdx.x] = c1;
-  __syncthreads();
+  long long t0, t1;
+  long long r0 = block_scan(c0, s0, t0) - c0;   // (its barrier also publishes the sums above)
+  long long r1 = block_scan(c1, s1, t1) - c1;
+  for (int b = b0; b < b1; ++b) {
+    const long long u0 = a.bsum[b], u1 = a.bsum[nb + b];
+    a.bsum[b] = r0;
+    a.bsum[nb + b] = r1;
+    r0 += u0;
+    r1 += u1;
+  }
   if (threadIdx.x == 0) {
     double ar = 0.0;
     long long dr = 0, wl = 0;
@@ -1178,59 +1175,38 @@ __global__ __launch_bounds__(kScanThreads) void k_rt_scan_blocks(Args one, Batch
       dr += s_drop[w];
       wl += s_wall[w];
     }
-    a.hdr->area_sum = ar;
-    a.hdr->n_dropped = dr;
-    a.hdr->n_wall = wl;
-  }
-  // serial over the 1024 chunk sums by one thread: 1024 additions
-  if (threadIdx.x == 0) {
-    long long r0 = 0, r1 = 0;
-    for (int t = 0; t < kScanThreads; ++t) {
-      const long long u0 = s0[t], u1 = s1[t];
-      s0[t] = r0;
-      s1[t] = r1;
-      r0 += u0;
-      r1 += u1;
-    }
-    Hdr* h = a.hdr;
-    h->n_csr = r0;
-    h->n_edges = r1;
-    int f = 0;
-    if (r0 > a.cap_csr || r1 > a.cap_edges) f |= RICH_RETESS_CAP;
-    if (r0 != 2 * r1 - h->n_wall) f |= RICH_RETESS_ASYM;   // an unmatched kept slot
+    Hdr h = *a.hdr;
+    h.area_sum = ar;
+    h.n_dropped = dr;
+    h.n_wall = wl;
+    h.n_csr = t0;
+    h.n_edges = t1;
+    h.n_clip = s_clip;
+    if (t0 > a.cap_csr || t1 > a.cap_edges) h.flags |= RICH_RETESS_CAP;
+    if (t0 != 2 * t1 - wl) h.flags |= RICH_RETESS_ASYM;   // an unmatched kept slot
     const double box = a.Lx * a.Ly;
-    if (!(fabs(h->area_sum - box) <= 1e-10 * box)) f |= RICH_RETESS_AREA;
-    if (f) h->flags |= f;
-  }
-  __syncthreads();
-  long long r0 = s0[threadIdx.x], r1 = s1[threadIdx.x];
-  for (int b = b0; b < b1; ++b) {
-    const long long u0 = a.bsum[b], u1 = a.bsum[nb + b];
-    a.bsum[b] = r0;
-    a.bsum[nb + b] = r1;
-    r0 += u0;
-    r1 += u1;
-  }
-}
-
-template <bool B>
-__global__ __launch_bounds__(kScanThreads) void k_rt_scan_add(Args one, Batch bt) {
-  int blk;
-  const Args& a = block_run<B>(one, bt.sstart, bt, blk);
-  const int i = blk * kScanThreads + threadIdx.x;
-  if (i == 0) {
-    a.off[0] = 0;
-    a.eoff[0] = 0;
-  }
-  if (i < a.n) {
-    a.off[i + 1] += (int32_t)a.bsum[blk];
-    a.eoff[i + 1] += (int32_t)a.bsum[a.n_scan_blocks + blk];
+    if (!(fabs(ar - box) <= 1e-10 * box)) h.flags |= RICH_RETESS_AREA;
+    h.sticky |= h.flags;
+    *a.hdr = h;
+    if (B) {
+      bt.hdr_out[blockIdx.x] = h;
+      bt.flags_out[blockIdx.x] = h.flags;
+    }
   }
 }
 
 // ---------------------------------------------------------------------------
 // edge records and CSR entries
 // ---------------------------------------------------------------------------
+// First CSR entry / first owned edge of cell c: its scan block's offset plus
+// its own within the block.
+__device__ __forceinline__ int csr_offset(const Args& a, int c) {
+  return (int)a.bsum[c / kScanThreads] + (int)(a.cnt[c] & 0xFFFFu);
+}
+__device__ __forceinline__ int edge_offset(const Args& a, int c) {
+  return (int)a.bsum[a.n_scan_blocks + c / kScanThreads] + (int)(a.cnt[c] >> 16);
+}
+
 // Each cell writes, for every edge it owns (its owned slots in slot order
 // from eoff[i]): the edge record, its own CSR entry 2 e at the slot's rank
 // among its kept slots, and, unless the edge is a wall, the neighbour's entry
@@ -1247,21 +1223,20 @@ __global__ __launch_bounds__(kGroupThreads) void k_rt_emit(Args one, Batch bt) {
   const int l = (int)threadIdx.x % kGroup;
   const int i = blk * kThreads + (int)threadIdx.x / kGroup;
   if (i >= a.n) return;  // whole groups
-  if (a.hdr->flags != 0) {
-    if (l == 0) {
-      a.off[i + 1] = 0;
-      a.eoff[i + 1] = 0;
-      if (i == 0) {
-        a.off[0] = 0;
-        a.eoff[0] = 0;
-      }
+  const bool failed = a.hdr->flags != 0;
+  const int k = csr_offset(a, i);
+  int e = edge_offset(a, i);
+  if (l == 0) {
+    a.off[i] = failed ? 0 : k;
+    a.eoff[i] = failed ? 0 : e;
+    if (i == a.n - 1) {   // the totals close the offsets
+      a.off[a.n] = failed ? 0 : (int32_t)a.hdr->n_csr;
+      a.eoff[a.n] = failed ? 0 : (int32_t)a.hdr->n_edges;
     }
-    return;
   }
+  if (failed) return;
   const int d = a.deg[i];
   const size_t s0 = (size_t)i * kMaxFan;
-  const int k = a.off[i];
-  int e = a.eoff[i];
   for (int base = 0; base < d; base += kGroup) {
     const int q = base + l;
     const uint8_t f = q < d ? a.s_flag[s0 + q] : (uint8_t)0;
@@ -1282,7 +1257,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_rt_emit(Args one, Batch bt) {
       if ((int)((uint32_t)id >> kShift) < kWallX0) {
         const int j = (int)((uint32_t)id & kMask);
         const int t = a.s_back[s0 + q];
-        a.idx[a.off[j] + (a.s_flag[(size_t)j * kMaxFan + t] >> 2)] = 2 * ee + 1;
+        a.idx[csr_offset(a, j) + (a.s_flag[(size_t)j * kMaxFan + t] >> 2)] = 2 * ee + 1;
       }
     }
     e += __popc(mo);
@@ -1305,7 +1280,7 @@ namespace {
 size_t rt_align(size_t v) { return (v + 255) / 256 * 256; }
 
 struct RtLayout {
-  size_t deg, s_nb, s_geo, s_flag, s_back, bsum, cpart, qcnt, queue, xy, total;
+  size_t deg, s_nb, s_geo, s_flag, s_back, cnt, bsum, cpart, qcnt, queue, xy, total;
   int nb, qcap;
 };
 
@@ -1319,6 +1294,7 @@ RtLayout rt_layout(int64_t n) {
   L.s_geo = o;  o += rt_align(24 * slots);
   L.s_flag = o; o += rt_align(slots);
   L.s_back = o; o += rt_align(slots);
+  L.cnt = o;    o += rt_align(4 * (size_t)n);
   L.bsum = o;   o += rt_align(16 * (size_t)L.nb);
   L.cpart = o;
   const int64_t blocks = (n + retess::kThreads - 1) / retess::kThreads;
@@ -1384,6 +1360,7 @@ int make_args(const rich_mesh* prev, const double* x, const double* y,
   a.s_geo = reinterpret_cast<double*>(w + L.s_geo);
   a.s_flag = reinterpret_cast<uint8_t*>(w + L.s_flag);
   a.s_back = reinterpret_cast<uint8_t*>(w + L.s_back);
+  a.cnt = reinterpret_cast<uint32_t*>(w + L.cnt);
   a.bsum = reinterpret_cast<int64_t*>(w + L.bsum);
   a.cpart = reinterpret_cast<retess::CPart*>(w + L.cpart);
   a.qcnt = reinterpret_cast<int32_t*>(w + L.qcnt);
@@ -1402,14 +1379,13 @@ int make_args(const rich_mesh* prev, const double* x, const double* y,
   return RICH_OK;
 }
 
-// The eleven launches of one re-tessellation of one kind of box (B: of n_runs runs at once, with
+// The launches of one re-tessellation of one kind of box (B: of n_runs runs at once, with
 // gc cell blocks and gs scan blocks in all).
 template <bool B>
 void launch_all(const retess::Args& a, const retess::Batch& bt, int gc, int gs, int n_runs,
                 bool walls, bool periodic, hipStream_t st) {
   using namespace retess;
-  hipLaunchKernelGGL(k_rt_begin<B>, dim3(n_runs), dim3(64), 0, st, a, bt);
-  hipLaunchKernelGGL(k_rt_pack<B>, dim3(gc), dim3(kThreads), 0, st, a, bt);
+  hipLaunchKernelGGL(k_rt_begin<B>, dim3(gc), dim3(kThreads), 0, st, a, bt);
   if (walls) {
     hipLaunchKernelGGL((k_rt_vertex<B, true>), dim3(gc), dim3(kThreads), 0, st, a, bt);
     hipLaunchKernelGGL((k_rt_clip<B, true, kSlotsFast, false>), dim3(gc), dim3(kThreads), 0, st,
@@ -1427,9 +1403,7 @@ void launch_all(const retess::Args& a, const retess::Batch& bt, int gc, int gs, 
   hipLaunchKernelGGL(k_rt_classify<B>, dim3(gc), dim3(kGroupThreads), 0, st, a, bt);
   hipLaunchKernelGGL(k_rt_scan_local<B>, dim3(gs), dim3(kScanThreads), 0, st, a, bt);
   hipLaunchKernelGGL(k_rt_scan_blocks<B>, dim3(n_runs), dim3(kScanThreads), 0, st, a, bt);
-  hipLaunchKernelGGL(k_rt_scan_add<B>, dim3(gs), dim3(kScanThreads), 0, st, a, bt);
   hipLaunchKernelGGL(k_rt_emit<B>, dim3(gc), dim3(kGroupThreads), 0, st, a, bt);
-  hipLaunchKernelGGL(k_rt_end<B>, dim3(n_runs), dim3(64), 0, st, a, bt);
 }
 
 // Batch workspace: descriptors, the two start tables, result headers, flags.
