@@ -15,13 +15,10 @@
 // No polygon is edited: each candidate's bisector is cut down to the part
 // that every other candidate allows (two bounds kept as fractions), and the
 // candidates with a non-empty part are the cell's edges; their parts' ends
-// are the vertices.  The candidates (in LDS: 10 slots per cell, 16 for the
-// few cells that need more, and the 4 mirrors of a walled box in registers)
-// are the wall mirrors and the previous neighbours; a neighbour's neighbour
-// enters only
-// when its bisector crosses the cell those give (one further than twice the
-// largest vertex distance cannot, and is skipped at once).  The loops over
-// candidates have straight-line bodies, so the lanes of a wave stay together.
+// are the vertices.  The candidates (slots in LDS) are the wall mirrors and
+// the previous neighbours; a neighbour's neighbour enters only when its
+// bisector crosses the cell those give (one further than twice the largest
+// vertex distance cannot, and is skipped at once).
 //
 // Most cells keep their neighbours from one step to the next; for those a
 // cheaper proof suffices (k_rt_vertex: each vertex of the previous ring's
@@ -33,9 +30,8 @@
 //                 new points in pairs
 //   k_rt_vertex   one thread per cell: the cell from its previous ring, when
 //                 every vertex passes (else queued for the clip)
-//   k_rt_clip     one thread per queued cell: the cell's edges, area, centroid
-//                 (twice: 10 candidate slots over the queue, then 16 for the
-//                 cells left over)
+//   k_rt_clip     a group of lanes per queued cell: the cell's edges, area,
+//                 centroid
 //   k_rt_classify keep / own each slot by the input stage's rules, check
 //                 each kept edge against the neighbour's slot, count
 //   k_rt_scan_*   prefix sums of the counts (within and over blocks of cells),
@@ -45,6 +41,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <vector>
@@ -57,22 +54,16 @@ constexpr uint32_t kMask = 0x0FFFFFFFu;
 constexpr int kShift = 28;
 constexpr int kMaxFan = 20;    // edges of a finished cell (RICH_RETESS_FAN beyond)
 static_assert(kMaxFan <= 64, "a kept slot's rank fits the six upper bits of its flag byte");
-// Candidate slots of a cell in LDS (neighbours and entrants): the clip runs
-// with kSlotsFast of them, which lets a compute unit hold 3 waves per SIMD
-// (LDS bound: 2.5 with 12); the few cells that need more are marked and
-// clipped again by a second launch with kSlotsWide.
-constexpr int kSlotsFast = 10;
-constexpr int kSlotsWide = 16;
-constexpr int32_t kDegRetry = -1;   // deg[i] of a cell left to the wide launch
+// Candidates of a cell besides the 4 mirrors of a walled box: neighbours in
+// the previous mesh, and the neighbours' neighbours that entered.
+constexpr int kSlots = 16;
 constexpr int32_t kDegClip = -2;    // deg[i] of a cell the vertex check left to the clip
 // The cells the vertex check leaves are queued for the clip in kSeg
 // segments (block b of a run appends to segment b % kSeg), each with its own
 // counter on its own 128-byte line, so that the blocks' appends do not all
-// meet on one address; the clip then runs dense waves over the queue.
+// meet on one address; the clip's blocks then take them from there.
 constexpr int kSeg = 64;
 constexpr int kSegStride = 32;      // int32 counters 128 bytes apart
-constexpr int kRetry = 1 << 30;     // (private bit) more candidates than slots
-                               // (a walled box adds its 4 mirrors, held in registers)
 constexpr int kRingMax = 64;   // CSR entries read per cell of the previous mesh
 constexpr int kThreads = 64;
 constexpr int kScanThreads = 1024;
@@ -231,74 +222,31 @@ __global__ __launch_bounds__(kThreads) void k_rt_begin(Args one, Batch bt) {
 // ---------------------------------------------------------------------------
 // the cell of one point
 // ---------------------------------------------------------------------------
-// A lane's candidate slots in LDS: slot u of the lane holds the displacement d
-// from r_i to a generating point and its id (cell | code << 28); slot u of
-// lane t lives at [u * kThreads + t], so a wave's accesses to one slot are
-// consecutive.
-// Slots below BASE are not in LDS (a walled box's mirrors, held in
-// registers); slot u >= BASE lives at LDS slot u - BASE.
-template <int BASE>
-struct Slots {
-  double* dx;
-  double* dy;
-  int32_t* id;
-  __device__ double& x(int u) const { return dx[(u - BASE) * kThreads]; }
-  __device__ double& y(int u) const { return dy[(u - BASE) * kThreads]; }
-  __device__ int32_t& n(int u) const { return id[(u - BASE) * kThreads]; }
-};
-
+// Counter-clockwise order of directions: the upper half-plane (from angle 0
+// inclusive) before the lower one, then by the sign of the cross product.
+__device__ __forceinline__ bool ccw_before(double ax, double ay, double bx, double by) {
+  const int ha = (ay < 0.0 || (ay == 0.0 && ax < 0.0)) ? 1 : 0;
+  const int hb = (by < 0.0 || (by == 0.0 && bx < 0.0)) ? 1 : 0;
+  if (ha != hb) return ha < hb;
+  return ax * by - ay * bx > 0.0;
+}
 
 // The part of the bisector of displacement (dux, duy) (the line
 // p.d = |d|^2/2, parametrised p(t) = d/2 + t (-duy, dux), t increasing
 // counter-clockwise about r_i) that satisfies p.d_v <= |d_v|^2/2 for every
-// slot v of mask vm except `self`: [t_lo, t_hi].  The bounds are kept as
-// fractions and compared by cross-multiplication, so the loop divides
-// nothing.  Returns false when that part is empty, or when a slot of the
-// same id comes before `self` (a duplicate); *bounded is false when one end
-// is open (the slots do not enclose the point).
-template <bool WALLS>
-__device__ __forceinline__ bool bisector_part(const Slots<WALLS ? 4 : 0>& S, double wy0,
-                                              double wx1, double wy2, double wx3, uint32_t vm,
-                                              int nv, int self, double dux, double duy,
-                                              int32_t idu, double& tlo, double& thi,
-                                              bool& bounded) {
-  const double mux = 0.5 * dux, muy = 0.5 * duy;
-  const double eux = -duy, euy = dux;
-  // No bound yet is hn / hd = +inf and ln / ld = -inf: the first finite
-  // bound of each side then wins its comparison (b and a are finite), so
-  // no flag tracks whether a side is bounded.
+// candidate v it was cut by: [lo, hi].  The bounds are kept as fractions and
+// compared by cross-multiplication, so a cut divides nothing, and no bound
+// yet is hn / hd = +inf and ln / ld = -inf: the first finite bound of each
+// side then wins its comparison (b and a are finite), so no flag tracks
+// whether a side is bounded.
+struct Part {
+  double mux, muy, eux, euy;
   double ln = -INFINITY, ld = 1.0, hn = INFINITY, hd = 1.0;
   bool empty = false;
-  // straight-line bodies (selects, no branches); the mirrors' constraints
-  auto cut = [&](double dvx, double dvy, bool act) {
-    const double a0 = eux * dvx + euy * dvy;
-    const double b0 = 0.5 * (dvx * dvx + dvy * dvy) - (mux * dvx + muy * dvy);
-    const double a = act ? a0 : 0.0;
-    const double b = act ? b0 : 1.0;
-    // a > 0: t <= b / a;  a < 0: t >= (-b) / (-a);  a = 0, b < 0: no t
-    const bool up = a > 0.0 && b * hd < hn * a;
-    hn = up ? b : hn;
-    hd = up ? a : hd;
-    const bool dn = a < 0.0 && -b * ld > ln * -a;
-    ln = dn ? -b : ln;
-    ld = dn ? -a : ld;
-    empty = empty || (a == 0.0 && b < 0.0);
-  };
-  constexpr int BASE = WALLS ? 4 : 0;
-  if constexpr (WALLS) {  // the mirrors (0, wy0), (wx1, 0), (0, wy2), (wx3, 0) first
-    cut(0.0, wy0, (vm & 1u) && self != 0);
-    cut(wx1, 0.0, ((vm >> 1) & 1u) && self != 1);
-    cut(0.0, wy2, ((vm >> 2) & 1u) && self != 2);
-    cut(wx3, 0.0, ((vm >> 3) & 1u) && self != 3);
-  }
-  // then the lane's LDS slots
-#pragma unroll 4
-  for (int v = BASE; v < nv; ++v) {
-    const double dvx = S.x(v), dvy = S.y(v);
-    const bool use = ((vm >> v) & 1u) && v != self;
-    const bool same = use && S.n(v) == idu;
-    empty = empty || (same && v < self);
-    const bool act = use && !same;
+  __device__ Part(double dux, double duy)
+      : mux(0.5 * dux), muy(0.5 * duy), eux(-duy), euy(dux) {}
+  // straight-line (selects, no branches)
+  __device__ __forceinline__ void cut(double dvx, double dvy, bool act) {
     const double a0 = eux * dvx + euy * dvy;
     const double b0 = 0.5 * (dvx * dvx + dvy * dvy) - (mux * dvx + muy * dvy);
     const double a = act ? a0 : 0.0;
@@ -312,12 +260,375 @@ __device__ __forceinline__ bool bisector_part(const Slots<WALLS ? 4 : 0>& S, dou
     ld = dn ? -a : ld;
     empty = empty || (a == 0.0 && b < 0.0);
   }
-  bounded = ln != -INFINITY && hn != INFINITY;
-  if (empty || !bounded || !(ln * hd < hn * ld)) return false;
-  tlo = ln / ld;
-  thi = hn / hd;
-  return true;
+  // false when one end is open (the candidates do not enclose the point)
+  __device__ __forceinline__ bool bounded() const { return ln != -INFINITY && hn != INFINITY; }
+  __device__ __forceinline__ bool live() const { return !empty && bounded() && ln * hd < hn * ld; }
+};
+
+// The cells of a queue, kClipLanes lanes each: lane l holds candidates l and
+// l + kClipLanes, so the trials of every candidate against every other one,
+// a serial chain of hundreds of operations and loads for one lane, run side
+// by side, and the neighbours' neighbours are loaded 48 at a time.  A small
+// mesh queues a wave or two of cells, and that chain on an otherwise idle
+// chip is its time: one lane per cell took 143 us for 600 cells of a 64 x 64
+// tube, this 32 us; 205 -> 111 us for 60 113 cells of a 511 x 511 one.  Of
+// 370 000 cells (2048 x 2048 wave) the vector ALU is the bound (about 2000
+// instructions per wave of 4 cells) and both take 450-530 us.
+constexpr int kClipLanes = 16;
+constexpr int kClipThreads = 256;
+constexpr int kClipCells = kClipThreads / kClipLanes;   // cells of a block at a time
+constexpr int kClipMaxBlocks = kSeg * 32;               // of one run: the blocks stride
+
+// A cell's candidates in LDS: displacement from r_i to the generating point
+// and its id (cell | code << 28), read by the whole group.  (The size of a
+// group's block keeps the four groups of a wave on different banks.)
+template <int NS>
+struct ClipSlots {
+  double dx[NS], dy[NS];
+  double c[NS], sx[NS], sy[NS];   // shoelace terms of the live ones
+  int32_t id[NS];
+  int32_t row[kClipLanes], pre[kClipLanes];   // ring members' CSR rows, entries before each
+};
+
+// The lanes of one wave read what others of it wrote.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
+// This group's bits of a ballot.
+__device__ __forceinline__ uint32_t clip_bits(bool v) {
+  const unsigned long long m = __ballot(v);
+  return (uint32_t)(m >> (threadIdx.x & 63 & ~(kClipLanes - 1))) & ((1u << kClipLanes) - 1u);
+}
+
+// One queued cell.  With walls, slots 0-3 hold the point's mirrors (they
+// bound it); then come the cell's neighbours in the previous mesh; the first
+// pass finds the polygon those allow.  The neighbours' neighbours then enter
+// only when their bisector crosses that polygon, in CSR order; the second
+// pass gives the cell, its area, centroid and edges in counter-clockwise
+// order.
+template <bool WALLS>
+__device__ void clip_cell(const Args& a, int i, ClipSlots<kSlots + (WALLS ? 4 : 0)>& S) {
+  constexpr int BASE = WALLS ? 4 : 0;   // mirror slots
+  constexpr int NS = kSlots + BASE;     // candidates per cell
+  static_assert(NS <= 2 * kClipLanes && NS <= kMaxFan, "two candidates per lane");
+  const int l = (int)threadIdx.x & (kClipLanes - 1);
+  const double xi = a.x[i], yi = a.y[i];
+  int bad = 0;
+  if (WALLS) {
+    if (!(xi > a.x0 && xi < a.x1 && yi > a.y0 && yi < a.y1)) bad |= RICH_RETESS_POINT;
+    // the point's mirrors across the walls y0, x1, y1, x0
+    if (l < 4) {
+      S.dx[l] = l == 1 ? 2.0 * (a.x1 - xi) : (l == 3 ? 2.0 * (a.x0 - xi) : 0.0);
+      S.dy[l] = l == 0 ? 2.0 * (a.y0 - yi) : (l == 2 ? 2.0 * (a.y1 - yi) : 0.0);
+      S.id[l] = pack(i, l == 0 ? kWallY0 : l == 1 ? kWallX1 : l == 2 ? kWallY1 : kWallX0);
+    }
+  } else {
+    // no bounds: the neighbours enclose the point (a cell they leave open
+    // is reported, and rebuilt on the host)
+    if (!(xi >= a.x0 && xi < a.x1 && yi >= a.y0 && yi < a.y1)) bad |= RICH_RETESS_POINT;
+  }
+  // displacement of point (xc, yc) of cell c from r_i (nearest periodic
+  // image) and its id
+  auto displacement = [&](int c, double xc, double yc, double& dx, double& dy) -> int32_t {
+    dx = xc - xi;
+    dy = yc - yi;
+    int code = 0;
+    if (!WALLS) {
+      int sx = 0, sy = 0;
+      if (dx > 0.5 * a.Lx) { dx -= a.Lx; sx = -1; } else if (dx < -0.5 * a.Lx) { dx += a.Lx; sx = 1; }
+      if (dy > 0.5 * a.Ly) { dy -= a.Ly; sy = -1; } else if (dy < -0.5 * a.Ly) { dy += a.Ly; sy = 1; }
+      if (sx != 0 || sy != 0) code = shift_code(sx, sy);
+    }
+    return pack(c, code);
+  };
+
+  // the ring: lane l loads CSR entry l (-1: past the end, out of range, or
+  // the cell itself, as a wall's entry is) and that neighbour's own CSR row
+  int k0 = 0, k1 = 0;
+  if (!bad) {
+    k0 = a.p_off[i];
+    k1 = a.p_off[i + 1];
+    if (k0 < 0 || k1 < k0 || k1 > a.p_n_csr) {
+      bad |= RICH_RETESS_CLIP;
+      k1 = k0;
+    } else if (k1 - k0 > kSlots) {
+      bad |= RICH_RETESS_FAN;
+      k1 = k0;
+    }
+  }
+  int c = l < k1 - k0 ? prev_neighbour(a, k0 + l) : -1;
+  if (c >= a.n || c == i) c = -1;
+  int row = 0, len = 0;
+  if (c >= 0) {
+    row = a.p_off[c];
+    len = a.p_off[c + 1] - row;
+    if (row < 0 || len < 0 || row + (int64_t)len > a.p_n_csr || len > kRingMax) {
+      bad |= RICH_RETESS_CLIP;
+      len = 0;
+    }
+  }
+  for (int o = kClipLanes / 2; o > 0; o >>= 1) bad |= __shfl_xor(bad, o);
+  const uint32_t ring = clip_bits(c >= 0);
+  int nv = BASE + __popc(ring);
+  if (c >= 0) {
+    const int u = BASE + __popc(ring & ((1u << l) - 1u));
+    const double2 p = a.xy[c];
+    double dx, dy;
+    S.id[u] = displacement(c, p.x, p.y, dx, dy);
+    S.dx[u] = dx;
+    S.dy[u] = dy;
+  }
+  int pre = len;   // entries of the ring members before this one
+  for (int o = 1; o < kClipLanes; o <<= 1) {
+    const int v = __shfl_up(pre, o, kClipLanes);
+    if (l >= o) pre += v;
+  }
+  const int total = __shfl(pre, kClipLanes - 1, kClipLanes);
+  pre -= len;
+  S.row[l] = row;
+  S.pre[l] = pre;
+  wave_sync();
+
+  // first pass: the polygon of the bounds and the first ring, and the
+  // largest distance of its vertices
+  uint32_t em = 0;
+  double r2 = 0.0;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int u = l + h * kClipLanes;
+    bool live = false;
+    if (!bad && u < nv) {
+      const double dux = S.dx[u], duy = S.dy[u];
+      const int32_t idu = S.id[u];
+      Part p(dux, duy);
+      for (int v = 0; v < nv; ++v) {
+        const bool same = v != u && S.id[v] == idu;   // a duplicate: the first stands
+        p.empty = p.empty || (same && v < u);
+        p.cut(S.dx[v], S.dy[v], v != u && !same);
+      }
+      live = p.live();
+      if (live) {
+        const double t = p.hn / p.hd;
+        const double px = 0.5 * dux - t * duy, py = 0.5 * duy + t * dux;
+        r2 = fmax(r2, px * px + py * py);
+      } else if (!p.bounded()) {
+        bad |= RICH_RETESS_CLIP;
+      }
+    }
+    em |= clip_bits(live) << (h * kClipLanes);
+  }
+  for (int o = kClipLanes / 2; o > 0; o >>= 1) {
+    r2 = fmax(r2, __shfl_xor(r2, o));
+    bad |= __shfl_xor(bad, o);
+  }
+
+  // second ring: a candidate enters when its bisector crosses the polygon
+  // of the slots (one further than twice the largest vertex distance
+  // cannot, and is skipped at once), which includes those that entered
+  // before it.  The lanes try their candidates against the slots together;
+  // those that cross then enter in order, each one cutting the ones after it.
+  constexpr int CH = 3;   // candidates of a lane whose loads are in flight together
+  for (int t0 = 0; t0 < total && !bad; t0 += CH * kClipLanes) {
+    int cc[CH];
+    double2 cp[CH];
+#pragma unroll
+    for (int h = 0; h < CH; ++h) {
+      const int t = t0 + h * kClipLanes + l;
+      int m = 0;   // the ring member whose row holds entry t: the last with pre <= t
+#pragma unroll
+      for (int s = kClipLanes / 2; s > 0; s >>= 1)
+        if (S.pre[m + s] <= t) m += s;
+      cc[h] = t < total ? prev_neighbour(a, S.row[m] + t - S.pre[m]) : -1;
+      if (cc[h] >= a.n || cc[h] == i) cc[h] = -1;
+    }
+#pragma unroll
+    for (int h = 0; h < CH; ++h) cp[h] = a.xy[cc[h] < 0 ? 0 : cc[h]];
+#pragma unroll
+    for (int h = 0; h < CH; ++h) {
+      double dx, dy;
+      const int32_t id = displacement(cc[h], cp[h].x, cp[h].y, dx, dy);
+      bool on = cc[h] >= 0 && !(4.0 * r2 <= dx * dx + dy * dy);
+      for (int v = BASE; v < nv; ++v) on = on && S.id[v] != id;
+      if (clip_bits(on) == 0u) continue;
+      Part p(dx, dy);
+      for (int v = 0; v < nv; ++v) p.cut(S.dx[v], S.dy[v], true);
+      uint32_t in;
+      while ((in = clip_bits(on && p.live())) != 0u && !bad) {
+        const int f = __ffs(in) - 1;
+        const double fx = __shfl(dx, f, kClipLanes), fy = __shfl(dy, f, kClipLanes);
+        const int32_t fid = __shfl(id, f, kClipLanes);
+        // a new slot, else one whose bisector bounds nothing (it stays
+        // redundant as candidates are added; a mirror is never reused)
+        int u = nv;
+        if (nv < NS) {
+          ++nv;
+        } else {
+          const uint32_t usable = ~em & ((1u << NS) - 1u) & ~((1u << BASE) - 1u);
+          u = __ffs(usable) - 1;
+          if (usable == 0u) {
+            bad |= RICH_RETESS_FAN;
+            break;
+          }
+        }
+        em |= 1u << u;   // holds a cutting candidate now: not reusable
+        wave_sync();
+        if (l == f) {
+          S.dx[u] = dx;
+          S.dy[u] = dy;
+          S.id[u] = id;
+        }
+        wave_sync();
+        on = on && id != fid;
+        p.cut(fx, fy, on);
+      }
+    }
+  }
+
+  rich_cell cr;
+  cr.px = xi;
+  cr.py = yi;
+  cr.pad = 0.0;
+  cr.area = 0.0;
+  cr.sx = xi;
+  cr.sy = yi;
+  // second pass: each candidate's part of its bisector.  A live one is an
+  // edge: its place is its counter-clockwise rank among all the candidates
+  // (same direction: by slot) less the ranks of those that bound nothing,
+  // and its triangle with the point is added to the shoelace sums in slot
+  // order.
+  uint32_t fm = 0, holes = 0;
+  int rank[2] = {0, 0};
+  double len_[2] = {0.0, 0.0}, mx[2] = {0.0, 0.0}, my[2] = {0.0, 0.0};
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int u = l + h * kClipLanes;
+    bool live = false;
+    if (!bad && u < nv) {
+      const double dux = S.dx[u], duy = S.dy[u];
+      const int32_t idu = S.id[u];
+      Part p(dux, duy);
+      for (int v = 0; v < nv; ++v) {
+        const double dvx = S.dx[v], dvy = S.dy[v];
+        const bool other = v != u;
+        const bool same = other && S.id[v] == idu;
+        p.empty = p.empty || (same && v < u);
+        p.cut(dvx, dvy, other && !same);
+        rank[h] += (other && (ccw_before(dvx, dvy, dux, duy) ||
+                              (v < u && !ccw_before(dux, duy, dvx, dvy)))) ? 1 : 0;
+      }
+      live = p.live();
+      if (live) {
+        const double tlo = p.ln / p.ld, thi = p.hn / p.hd;
+        const double ux = 0.5 * dux - tlo * duy, uy = 0.5 * duy + tlo * dux;
+        const double wx = 0.5 * dux - thi * duy, wy = 0.5 * duy + thi * dux;
+        S.c[u] = ux * wy - uy * wx;
+        S.sx[u] = ux + wx;
+        S.sy[u] = uy + wy;
+        const double ex = wx - ux, ey = wy - uy;
+        len_[h] = sqrt(ex * ex + ey * ey);
+        mx[h] = xi + 0.5 * (ux + wx);
+        my[h] = yi + 0.5 * (uy + wy);
+      } else {
+        if (!p.bounded()) bad |= RICH_RETESS_CLIP;
+        holes |= 1u << rank[h];
+      }
+    }
+    fm |= clip_bits(live) << (h * kClipLanes);
+  }
+  for (int o = kClipLanes / 2; o > 0; o >>= 1) {
+    holes |= __shfl_xor(holes, o);
+    bad |= __shfl_xor(bad, o);
+  }
+  const int deg = __popc(fm);
+  if (deg < 3) bad |= RICH_RETESS_CLIP;
+  if (bad) {
+    if (l == 0) {
+      atomicOr(&a.hdr->flags, bad);
+      a.deg[i] = 0;
+      a.cells[i] = cr;
+    }
+    return;
+  }
+  const size_t s0 = (size_t)i * kMaxFan;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int u = l + h * kClipLanes;
+    if ((fm >> u) & 1u) {
+      const int q = rank[h] - __popc(holes & ((1u << rank[h]) - 1u));   // < NS <= kMaxFan
+      a.s_nb[s0 + q] = S.id[u];
+      double* g = a.s_geo + 3 * (s0 + q);
+      g[0] = len_[h];
+      g[1] = mx[h];
+      g[2] = my[h];
+    }
+  }
+  wave_sync();
+  double A2 = 0.0, cx = 0.0, cy = 0.0;
+  for (int v = 0; v < nv; ++v) {
+    if (!((fm >> v) & 1u)) continue;
+    const double cv = S.c[v];
+    A2 += cv;
+    cx += S.sx[v] * cv;
+    cy += S.sy[v] * cv;
+  }
+  if (l == 0) {
+    a.deg[i] = deg;
+    cr.area = 0.5 * A2;
+    cr.sx = xi + cx / (3.0 * A2);
+    cr.sy = yi + cy / (3.0 * A2);
+    a.cells[i] = cr;
+  }
+}
+
+// Block b of a run takes entries of queue segment b % kSeg, as many cells at
+// a time as it has groups.  Each launch serves one kind of run (a batch of
+// both kinds takes two launches), so a run's results never depend on the
+// other runs.
+template <bool B, bool WALLS>
+__global__ __launch_bounds__(kClipThreads) void k_rt_clip(Args one, Batch bt) {
+  __shared__ ClipSlots<kSlots + (WALLS ? 4 : 0)> s_slots[kClipCells];
+  int blk, nblk = gridDim.x;
+  const Args& a = block_run<B>(one, bt.cstart, bt, blk);
+  if ((a.bc == (int)RICH_BOUNDARY_PERIODIC) == WALLS) return;  // the other launch's run
+  if (B) nblk = (a.n + kThreads - 1) / kThreads;
+  const int seg = blk % kSeg;
+  const int queued = min(a.qcnt[seg * kSegStride], a.qcap);
+  const int group = (int)threadIdx.x / kClipLanes;
+  const int step = kClipCells * ((nblk - seg + kSeg - 1) / kSeg);   // the segment's blocks
+  for (int e = (blk / kSeg) * kClipCells + group; e < queued; e += step) {
+    const int i = a.queue[(size_t)seg * a.qcap + e];
+    if (i < 0 || i >= a.n || a.deg[i] != kDegClip) continue;
+    clip_cell<WALLS>(a, i, s_slots[group]);
+    wave_sync();   // the slots are taken by the next cell
+  }
+}
+
+// ---------------------------------------------------------------------------
+// the cell of one point when it keeps its previous neighbours
+// ---------------------------------------------------------------------------
+// Under the small moves of a time step most cells keep their neighbours, and
+// the previous mesh lists them counter-clockwise.  Then the cell's vertices
+// are the points equidistant from r_i and two consecutive neighbours, and
+// the cell is proved by checking each vertex against every other candidate
+// (one dot product), instead of cutting every bisector by every other one.
+// The proof holds in exact arithmetic when every consecutive pair turns
+// counter-clockwise by less than half a turn (and more than kVertexSin), the
+// ring winds once, and every vertex lies inside every other candidate's half
+// plane by a margin far above the rounding of the test (kVertexMargin of the
+// candidate's half squared distance plus the largest squared vertex distance;
+// with one margin for all vertices, the vertex of largest projection on a
+// candidate decides for all of them): the polygon is then the intersection of the
+// candidates' half planes, and its edges (all of positive length, well above
+// the input stage's cut for dropping one) are the ring's neighbours.  The
+// candidates are the clip's: the mirrors of a walled box, the ring, and the
+// neighbours' neighbours that could reach a vertex.  A cell that fails any
+// of these tests (a new neighbour, a lost one, a near-degenerate vertex, a
+// ring longer than kRingFast or next to a wall) is queued for the clip
+// launches (deg = kDegClip), which decide every case.
+constexpr int kRingFast = 8;            // ring entries held in registers
+constexpr double kVertexMargin = 1e-9;  // relative margin of every vertex test
+constexpr double kVertexSin = 0.05;     // least sine of a consecutive pair's angle
 
 // The cells and points of CSR entries k0 .. k0+CH-1 of the previous mesh
 // (those below k1), loaded level by level: entries, then their edges, then
@@ -348,353 +659,6 @@ __device__ __forceinline__ void ring_chunk(const Args& a, int k0, int k1, int se
     cy[m] = p.y;
   }
 }
-
-// Counter-clockwise order of directions: the upper half-plane (from angle 0
-// inclusive) before the lower one, then by the sign of the cross product.
-__device__ __forceinline__ bool ccw_before(double ax, double ay, double bx, double by) {
-  const int ha = (ay < 0.0 || (ay == 0.0 && ax < 0.0)) ? 1 : 0;
-  const int hb = (by < 0.0 || (by == 0.0 && bx < 0.0)) ? 1 : 0;
-  if (ha != hb) return ha < hb;
-  return ax * by - ay * bx > 0.0;
-}
-
-// One thread per cell that the vertex check left (deg = kDegClip; the
-// other lanes return at once).  With walls, slots 0-3 hold the point's mirrors
-// (they bound it); then come the cell's neighbours in the previous mesh; the
-// first pass finds the polygon those allow.  The neighbours' neighbours then enter only when their
-// bisector crosses that polygon, into slots that bound nothing; the second
-// pass gives the cell, its area, centroid and edges in counter-clockwise
-// order.  Every slot v is tried against every slot u (a fixed loop with no
-// polygon to edit), so lanes of a wave stay together.  The candidate slots
-// are the block's LDS, which sets how many waves a compute unit holds: a cell
-// has SL of them, and a walled box's four mirrors (slots 0-3) are held in
-// registers, so both kinds of run give SL slots to neighbours and entrants.
-// The first launch (SL = kSlotsFast) leaves a cell that needs more slots
-// marked (deg = kDegRetry) instead of failing the mesh; the second (WIDE,
-// SL = kSlotsWide) clips only those cells, with the same arithmetic, and
-// fails the mesh if even that is not enough.  Each launch serves one kind of
-// run (a batch of both kinds takes two launches of each), so a run's results
-// never depend on the other runs.
-template <bool B, bool WALLS, int SL, bool WIDE>
-__global__ __launch_bounds__(kThreads) void k_rt_clip(Args one, Batch bt) {
-  constexpr int BASE = WALLS ? 4 : 0;   // mirror slots, held in registers
-  constexpr int NS = SL + BASE;         // candidates per cell
-  static_assert(NS <= 32, "slot masks are 32-bit");
-  constexpr int kFull = WIDE ? RICH_RETESS_FAN : kRetry;   // out of slots
-  __shared__ double s_dx[SL * kThreads], s_dy[SL * kThreads];
-  __shared__ int32_t s_id[SL * kThreads];
-  int blk;
-  const Args& a = block_run<B>(one, bt.cstart, bt, blk);
-  if ((a.bc == (int)RICH_BOUNDARY_PERIODIC) == WALLS) return;  // the other launch's run
-  int i;
-  if (WIDE) {
-    i = blk * kThreads + threadIdx.x;
-    if (i >= a.n || a.deg[i] != kDegRetry) return;   // done by an earlier launch
-  } else {
-    // entry e of queue segment blk % kSeg (e < qcap for every block of the run)
-    const int seg = blk % kSeg;
-    const int e = (blk / kSeg) * kThreads + (int)threadIdx.x;
-    if (e >= a.qcnt[seg * kSegStride]) return;
-    i = a.queue[(size_t)seg * a.qcap + e];
-    if (i < 0 || i >= a.n || a.deg[i] != kDegClip) return;
-  }
-  const Slots<BASE> S{s_dx + threadIdx.x, s_dy + threadIdx.x, s_id + threadIdx.x};
-  // a walled box: the point's mirrors across the walls y0, x1, y1, x0 (slots
-  // 0-3) are the displacements (0, wy0), (wx1, 0), (0, wy2), (wx3, 0)
-  double wy0 = 0.0, wx1 = 0.0, wy2 = 0.0, wx3 = 0.0;
-  const double xi = a.x[i], yi = a.y[i];
-  int bad = 0;
-  constexpr bool periodic = !WALLS;
-  // live slots are 0 .. nv-1; vm marks those that hold a candidate
-  int nv = 0;
-  uint32_t vm = 0u;
-  if (periodic) {
-    // no bounds: the neighbours enclose the point (a cell they leave open
-    // is reported, and rebuilt on the host)
-    if (!(xi >= a.x0 && xi < a.x1 && yi >= a.y0 && yi < a.y1)) bad |= RICH_RETESS_POINT;
-  } else {
-    if (!(xi > a.x0 && xi < a.x1 && yi > a.y0 && yi < a.y1)) bad |= RICH_RETESS_POINT;
-    // the point's mirrors across the walls y0, x1, y1, x0
-    wy0 = 2.0 * (a.y0 - yi);
-    wx1 = 2.0 * (a.x1 - xi);
-    wy2 = 2.0 * (a.y1 - yi);
-    wx3 = 2.0 * (a.x0 - xi);
-    nv = 4;
-    vm = 0xFu;
-  }
-  // candidate u: displacement and id (with walls, u < 4 is a mirror)
-  auto cand = [&](int u, double& dx, double& dy) -> int32_t {
-    if (WALLS && u < 4) {
-      dx = u == 1 ? wx1 : (u == 3 ? wx3 : 0.0);
-      dy = u == 0 ? wy0 : (u == 2 ? wy2 : 0.0);
-      return pack(i, u == 0 ? kWallY0 : u == 1 ? kWallX1 : u == 2 ? kWallY1 : kWallX0);
-    }
-    dx = S.x(u);
-    dy = S.y(u);
-    return S.n(u);
-  };
-
-  // displacement of cell c from r_i (nearest periodic image) and its id
-  auto displacement = [&](int c, double xc, double yc, double& dx, double& dy) -> int32_t {
-    dx = xc - xi;
-    dy = yc - yi;
-    int code = 0;
-    if (periodic) {
-      int sx = 0, sy = 0;
-      if (dx > 0.5 * a.Lx) { dx -= a.Lx; sx = -1; } else if (dx < -0.5 * a.Lx) { dx += a.Lx; sx = 1; }
-      if (dy > 0.5 * a.Ly) { dy -= a.Ly; sy = -1; } else if (dy < -0.5 * a.Ly) { dy += a.Ly; sy = 1; }
-      if (sx != 0 || sy != 0) code = shift_code(sx, sy);
-    }
-    return pack(c, code);
-  };
-
-  int k0 = 0, k1 = 0;
-  if (!bad) {
-    k0 = a.p_off[i];
-    k1 = a.p_off[i + 1];
-    if (k0 < 0 || k1 < k0 || k1 > a.p_n_csr) {
-      bad |= RICH_RETESS_CLIP;
-      k1 = k0;
-    } else if (k1 - k0 > NS - nv) {
-      bad |= kFull;
-      k1 = k0;
-    }
-  }
-  constexpr int CH = 8;  // candidates loaded together
-  for (int k = k0; k < k1; k += CH) {
-    int c[CH];
-    double cx[CH], cy[CH];
-    ring_chunk<CH>(a, k, k1, i, c, cx, cy);
-#pragma unroll
-    for (int m = 0; m < CH; ++m) {
-      if (c[m] < 0) continue;
-      double dx, dy;
-      S.n(nv) = displacement(c[m], cx[m], cy[m], dx, dy);
-      S.x(nv) = dx;
-      S.y(nv) = dy;
-      vm |= 1u << nv;
-      ++nv;
-    }
-  }
-
-  // first pass: the polygon of the bounds and the first ring, and the
-  // largest distance of its vertices
-  uint32_t em = 0;
-  double r2 = 0.0;
-  if (!bad) {
-    for (int u = 0; u < nv; ++u) {
-      if (!((vm >> u) & 1u)) continue;
-      double tlo, thi;
-      bool bounded;
-      double dux, duy;
-      const int32_t idu = cand(u, dux, duy);
-      if (bisector_part<WALLS>(S, wy0, wx1, wy2, wx3, vm, nv, u, dux, duy, idu, tlo, thi, bounded)) {
-        em |= 1u << u;
-        const double px = 0.5 * dux - thi * duy, py = 0.5 * duy + thi * dux;
-        r2 = fmax(r2, px * px + py * py);
-      } else if (!bounded) {
-        bad |= RICH_RETESS_CLIP;
-      }
-    }
-  }
-
-  // second ring: a candidate enters when its bisector crosses the polygon
-  // (a candidate further than twice the largest vertex distance cannot).
-  // The cheap tests (distance, already a slot) run as the candidates are
-  // loaded; the survivors wait in a short queue and meet the polygon test
-  // in their order when the queue is full or the ring is done, so that the
-  // wave runs the costly test a few times per cell instead of once per
-  // candidate position (whichever lane of the wave needed it).  Candidates
-  // meet the test in the same order, against the same slots, as one by one.
-  constexpr int QN = 4;   // 2, 6 and 8 measured slower
-  double qx[QN], qy[QN];
-  int32_t qid[QN];
-  int qn = 0;
-  auto flush = [&]() {
-#pragma unroll
-    for (int p = 0; p < QN; ++p) {
-      if (p >= qn || bad) continue;
-      double tlo, thi;
-      bool bounded;
-      if (!bisector_part<WALLS>(S, wy0, wx1, wy2, wx3, vm, nv, -1, qx[p], qy[p], qid[p], tlo,
-                                thi, bounded))
-        continue;
-      // a new slot, else one whose bisector bounds nothing (it stays
-      // redundant as candidates are added)
-      int u = nv;
-      if (nv < NS) {
-        ++nv;
-      } else {
-        // (a mirror is never reused)
-        const uint32_t usable = ~em & ((1u << NS) - 1u) & ~((1u << BASE) - 1u);
-        if (usable == 0u) {
-          bad |= kFull;
-          continue;
-        }
-        u = __ffs(usable) - 1;
-      }
-      S.x(u) = qx[p];
-      S.y(u) = qy[p];
-      S.n(u) = qid[p];
-      vm |= 1u << u;
-      em |= 1u << u;   // holds a cutting candidate now: not reusable
-    }
-    qn = 0;
-  };
-  for (int k = k0; k < k1 && !bad; ++k) {
-    const int j = prev_neighbour(a, k);
-    if (j < 0 || j >= a.n || j == i) continue;
-    const int l0 = a.p_off[j], l1 = a.p_off[j + 1];
-    if (l0 < 0 || l1 < l0 || l1 > a.p_n_csr || l1 - l0 > kRingMax) {
-      bad |= RICH_RETESS_CLIP;
-      break;
-    }
-    for (int l = l0; l < l1 && !bad; l += CH) {
-      int cc[CH];
-      double ccx[CH], ccy[CH];
-      ring_chunk<CH>(a, l, l1, i, cc, ccx, ccy);
-      for (int m = 0; m < CH; ++m) {
-        if (cc[m] < 0) continue;
-        double dx, dy;
-        const int32_t id = displacement(cc[m], ccx[m], ccy[m], dx, dy);
-        if (4.0 * r2 <= dx * dx + dy * dy) continue;
-        // (over every slot, the loads issued together; vm marks the live ones)
-        bool known = false;
-#pragma unroll
-        for (int v = BASE; v < NS; ++v) known = known || (v < nv && ((vm >> v) & 1u) && S.n(v) == id);
-#pragma unroll
-        for (int p = 0; p < QN; ++p) known = known || (p < qn && qid[p] == id);
-        if (known) continue;
-#pragma unroll
-        for (int p = 0; p < QN; ++p) {
-          if (p == qn) {
-            qx[p] = dx;
-            qy[p] = dy;
-            qid[p] = id;
-          }
-        }
-        if (++qn == QN) flush();
-      }
-    }
-  }
-  if (!bad) flush();
-
-  rich_cell cr;
-  cr.px = xi;
-  cr.py = yi;
-  cr.pad = 0.0;
-  if (bad) {
-    // out of slots alone: left to the wide launch; anything else fails the mesh
-    const int pub = bad & ~kRetry;
-    if (pub) atomicOr(&a.hdr->flags, pub);
-    a.deg[i] = pub ? 0 : kDegRetry;
-    cr.area = 0.0;
-    cr.sx = xi;
-    cr.sy = yi;
-    a.cells[i] = cr;
-    return;
-  }
-  // second pass: each candidate's part of its bisector.  A live one (an
-  // edge) is written at once, at its counter-clockwise rank among all the
-  // candidates (same direction: by slot), and its triangle with the point
-  // is added to the shoelace sums in slot order; the positions left by
-  // candidates that bound nothing are closed up afterwards, which leaves
-  // the live ones in counter-clockwise order.
-  uint32_t fm = 0, holes = 0;
-  double A2 = 0.0, cx = 0.0, cy = 0.0;
-  const size_t s0 = (size_t)i * kMaxFan;
-  for (int u = 0; u < nv; ++u) {
-    if (!((vm >> u) & 1u)) continue;
-    double dux, duy;
-    const int32_t idu = cand(u, dux, duy);
-    int rank = 0;
-    for (int v = 0; v < nv; ++v) {
-      if (!((vm >> v) & 1u) || v == u) continue;
-      double vx, vy;
-      cand(v, vx, vy);
-      rank += (ccw_before(vx, vy, dux, duy) || (v < u && !ccw_before(dux, duy, vx, vy))) ? 1 : 0;
-    }
-    double tlo, thi;
-    bool bounded;
-    if (!bisector_part<WALLS>(S, wy0, wx1, wy2, wx3, vm, nv, u, dux, duy, idu, tlo, thi, bounded)) {
-      if (!bounded) bad |= RICH_RETESS_CLIP;
-      holes |= 1u << rank;
-      continue;
-    }
-    fm |= 1u << u;
-    const double ux = 0.5 * dux - tlo * duy, uy = 0.5 * duy + tlo * dux;
-    const double wx = 0.5 * dux - thi * duy, wy = 0.5 * duy + thi * dux;
-    const double c = ux * wy - uy * wx;
-    A2 += c;
-    cx += (ux + wx) * c;
-    cy += (uy + wy) * c;
-    const double ex = wx - ux, ey = wy - uy;
-    a.s_nb[s0 + rank] = idu;   // rank < number of candidates <= NS < kMaxFan
-    double* g = a.s_geo + 3 * (s0 + rank);
-    g[0] = sqrt(ex * ex + ey * ey);
-    g[1] = xi + 0.5 * (ux + wx);
-    g[2] = yi + 0.5 * (uy + wy);
-  }
-  const int deg = __popc(fm);
-  if (deg < 3 || deg > kMaxFan) bad |= deg > kMaxFan ? RICH_RETESS_FAN : RICH_RETESS_CLIP;
-  if (!bad && holes != 0u) {
-    __threadfence_block();  // this lane's row writes above are read back below
-    const int total = __popc(vm);
-    for (int p = 0, q = 0; p < total; ++p) {
-      if ((holes >> p) & 1u) continue;
-      if (q != p) {
-        a.s_nb[s0 + q] = a.s_nb[s0 + p];
-        const double* g = a.s_geo + 3 * (s0 + p);
-        double* h = a.s_geo + 3 * (s0 + q);
-        const double g0 = g[0], g1 = g[1], g2 = g[2];
-        h[0] = g0;
-        h[1] = g1;
-        h[2] = g2;
-      }
-      ++q;
-    }
-  }
-  if (bad) {
-    atomicOr(&a.hdr->flags, bad);
-    a.deg[i] = 0;
-    cr.area = 0.0;
-    cr.sx = xi;
-    cr.sy = yi;
-    a.cells[i] = cr;
-    return;
-  }
-  a.deg[i] = deg;
-  cr.area = 0.5 * A2;
-  cr.sx = xi + cx / (3.0 * A2);
-  cr.sy = yi + cy / (3.0 * A2);
-  a.cells[i] = cr;
-}
-
-// ---------------------------------------------------------------------------
-// the cell of one point when it keeps its previous neighbours
-// ---------------------------------------------------------------------------
-// Under the small moves of a time step most cells keep their neighbours, and
-// the previous mesh lists them counter-clockwise.  Then the cell's vertices
-// are the points equidistant from r_i and two consecutive neighbours, and
-// the cell is proved by checking each vertex against every other candidate
-// (one dot product), instead of cutting every bisector by every other one.
-// The proof holds in exact arithmetic when every consecutive pair turns
-// counter-clockwise by less than half a turn (and more than kVertexSin), the
-// ring winds once, and every vertex lies inside every other candidate's half
-// plane by a margin far above the rounding of the test (kVertexMargin of the
-// candidate's half squared distance plus the largest squared vertex distance;
-// with one margin for all vertices, the vertex of largest projection on a
-// candidate decides for all of them): the polygon is then the intersection of the
-// candidates' half planes, and its edges (all of positive length, well above
-// the input stage's cut for dropping one) are the ring's neighbours.  The
-// candidates are the clip's: the mirrors of a walled box, the ring, and the
-// neighbours' neighbours that could reach a vertex.  A cell that fails any
-// of these tests (a new neighbour, a lost one, a near-degenerate vertex, a
-// ring longer than kRingFast or next to a wall) is queued for the clip
-// launches (deg = kDegClip), which decide every case.
-constexpr int kRingFast = 8;            // ring entries held in registers
-constexpr double kVertexMargin = 1e-9;  // relative margin of every vertex test
-constexpr double kVertexSin = 0.05;     // least sine of a consecutive pair's angle
 
 // (launch bounds for 4 waves per SIMD: a few registers spill, which costs
 // less than the latency 3 waves leave exposed)
@@ -1385,20 +1349,15 @@ template <bool B>
 void launch_all(const retess::Args& a, const retess::Batch& bt, int gc, int gs, int n_runs,
                 bool walls, bool periodic, hipStream_t st) {
   using namespace retess;
+  const int gq = B ? gc : std::min(gc, kClipMaxBlocks);   // (a batch's blocks find their run by gc)
   hipLaunchKernelGGL(k_rt_begin<B>, dim3(gc), dim3(kThreads), 0, st, a, bt);
   if (walls) {
     hipLaunchKernelGGL((k_rt_vertex<B, true>), dim3(gc), dim3(kThreads), 0, st, a, bt);
-    hipLaunchKernelGGL((k_rt_clip<B, true, kSlotsFast, false>), dim3(gc), dim3(kThreads), 0, st,
-                       a, bt);
-    hipLaunchKernelGGL((k_rt_clip<B, true, kSlotsWide, true>), dim3(gc), dim3(kThreads), 0, st,
-                       a, bt);
+    hipLaunchKernelGGL((k_rt_clip<B, true>), dim3(gq), dim3(kClipThreads), 0, st, a, bt);
   }
   if (periodic) {
     hipLaunchKernelGGL((k_rt_vertex<B, false>), dim3(gc), dim3(kThreads), 0, st, a, bt);
-    hipLaunchKernelGGL((k_rt_clip<B, false, kSlotsFast, false>), dim3(gc), dim3(kThreads), 0, st,
-                       a, bt);
-    hipLaunchKernelGGL((k_rt_clip<B, false, kSlotsWide, true>), dim3(gc), dim3(kThreads), 0, st,
-                       a, bt);
+    hipLaunchKernelGGL((k_rt_clip<B, false>), dim3(gq), dim3(kClipThreads), 0, st, a, bt);
   }
   hipLaunchKernelGGL(k_rt_classify<B>, dim3(gc), dim3(kGroupThreads), 0, st, a, bt);
   hipLaunchKernelGGL(k_rt_scan_local<B>, dim3(gs), dim3(kScanThreads), 0, st, a, bt);
