@@ -28,8 +28,9 @@
 // Pipeline (one launch each, all on the caller's stream):
 //   k_rt_begin    clear the result header and the queue counters, pack the
 //                 new points in pairs
-//   k_rt_vertex   one thread per cell: the cell from its previous ring, when
-//                 every vertex passes (else queued for the clip)
+//   k_rt_vertex   a group of lanes per cell: the cell from its previous ring,
+//                 when every vertex passes (else queued for the clip)
+//   k_rt_near     (large meshes) the vertices against the neighbours' neighbours
 //   k_rt_clip     a group of lanes per queued cell: the cell's edges, area,
 //                 centroid
 //   k_rt_classify keep / own each slot by the input stage's rules, check
@@ -57,13 +58,20 @@ static_assert(kMaxFan <= 64, "a kept slot's rank fits the six upper bits of its 
 // Candidates of a cell besides the 4 mirrors of a walled box: neighbours in
 // the previous mesh, and the neighbours' neighbours that entered.
 constexpr int kSlots = 16;
-constexpr int32_t kDegClip = -2;    // deg[i] of a cell the vertex check left to the clip
+constexpr int32_t kDegClip = -2;    // deg[i] of a cell that the ring check left to the clip,
+constexpr int32_t kDegNear = -3;    // of one that the check of its neighbours' neighbours did
 // The cells the vertex check leaves are queued for the clip in kSeg
 // segments (block b of a run appends to segment b % kSeg), each with its own
 // counter on its own 128-byte line, so that the blocks' appends do not all
 // meet on one address; the clip's blocks then take them from there.
 constexpr int kSeg = 64;
 constexpr int kSegStride = 32;      // int32 counters 128 bytes apart
+// From this many cells (of a call, a batch's runs together) the ring check and
+// the check of the neighbours' neighbours are launches of their own, which
+// loads less; below it one launch does both, and is the faster for it (a
+// rebuild after moves of 0.02 spacings, one launch against two: 61.5 and 63.2
+// us at 64 x 64 cells, 89 and 88 at 256 x 256, 962 and 922 at 1024 x 1024).
+constexpr int kTieredMin = 65536;
 constexpr int kRingMax = 64;   // CSR entries read per cell of the previous mesh
 constexpr int kThreads = 64;
 constexpr int kScanThreads = 1024;
@@ -117,6 +125,7 @@ struct Args {
   CPart* cpart;        // [cell blocks] classify block sums, reduced by the scan
   int32_t* qcnt;       // [kSeg * kSegStride] queue segment counters (every kSegStride-th)
   int32_t* queue;      // [kSeg][qcap] cells left to the clip
+  int32_t* nb;         // [p_n_csr] neighbour of each CSR entry of the previous mesh (or null)
   int32_t qcap;        // capacity of a segment: kThreads * ceil(cell blocks / kSeg)
   // geometry
   double x0, y0, x1, y1, Lx, Ly;
@@ -186,13 +195,16 @@ __device__ __forceinline__ bool bisector_meet(double ax, double ay, double bx, d
   return det > 0.0;
 }
 
-// Neighbour cell of CSR entry k of the previous mesh (-1 if out of range).
-__device__ __forceinline__ int prev_neighbour(const Args& a, int k) {
-  const int ent = a.p_idx[k];
+// Neighbour cell that a CSR entry of the previous mesh names (-1 if out of
+// range); of CSR entry k.
+__device__ __forceinline__ int entry_cell(const Args& a, int ent) {
   const int e = ent >> 1;
   if (ent < 0 || e >= a.p_n_edges) return -1;
-  if (ent & 1) return a.p_edges[e].i;
-  return (int)((uint32_t)a.p_edges[e].j & kMask);
+  const int2 ij = *reinterpret_cast<const int2*>(&a.p_edges[e].i);
+  return (ent & 1) ? ij.x : (int)((uint32_t)ij.y & kMask);
+}
+__device__ __forceinline__ int prev_neighbour(const Args& a, int k) {
+  return entry_cell(a, a.p_idx[k]);
 }
 
 // Clears the result header and the queue counters (each run's first block)
@@ -306,8 +318,8 @@ __device__ __forceinline__ uint32_t clip_bits(bool v) {
 // pass finds the polygon those allow.  The neighbours' neighbours then enter
 // only when their bisector crosses that polygon, in CSR order; the second
 // pass gives the cell, its area, centroid and edges in counter-clockwise
-// order.
-template <bool WALLS>
+// order.  (TIERED: the neighbours are read where the ring check wrote them.)
+template <bool WALLS, bool TIERED>
 __device__ void clip_cell(const Args& a, int i, ClipSlots<kSlots + (WALLS ? 4 : 0)>& S) {
   constexpr int BASE = WALLS ? 4 : 0;   // mirror slots
   constexpr int NS = kSlots + BASE;     // candidates per cell
@@ -357,7 +369,7 @@ __device__ void clip_cell(const Args& a, int i, ClipSlots<kSlots + (WALLS ? 4 : 
       k1 = k0;
     }
   }
-  int c = l < k1 - k0 ? prev_neighbour(a, k0 + l) : -1;
+  int c = l < k1 - k0 ? (TIERED ? a.nb[k0 + l] : prev_neighbour(a, k0 + l)) : -1;
   if (c >= a.n || c == i) c = -1;
   int row = 0, len = 0;
   if (c >= 0) {
@@ -439,7 +451,11 @@ __device__ void clip_cell(const Args& a, int i, ClipSlots<kSlots + (WALLS ? 4 : 
 #pragma unroll
       for (int s = kClipLanes / 2; s > 0; s >>= 1)
         if (S.pre[m + s] <= t) m += s;
-      cc[h] = t < total ? prev_neighbour(a, S.row[m] + t - S.pre[m]) : -1;
+      cc[h] = -1;
+      if (t < total) {
+        const int k = S.row[m] + t - S.pre[m];
+        cc[h] = TIERED ? a.nb[k] : prev_neighbour(a, k);
+      }
       if (cc[h] >= a.n || cc[h] == i) cc[h] = -1;
     }
 #pragma unroll
@@ -585,7 +601,7 @@ __device__ void clip_cell(const Args& a, int i, ClipSlots<kSlots + (WALLS ? 4 : 
 // a time as it has groups.  Each launch serves one kind of run (a batch of
 // both kinds takes two launches), so a run's results never depend on the
 // other runs.
-template <bool B, bool WALLS>
+template <bool B, bool WALLS, bool TIERED>
 __global__ __launch_bounds__(kClipThreads) void k_rt_clip(Args one, Batch bt) {
   __shared__ ClipSlots<kSlots + (WALLS ? 4 : 0)> s_slots[kClipCells];
   int blk, nblk = gridDim.x;
@@ -598,8 +614,8 @@ __global__ __launch_bounds__(kClipThreads) void k_rt_clip(Args one, Batch bt) {
   const int step = kClipCells * ((nblk - seg + kSeg - 1) / kSeg);   // the segment's blocks
   for (int e = (blk / kSeg) * kClipCells + group; e < queued; e += step) {
     const int i = a.queue[(size_t)seg * a.qcap + e];
-    if (i < 0 || i >= a.n || a.deg[i] != kDegClip) continue;
-    clip_cell<WALLS>(a, i, s_slots[group]);
+    if (i < 0 || i >= a.n || (a.deg[i] != kDegClip && a.deg[i] != kDegNear)) continue;
+    clip_cell<WALLS, TIERED>(a, i, s_slots[group]);
     wave_sync();   // the slots are taken by the next cell
   }
 }
@@ -624,254 +640,34 @@ __global__ __launch_bounds__(kClipThreads) void k_rt_clip(Args one, Batch bt) {
 // candidates are the clip's: the mirrors of a walled box, the ring, and the
 // neighbours' neighbours that could reach a vertex.  A cell that fails any
 // of these tests (a new neighbour, a lost one, a near-degenerate vertex, a
-// ring longer than kRingFast or next to a wall) is queued for the clip
+// ring longer than kGroup or next to a wall) is queued for the clip
 // launches (deg = kDegClip), which decide every case.
-constexpr int kRingFast = 8;            // ring entries held in registers
+//
+// Of the ring itself only the entries next to a vertex's own two are tried:
+// the distance of a convex polygon's vertices from one of its sides grows
+// and then falls along the polygon, so those are the nearest ones.
+//
+// The neighbours' neighbours (about 36 per cell, most of them several times
+// over) are most of the loads.  Large meshes therefore try only the ring at
+// first (TIER_RING), and a second pass (k_rt_near) tries the neighbours'
+// neighbours of those cells that have a failed neighbour.  For the others
+// they cannot matter: every edge of the old triangulation at the point or at
+// one of its neighbours is then locally Delaunay, and a point inside a
+// vertex's circle would have to be reached from it across such edges only,
+// each crossing keeping the point inside the next circle, until a triangle
+// holds it as a corner.  (The path could leave the neighbours' triangles
+// through an edge of two further points; no cell of 3.5 million, random and
+// regular meshes with moves from 0 to 0.3 spacings, was decided otherwise.
+// The areas and the match of the edges certify the mesh in any case.)
+// kGroup lanes work on a cell, one per neighbour; the group's loads and
+// stores are contiguous.  (One lane per cell and all candidates at once took
+// 1648 us on the 2048 x 2048 wave, bound by the gathers and their address
+// arithmetic; the two passes take 666, of which 1.1 GB written and 0.43 GB
+// read are 360 at the rate of a large copy, and 309 us.  64 x 64 tube: a
+// chain of 24 dependent loads, 38 -> 10 us in one launch.)
 constexpr double kVertexMargin = 1e-9;  // relative margin of every vertex test
 constexpr double kVertexSin = 0.05;     // least sine of a consecutive pair's angle
-
-// The cells and points of CSR entries k0 .. k0+CH-1 of the previous mesh
-// (those below k1), loaded level by level: entries, then their edges, then
-// the points, each level's loads in flight together.  c[m] = -1 for an entry
-// past k1, out of range, or naming cell `self` (its point load reads cell 0;
-// no edge is read for an entry out of range).
-template <int CH>
-__device__ __forceinline__ void ring_chunk(const Args& a, int k0, int k1, int self, int* c,
-                                           double* cx, double* cy) {
-#pragma unroll
-  for (int m = 0; m < CH; ++m) c[m] = k0 + m < k1 ? a.p_idx[k0 + m] : -1;
-#pragma unroll
-  for (int m = 0; m < CH; ++m) {
-    const int ent = c[m];
-    const int e = ent >> 1;
-    int cell = -1;
-    if (ent >= 0 && e < a.p_n_edges) {  // no load for an entry out of range
-      const rich_edge& pe = a.p_edges[e];
-      cell = (ent & 1) ? pe.i : (int)((uint32_t)pe.j & kMask);
-    }
-    c[m] = (cell < 0 || cell >= a.n || cell == self) ? -1 : cell;
-  }
-#pragma unroll
-  for (int m = 0; m < CH; ++m) {
-    const int cell = c[m] < 0 ? 0 : c[m];
-    const double2 p = a.xy[cell];
-    cx[m] = p.x;
-    cy[m] = p.y;
-  }
-}
-
-// (launch bounds for 4 waves per SIMD: a few registers spill, which costs
-// less than the latency 3 waves leave exposed)
-template <bool B, bool WALLS>
-__global__ __launch_bounds__(kThreads, 4) void k_rt_vertex(Args one, Batch bt) {
-  constexpr int N = kRingFast;
-  int blk;
-  const Args& a = block_run<B>(one, bt.cstart, bt, blk);
-  const int i = blk * kThreads + threadIdx.x;
-  if (i >= a.n) return;
-  if ((a.bc == (int)RICH_BOUNDARY_PERIODIC) == WALLS) return;  // the other launch's run
-  const double xi = a.x[i], yi = a.y[i];
-  bool ok = WALLS ? (xi > a.x0 && xi < a.x1 && yi > a.y0 && yi < a.y1)
-                  : (xi >= a.x0 && xi < a.x1 && yi >= a.y0 && yi < a.y1);
-  int k0 = a.p_off[i], k1 = a.p_off[i + 1];
-  const int n = k1 - k0;
-  ok = ok && k0 >= 0 && n >= 3 && n <= N && k1 <= a.p_n_csr;
-  if (!ok) k1 = k0;   // (nothing of the ring is loaded)
-
-  // displacement of cell c from r_i (nearest periodic image) and its id.
-  // The image is sought only when some lane of the wave needs it (a wave
-  // holds nearby cells, so all but the waves at the box's edges skip it);
-  // otherwise the plain difference is that image and its code is 0.
-  auto displacement = [&](int c, double xc, double yc, double& dx, double& dy) -> int32_t {
-    dx = xc - xi;
-    dy = yc - yi;
-    int code = 0;
-    if (!WALLS && __any(fabs(dx) > 0.5 * a.Lx || fabs(dy) > 0.5 * a.Ly)) {
-      int sx = 0, sy = 0;
-      if (dx > 0.5 * a.Lx) { dx -= a.Lx; sx = -1; } else if (dx < -0.5 * a.Lx) { dx += a.Lx; sx = 1; }
-      if (dy > 0.5 * a.Ly) { dy -= a.Ly; sy = -1; } else if (dy < -0.5 * a.Ly) { dy += a.Ly; sy = 1; }
-      if (sx != 0 || sy != 0) code = shift_code(sx, sy);
-    }
-    return pack(c, code);
-  };
-
-  // the ring: displacements, half squared lengths, ids (a wall entry or an
-  // entry out of range fails the cell)
-  int c[N];
-  double dx[N], dy[N], h[N];
-  int32_t id[N];
-  {
-    double cx[N], cy[N];
-    ring_chunk<N>(a, k0, k1, i, c, cx, cy);
-#pragma unroll
-    for (int m = 0; m < N; ++m) {
-      ok = ok && (m >= n || c[m] >= 0);
-      id[m] = displacement(c[m] < 0 ? 0 : c[m], cx[m], cy[m], dx[m], dy[m]);
-      h[m] = 0.5 * (dx[m] * dx[m] + dy[m] * dy[m]);
-    }
-  }
-
-  // vertex k: equidistant from r_i, ring entries k and k+1 (cyclically)
-  double vx[N], vy[N];
-  double r2 = 0.0;
-  int wraps = 0, start = 0;
-#pragma unroll
-  for (int k = 0; k < N; ++k) {
-    const bool last = k + 1 >= n;
-    const double ax = dx[k], ay = dy[k], ha = h[k];
-    const double bx = last ? dx[0] : dx[k + 1 < N ? k + 1 : 0];
-    const double by = last ? dy[0] : dy[k + 1 < N ? k + 1 : 0];
-    const double hb = last ? h[0] : h[k + 1 < N ? k + 1 : 0];
-    const double det = ax * by - ay * bx;
-    // det = |a| |b| sin(angle); a turn of less than half a turn, by a margin
-    const bool turn = det > 0.0 && det * det > (4.0 * kVertexSin * kVertexSin) * ha * hb;
-    const double inv = 1.0 / (turn ? det : 1.0);
-    vx[k] = (ha * by - hb * ay) * inv;
-    vy[k] = (ax * hb - ha * bx) * inv;
-    const double q = vx[k] * vx[k] + vy[k] * vy[k];
-    if (k < n) {
-      ok = ok && turn;
-      r2 = fmax(r2, q);
-      // the ring winds once: exactly one step passes angle 0
-      if (ccw_before(bx, by, ax, ay)) {
-        ++wraps;
-        start = last ? 0 : k + 1;
-      }
-    }
-  }
-  ok = ok && wraps == 1;
-
-  // every vertex inside every other candidate's half plane, by the margin
-  const double mr = kVertexMargin * r2;
-  auto inside = [&](int k, double ux, double uy, double hu) -> bool {
-    return hu - (vx[k] * ux + vy[k] * uy) > kVertexMargin * hu + mr;
-  };
-#pragma unroll
-  for (int k = 0; k < N; ++k) {
-#pragma unroll
-    for (int v = 0; v < N; ++v) {
-      // not the vertex's own two entries (k and k+1, cyclically)
-      const bool own = v == k || (v == k + 1 && k + 1 < n) || (v == 0 && k + 1 == n);
-      if (k < n && v < n && !own) ok = ok && inside(k, dx[v], dy[v], h[v]);
-    }
-  }
-  if (WALLS) {
-    // the point's mirrors across the walls y0, x1, y1, x0
-    const double wy0 = 2.0 * (a.y0 - yi), wx1 = 2.0 * (a.x1 - xi);
-    const double wy2 = 2.0 * (a.y1 - yi), wx3 = 2.0 * (a.x0 - xi);
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-      if (k < n) {
-        ok = ok && inside(k, 0.0, wy0, 0.5 * wy0 * wy0) && inside(k, wx1, 0.0, 0.5 * wx1 * wx1) &&
-             inside(k, 0.0, wy2, 0.5 * wy2 * wy2) && inside(k, wx3, 0.0, 0.5 * wx3 * wx3);
-      }
-    }
-  }
-
-  // the neighbours' neighbours: one nearer than twice the largest vertex
-  // distance (with the margin) that is not in the ring must leave every
-  // vertex inside its half plane
-  const double reach = 4.0 * r2 * (1.0 + kVertexMargin);
-  for (int m = 0; m < n && ok; ++m) {
-    int j = c[0];
-#pragma unroll
-    for (int t = 1; t < N; ++t) j = t == m ? c[t] : j;
-    const int l0 = a.p_off[j], l1 = a.p_off[j + 1];
-    if (l0 < 0 || l1 < l0 || l1 > a.p_n_csr || l1 - l0 > kRingMax) {
-      ok = false;
-      break;
-    }
-    constexpr int CH = 8;
-    for (int l = l0; l < l1 && ok; l += CH) {
-      int cc[CH];
-      double ccx[CH], ccy[CH];
-      ring_chunk<CH>(a, l, l1, i, cc, ccx, ccy);
-#pragma unroll
-      for (int t = 0; t < CH; ++t) {
-        if (cc[t] < 0) continue;
-        double ux, uy;
-        const int32_t idu = displacement(cc[t], ccx[t], ccy[t], ux, uy);
-        const double d2 = ux * ux + uy * uy;
-        if (!(d2 < reach)) continue;
-        bool known = false;
-#pragma unroll
-        for (int v = 0; v < N; ++v) known = known || (v < n && id[v] == idu);
-        if (known) continue;
-        // the largest projection of a vertex on the candidate
-        double p = vx[0] * ux + vy[0] * uy;
-#pragma unroll
-        for (int k = 1; k < N; ++k)
-          if (k < n) p = fmax(p, vx[k] * ux + vy[k] * uy);
-        const double hu = 0.5 * d2;
-        ok = ok && hu - p > kVertexMargin * hu + mr;
-      }
-    }
-  }
-
-  // a failing cell is appended to the block's queue segment (one atomic
-  // per wave; a block is one wave)
-  static_assert(kThreads == 64, "a block is one wave");
-  const unsigned long long fails = __ballot(!ok);
-  if (fails != 0ull) {
-    const int lane = (int)threadIdx.x;
-    const int leader = __ffsll((long long)__ballot(true)) - 1;
-    const int seg = blk % kSeg;
-    int base = 0;
-    if (lane == leader) base = atomicAdd(&a.qcnt[seg * kSegStride], __popcll(fails));
-    base = __shfl(base, leader);
-    if (!ok) {
-      a.queue[(size_t)seg * a.qcap + base + __popcll(fails & ((1ull << lane) - 1ull))] = i;
-      a.deg[i] = kDegClip;
-      return;
-    }
-  }
-  // edge k runs from vertex k-1 to vertex k; its slot is its counter-
-  // clockwise rank, counted from the entry of least angle
-  double pvx = vx[0], pvy = vy[0];
-#pragma unroll
-  for (int t = 1; t < N; ++t) {
-    pvx = t == n - 1 ? vx[t] : pvx;
-    pvy = t == n - 1 ? vy[t] : pvy;
-  }
-  double A2 = 0.0, sx = 0.0, sy = 0.0;
-  const size_t s0 = (size_t)i * kMaxFan;
-#pragma unroll
-  for (int k = 0; k < N; ++k) {
-    if (k < n) {
-      const double ux = pvx, uy = pvy, wx = vx[k], wy = vy[k];
-      const double cr = ux * wy - uy * wx;
-      A2 += cr;
-      sx += (ux + wx) * cr;
-      sy += (uy + wy) * cr;
-      const double ex = wx - ux, ey = wy - uy;
-      const int rank = k >= start ? k - start : k - start + n;
-      a.s_nb[s0 + rank] = id[k];
-      double* g = a.s_geo + 3 * (s0 + rank);
-      g[0] = sqrt(ex * ex + ey * ey);
-      g[1] = xi + 0.5 * (ux + wx);
-      g[2] = yi + 0.5 * (uy + wy);
-      pvx = wx;
-      pvy = wy;
-    }
-  }
-  a.deg[i] = n;
-  rich_cell cr;
-  cr.px = xi;
-  cr.py = yi;
-  cr.pad = 0.0;
-  cr.area = 0.5 * A2;
-  cr.sx = xi + sx / (3.0 * A2);
-  cr.sy = yi + sy / (3.0 * A2);
-  a.cells[i] = cr;
-}
-
-// ---------------------------------------------------------------------------
-// keep / own, certification, counts.  This kernel and the two emit kernels
-// give each cell a group of kGroup lanes, one per slot (a cell's slots are
-// contiguous, so a group's loads and stores are too, and the lanes of a
-// wave do like work); a block still covers kThreads cells.
-// ---------------------------------------------------------------------------
-constexpr int kGroup = 8;
+constexpr int kGroup = 8;               // lanes (and ring entries) of a cell
 constexpr int kGroupThreads = kThreads * kGroup;
 static_assert(64 % kGroup == 0, "groups do not straddle waves");
 
@@ -881,7 +677,312 @@ __device__ __forceinline__ uint32_t group_bits(bool v) {
   const int first = (int)(threadIdx.x & 63) & ~(kGroup - 1);
   return (uint32_t)(m >> first) & ((1u << kGroup) - 1u);
 }
+// The value of the lane opposite in the group at distance 1, 2 (quad
+// permutations) or in the other quad (half-row mirror, of values equal
+// within a quad): moves on the vector ALU.
+template <int CTRL>
+__device__ __forceinline__ double dpp_of(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(hi, CTRL, 0xF, 0xF, true),
+                          __builtin_amdgcn_mov_dpp(lo, CTRL, 0xF, 0xF, true));
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141;
+__device__ __forceinline__ double group_max(double v) {
+  v = fmax(v, dpp_of<kDppXor1>(v));
+  v = fmax(v, dpp_of<kDppXor2>(v));
+  return fmax(v, dpp_of<kDppHalfMirror>(v));
+}
+__device__ __forceinline__ double group_sum(double v) {
+  v += dpp_of<kDppXor1>(v);
+  v += dpp_of<kDppXor2>(v);
+  return v + dpp_of<kDppHalfMirror>(v);
+}
 
+// Lane l of a cell's group: ring entry l, its displacement from r_i, and the
+// vertex after it.
+struct Ring {
+  int n, start;       // entries; the entry of least angle
+  int c;              // neighbour cell, -1 past the end
+  int32_t id;
+  double xi, yi, dx, dy, vx, vy;
+  double r2;          // largest squared vertex distance of the cell
+};
+
+// Displacement of point (xc, yc) of cell c from (xi, yi) (nearest periodic
+// image) and its id.  The image is sought only when some lane of the wave
+// needs it (a wave holds nearby cells, so all but the waves at the box's
+// edges skip it); otherwise the plain difference is that image, of code 0.
+template <bool WALLS>
+__device__ __forceinline__ int32_t displacement(const Args& a, double xi, double yi, int c,
+                                                double xc, double yc, double& dx, double& dy) {
+  dx = xc - xi;
+  dy = yc - yi;
+  int code = 0;
+  if (!WALLS && __any(fabs(dx) > 0.5 * a.Lx || fabs(dy) > 0.5 * a.Ly)) {
+    int sx = 0, sy = 0;
+    if (dx > 0.5 * a.Lx) { dx -= a.Lx; sx = -1; } else if (dx < -0.5 * a.Lx) { dx += a.Lx; sx = 1; }
+    if (dy > 0.5 * a.Ly) { dy -= a.Ly; sy = -1; } else if (dy < -0.5 * a.Ly) { dy += a.Ly; sy = 1; }
+    if (sx != 0 || sy != 0) code = shift_code(sx, sy);
+  }
+  return pack(c, code);
+}
+
+// The ring of cell i (no cell: live = false) and whether it passes every
+// test that needs the ring alone.  NB: neighbours from a.nb (an earlier
+// launch wrote them), else from the entries' edges; WRITE: written there.
+template <bool WALLS, bool NB, bool WRITE>
+__device__ __forceinline__ bool load_ring(const Args& a, int i, bool live, Ring& r) {
+  const int l = (int)threadIdx.x & (kGroup - 1);
+  const double2 pi = a.xy[live ? i : 0];
+  r.xi = pi.x;
+  r.yi = pi.y;
+  int k0 = 0, n = 0;
+  if (live) {
+    k0 = a.p_off[i];
+    const int k1 = a.p_off[i + 1];
+    if (k0 >= 0 && k1 >= k0 && k1 <= a.p_n_csr) n = k1 - k0;
+  }
+  r.c = -1;
+  if (l < n) r.c = NB ? a.nb[k0 + l] : prev_neighbour(a, k0 + l);
+  if (WRITE) {
+    if (l < n) a.nb[k0 + l] = r.c;
+    if (n <= kRingMax)   // (a longer row is read by nobody)
+      for (int k = l + kGroup; k < n; k += kGroup) a.nb[k0 + k] = prev_neighbour(a, k0 + k);
+  }
+  if (r.c >= a.n || r.c == i) r.c = -1;   // out of range, or a wall's entry
+  const double2 p = a.xy[r.c < 0 ? 0 : r.c];
+  r.id = displacement<WALLS>(a, r.xi, r.yi, r.c < 0 ? 0 : r.c, p.x, p.y, r.dx, r.dy);
+  bool ok = WALLS ? (r.xi > a.x0 && r.xi < a.x1 && r.yi > a.y0 && r.yi < a.y1)
+                  : (r.xi >= a.x0 && r.xi < a.x1 && r.yi >= a.y0 && r.yi < a.y1);
+  ok = ok && n >= 3 && n <= kGroup && (l >= n || r.c >= 0);
+  r.n = n;
+
+  // vertex l: equidistant from r_i, ring entries l and l+1 (cyclically)
+  const int l1 = l + 1 < n ? l + 1 : 0, l2 = l1 + 1 < n ? l1 + 1 : 0, lp = l > 0 ? l - 1 : n - 1;
+  const double ax = r.dx, ay = r.dy;
+  const double bx = __shfl(ax, l1, kGroup), by = __shfl(ay, l1, kGroup);
+  const double ha = 0.5 * (ax * ax + ay * ay), hb = 0.5 * (bx * bx + by * by);
+  const double det = ax * by - ay * bx;
+  // det = |a| |b| sin(angle); a turn of less than half a turn, by a margin
+  const bool turn = det > 0.0 && det * det > (4.0 * kVertexSin * kVertexSin) * ha * hb;
+  const double inv = 1.0 / (turn ? det : 1.0);
+  r.vx = (ha * by - hb * ay) * inv;
+  r.vy = (ax * hb - ha * bx) * inv;
+  r.r2 = group_max(l < n ? r.vx * r.vx + r.vy * r.vy : 0.0);
+  ok = ok && (l >= n || turn);
+  // the ring winds once: exactly one step passes angle 0
+  const uint32_t wraps = group_bits(l < n && ccw_before(bx, by, ax, ay));
+  ok = ok && __popc(wraps) == 1;
+  r.start = __ffs(wraps) < n ? __ffs(wraps) : 0;
+  // the vertex inside the half planes of the entries beside its own two
+  // (the same one for a triangle), by the margin
+  const double mr = kVertexMargin * r.r2;
+  auto inside = [&](double ux, double uy, double hu) -> bool {
+    return hu - (r.vx * ux + r.vy * uy) > kVertexMargin * hu + mr;
+  };
+  {
+    const double ux = __shfl(ax, lp, kGroup), uy = __shfl(ay, lp, kGroup);
+    const double wx = __shfl(ax, l2, kGroup), wy = __shfl(ay, l2, kGroup);
+    ok = ok && (l >= n || (inside(ux, uy, 0.5 * (ux * ux + uy * uy)) &&
+                           inside(wx, wy, 0.5 * (wx * wx + wy * wy))));
+  }
+  if (WALLS) {
+    // the point's mirrors across the walls y0, x1, y1, x0
+    const double wy0 = 2.0 * (a.y0 - r.yi), wx1 = 2.0 * (a.x1 - r.xi);
+    const double wy2 = 2.0 * (a.y1 - r.yi), wx3 = 2.0 * (a.x0 - r.xi);
+    ok = ok && (l >= n || (inside(0.0, wy0, 0.5 * wy0 * wy0) && inside(wx1, 0.0, 0.5 * wx1 * wx1) &&
+                           inside(0.0, wy2, 0.5 * wy2 * wy2) && inside(wx3, 0.0, 0.5 * wx3 * wx3)));
+  }
+  return group_bits(!ok) == 0u;
+}
+
+// A cell's vertices and ring ids in LDS, for the lanes of its group (the
+// padding keeps the groups of a wave on different banks).
+struct Fan {
+  double2 v[kGroup + 1];
+  int32_t id[kGroup];
+};
+
+// Whether every neighbour's neighbour leaves every vertex of a ring that
+// passed inside its half plane: one nearer than twice the largest vertex
+// distance (with the margin) that is not in the ring is tried.  Lane m goes
+// through the entries of ring member m's row.
+template <bool WALLS, bool NB>
+__device__ __forceinline__ bool second_ring(const Args& a, int i, const Ring& r, Fan& F) {
+  const int l = (int)threadIdx.x & (kGroup - 1);
+  if (l < r.n) {
+    F.v[l] = make_double2(r.vx, r.vy);
+    F.id[l] = r.id;
+  }
+  wave_sync();
+  double2 v[kGroup];
+  int32_t id[kGroup];
+#pragma unroll
+  for (int k = 0; k < kGroup; ++k) {   // past the end: the first again
+    v[k] = F.v[k < r.n ? k : 0];
+    id[k] = F.id[k < r.n ? k : 0];
+  }
+  const double mr = kVertexMargin * r.r2;
+  const double reach = 4.0 * r.r2 * (1.0 + kVertexMargin);
+  bool ok = true;
+  int l0 = 0, l1 = 0;
+  if (r.c >= 0) {
+    l0 = a.p_off[r.c];
+    l1 = a.p_off[r.c + 1];
+    if (l0 < 0 || l1 < l0 || l1 > a.p_n_csr || l1 - l0 > kRingMax) {
+      ok = false;
+      l1 = l0;
+    }
+  }
+  constexpr int CH = 8;   // candidates whose loads are in flight together
+  for (; l0 < l1; l0 += CH) {
+    int c[CH];
+    double2 p[CH];
+#pragma unroll
+    for (int t = 0; t < CH; ++t) c[t] = l0 + t < l1 ? (NB ? a.nb[l0 + t] : a.p_idx[l0 + t]) : -1;
+    if (!NB) {
+#pragma unroll
+      for (int t = 0; t < CH; ++t) c[t] = entry_cell(a, c[t]);
+    }
+#pragma unroll
+    for (int t = 0; t < CH; ++t) {
+      if (c[t] >= a.n || c[t] == i) c[t] = -1;
+      p[t] = a.xy[c[t] < 0 ? 0 : c[t]];
+    }
+#pragma unroll
+    for (int t = 0; t < CH; ++t) {
+      if (c[t] < 0) continue;
+      double ux, uy;
+      const int32_t u = displacement<WALLS>(a, r.xi, r.yi, c[t], p[t].x, p[t].y, ux, uy);
+      const double d2 = ux * ux + uy * uy;
+      if (!(d2 < reach)) continue;
+      bool known = false;
+#pragma unroll
+      for (int k = 0; k < kGroup; ++k) known = known || id[k] == u;
+      if (known) continue;
+      // the largest projection of a vertex on the candidate
+      double q = v[0].x * ux + v[0].y * uy;
+#pragma unroll
+      for (int k = 1; k < kGroup; ++k) q = fmax(q, v[k].x * ux + v[k].y * uy);
+      const double hu = 0.5 * d2;
+      ok = ok && hu - q > kVertexMargin * hu + mr;
+    }
+  }
+  return group_bits(!ok) == 0u;
+}
+
+// Queues the groups' failing cells for the clip, in the queue segment of
+// their own block of cells (so that no segment overflows): one atomic per
+// wave, whose cells are of one block `home`.
+__device__ __forceinline__ void queue_failed(const Args& a, int home, int i, bool failed,
+                                             int32_t mark) {
+  const int lane = (int)threadIdx.x & 63;
+  const bool lead = failed && (lane & (kGroup - 1)) == 0;
+  const unsigned long long fails = __ballot(lead);
+  if (fails == 0ull) return;
+  const int first = __ffsll((long long)fails) - 1;
+  const int seg = home % kSeg;
+  int base = 0;
+  if (lane == first) base = atomicAdd(&a.qcnt[seg * kSegStride], __popcll(fails));
+  base = __shfl(base, first);
+  if (lead) {
+    a.queue[(size_t)seg * a.qcap + base + __popcll(fails & ((1ull << lane) - 1ull))] = i;
+    a.deg[i] = mark;
+  }
+}
+
+// The cells whose ring passes (RING: the ring alone is tried, and the
+// neighbours are written for k_rt_near and the clip; else their neighbours
+// too).
+template <bool B, bool WALLS, bool RING>
+__global__ __launch_bounds__(kGroupThreads) void k_rt_vertex(Args one, Batch bt) {
+  __shared__ Fan s_fan[RING ? 1 : kThreads];
+  int blk;
+  const Args& a = block_run<B>(one, bt.cstart, bt, blk);
+  if ((a.bc == (int)RICH_BOUNDARY_PERIODIC) == WALLS) return;  // the other launch's run
+  const int l = (int)threadIdx.x & (kGroup - 1);
+  const int i = blk * kThreads + (int)threadIdx.x / kGroup;
+  const bool live = i < a.n;
+  Ring r;
+  bool ok = load_ring<WALLS, false, RING>(a, i, live, r);
+  if constexpr (!RING) {
+    if (ok) ok = second_ring<WALLS, false>(a, i, r, s_fan[threadIdx.x / kGroup]);
+  }
+  queue_failed(a, blk, i, live && !ok, kDegClip);
+  if (!live || !ok) return;   // whole groups
+  // edge l runs from vertex l-1 to vertex l; its slot is its counter-
+  // clockwise rank, counted from the entry of least angle
+  const int lp = l > 0 ? l - 1 : r.n - 1;
+  const double ux = __shfl(r.vx, lp, kGroup), uy = __shfl(r.vy, lp, kGroup);
+  const double wx = r.vx, wy = r.vy;
+  double cr = ux * wy - uy * wx;
+  const size_t s0 = (size_t)i * kMaxFan;
+  if (l < r.n) {
+    const double ex = wx - ux, ey = wy - uy;
+    const int rank = l >= r.start ? l - r.start : l - r.start + r.n;
+    a.s_nb[s0 + rank] = r.id;
+    double* g = a.s_geo + 3 * (s0 + rank);
+    g[0] = sqrt(ex * ex + ey * ey);
+    g[1] = r.xi + 0.5 * (ux + wx);
+    g[2] = r.yi + 0.5 * (uy + wy);
+  } else {
+    cr = 0.0;
+  }
+  const double A2 = group_sum(cr);
+  const double sx = group_sum(cr * (ux + wx)), sy = group_sum(cr * (uy + wy));
+  if (l == 0) a.deg[i] = r.n;
+  // the cell record, a 16-byte part per lane
+  double2* cell = reinterpret_cast<double2*>(a.cells + i);
+  if (l == 0) cell[0] = make_double2(r.xi, r.yi);
+  if (l == 1) cell[1] = make_double2(0.5 * A2, r.xi + sx / (3.0 * A2));
+  if (l == 2) cell[2] = make_double2(r.yi + sy / (3.0 * A2), 0.0);
+}
+
+// The neighbours' neighbours of the cells whose ring passed but that have a
+// neighbour whose ring did not.  Each wave lists such cells among its own 64
+// (a lane per cell), goes through the list kThreads / kGroup cells at a time,
+// and queues those that fail for the clip with a mark of their own: the marks
+// that others look for stay those of the first pass.
+template <bool B, bool WALLS>
+__global__ __launch_bounds__(kThreads) void k_rt_near(Args one, Batch bt) {
+  constexpr int GROUPS = kThreads / kGroup;
+  __shared__ Fan s_fan[GROUPS];
+  __shared__ int s_list[kThreads];
+  static_assert(kThreads == 64, "a block is one wave");
+  int blk;
+  const Args& a = block_run<B>(one, bt.cstart, bt, blk);
+  if ((a.bc == (int)RICH_BOUNDARY_PERIODIC) == WALLS) return;  // the other launch's run
+  const int lane = (int)threadIdx.x;
+  bool near = false;
+  const int i0 = blk * kThreads + lane;
+  if (i0 < a.n && a.deg[i0] != kDegClip) {
+    const int k0 = a.p_off[i0], n = a.p_off[i0 + 1] - k0;   // (3 to kGroup entries, all in range)
+    int c[kGroup];
+#pragma unroll
+    for (int m = 0; m < kGroup; ++m) c[m] = m < n ? a.nb[k0 + m] : i0;
+#pragma unroll
+    for (int m = 0; m < kGroup; ++m) near = near || a.deg[c[m]] == kDegClip;
+  }
+  const unsigned long long nears = __ballot(near);
+  if (near) s_list[__popcll(nears & ((1ull << lane) - 1ull))] = i0;
+  wave_sync();
+  const int count = __popcll(nears), group = lane / kGroup;
+  for (int g = group; g - group < count; g += GROUPS) {   // (the whole wave)
+    const bool live = g < count;
+    const int i = live ? s_list[g] : 0;
+    Ring r;
+    bool ok = load_ring<WALLS, true, false>(a, i, live, r);
+    if (live) ok = second_ring<WALLS, true>(a, i, r, s_fan[group]);
+    queue_failed(a, blk, i, live && !ok, kDegNear);
+    wave_sync();   // the fans are taken by the next cells
+  }
+}
+
+// ---------------------------------------------------------------------------
+// keep / own, certification, counts.  This kernel and emit give each cell a
+// group of kGroup lanes too, one per slot; a block still covers kThreads
+// cells.
+// ---------------------------------------------------------------------------
 template <bool B>
 __global__ __launch_bounds__(kGroupThreads) void k_rt_classify(Args one, Batch bt) {
   int blk;
@@ -1243,8 +1344,15 @@ namespace {
 
 size_t rt_align(size_t v) { return (v + 255) / 256 * 256; }
 
+void rt_capacity(int64_t n, int64_t* ce, int64_t* cc) {
+  const int64_t r = (int64_t)std::ceil(std::sqrt((double)n));
+  *ce = 3 * n + 8 * r + 64;
+  *cc = 2 * *ce;
+}
+
 struct RtLayout {
-  size_t deg, s_nb, s_geo, s_flag, s_back, cnt, bsum, cpart, qcnt, queue, xy, total;
+  size_t deg, s_nb, s_geo, s_flag, s_back, cnt, bsum, cpart, qcnt, queue, xy, nbr, total;
+  int64_t nbr_cap;
   int nb, qcap;
 };
 
@@ -1267,14 +1375,11 @@ RtLayout rt_layout(int64_t n) {
   L.qcap = (int)(retess::kThreads * ((blocks + retess::kSeg - 1) / retess::kSeg));
   L.queue = o;  o += rt_align(4 * (size_t)retess::kSeg * (size_t)L.qcap);
   L.xy = o;     o += rt_align(16 * (size_t)n);
+  int64_t ce;
+  rt_capacity(n, &ce, &L.nbr_cap);
+  L.nbr = o;    o += rt_align(4 * (size_t)L.nbr_cap);
   L.total = o;
   return L;
-}
-
-void rt_capacity(int64_t n, int64_t* ce, int64_t* cc) {
-  const int64_t r = (int64_t)std::ceil(std::sqrt((double)n));
-  *ce = 3 * n + 8 * r + 64;
-  *cc = 2 * *ce;
 }
 
 // Checks one run's arguments and fills its descriptor; RICH_OK or the status.
@@ -1331,6 +1436,8 @@ int make_args(const rich_mesh* prev, const double* x, const double* y,
   a.queue = reinterpret_cast<int32_t*>(w + L.queue);
   a.qcap = L.qcap;
   a.xy = reinterpret_cast<double2*>(w + L.xy);
+  // (a previous mesh of more entries than a rebuilt one may have: no room)
+  if (prev->n_csr <= L.nbr_cap) a.nb = reinterpret_cast<int32_t*>(w + L.nbr);
   a.x0 = prev->box[0];
   a.y0 = prev->box[1];
   a.x1 = prev->box[2];
@@ -1343,22 +1450,31 @@ int make_args(const rich_mesh* prev, const double* x, const double* y,
   return RICH_OK;
 }
 
+// The launches that find the cells, for one kind of box.
+template <bool B, bool WALLS>
+void launch_cells(const retess::Args& a, const retess::Batch& bt, int gc, int gq, bool tiered,
+                  hipStream_t st) {
+  using namespace retess;
+  if (tiered) {
+    hipLaunchKernelGGL((k_rt_vertex<B, WALLS, true>), dim3(gc), dim3(kGroupThreads), 0, st, a, bt);
+    hipLaunchKernelGGL((k_rt_near<B, WALLS>), dim3(gc), dim3(kThreads), 0, st, a, bt);
+    hipLaunchKernelGGL((k_rt_clip<B, WALLS, true>), dim3(gq), dim3(kClipThreads), 0, st, a, bt);
+  } else {
+    hipLaunchKernelGGL((k_rt_vertex<B, WALLS, false>), dim3(gc), dim3(kGroupThreads), 0, st, a, bt);
+    hipLaunchKernelGGL((k_rt_clip<B, WALLS, false>), dim3(gq), dim3(kClipThreads), 0, st, a, bt);
+  }
+}
+
 // The launches of one re-tessellation of one kind of box (B: of n_runs runs at once, with
 // gc cell blocks and gs scan blocks in all).
 template <bool B>
 void launch_all(const retess::Args& a, const retess::Batch& bt, int gc, int gs, int n_runs,
-                bool walls, bool periodic, hipStream_t st) {
+                bool walls, bool periodic, bool tiered, hipStream_t st) {
   using namespace retess;
   const int gq = B ? gc : std::min(gc, kClipMaxBlocks);   // (a batch's blocks find their run by gc)
   hipLaunchKernelGGL(k_rt_begin<B>, dim3(gc), dim3(kThreads), 0, st, a, bt);
-  if (walls) {
-    hipLaunchKernelGGL((k_rt_vertex<B, true>), dim3(gc), dim3(kThreads), 0, st, a, bt);
-    hipLaunchKernelGGL((k_rt_clip<B, true>), dim3(gq), dim3(kClipThreads), 0, st, a, bt);
-  }
-  if (periodic) {
-    hipLaunchKernelGGL((k_rt_vertex<B, false>), dim3(gc), dim3(kThreads), 0, st, a, bt);
-    hipLaunchKernelGGL((k_rt_clip<B, false>), dim3(gq), dim3(kClipThreads), 0, st, a, bt);
-  }
+  if (walls) launch_cells<B, true>(a, bt, gc, gq, tiered, st);
+  if (periodic) launch_cells<B, false>(a, bt, gc, gq, tiered, st);
   hipLaunchKernelGGL(k_rt_classify<B>, dim3(gc), dim3(kGroupThreads), 0, st, a, bt);
   hipLaunchKernelGGL(k_rt_scan_local<B>, dim3(gs), dim3(kScanThreads), 0, st, a, bt);
   hipLaunchKernelGGL(k_rt_scan_blocks<B>, dim3(n_runs), dim3(kScanThreads), 0, st, a, bt);
@@ -1402,7 +1518,8 @@ int rich_retess(const rich_mesh* prev, const double* x, const double* y,
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int gc = (int)((n + retess::kThreads - 1) / retess::kThreads);
   const bool periodic = a.bc == (int)RICH_BOUNDARY_PERIODIC;
-  launch_all<false>(a, retess::Batch{}, gc, L.nb, 1, !periodic, periodic, st);
+  launch_all<false>(a, retess::Batch{}, gc, L.nb, 1, !periodic, periodic,
+                    a.nb != nullptr && n >= retess::kTieredMin, st);
   return hipGetLastError() == hipSuccess ? RICH_OK : RICH_E_DEVICE;
 }
 
@@ -1467,12 +1584,13 @@ int rich_retess_batch(int32_t n, const rich_mesh* const* prev, const double* con
   bt.hdr_out = reinterpret_cast<retess::Hdr*>(b + batch_hdr_offset(n));
   bt.flags_out = reinterpret_cast<int32_t*>(b + batch_flags_offset(n));
   bt.n_runs = n;
-  bool walls = false, periodic = false;
+  bool walls = false, periodic = false, tiered = gc >= retess::kTieredMin / retess::kThreads;
   for (const retess::Args& r : args) {
+    tiered = tiered && r.nb != nullptr;
     walls = walls || r.bc != (int)RICH_BOUNDARY_PERIODIC;
     periodic = periodic || r.bc == (int)RICH_BOUNDARY_PERIODIC;
   }
-  launch_all<true>(args[0], bt, (int)gc, (int)gs, n, walls, periodic, st);
+  launch_all<true>(args[0], bt, (int)gc, (int)gs, n, walls, periodic, tiered, st);
   return hipGetLastError() == hipSuccess ? RICH_OK : RICH_E_DEVICE;
 }
 
