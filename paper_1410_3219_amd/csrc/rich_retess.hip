@@ -33,12 +33,14 @@
 //   k_rt_near     (large meshes) the vertices against the neighbours' neighbours
 //   k_rt_clip     a group of lanes per queued cell: the cell's edges, area,
 //                 centroid
-//   k_rt_classify keep / own each slot by the input stage's rules, check
-//                 each kept edge against the neighbour's slot, count
-//   k_rt_scan_*   prefix sums of the counts (within and over blocks of cells),
-//                 totals, the checks that need every cell, the result header
+//   k_rt_count    kept and owned edges of each cell by the input stage's
+//                 rules, scanned within blocks of cells
+//   k_rt_scan_blocks  the scan over the blocks, totals, the checks of areas
+//                 and capacities
 //   k_rt_emit     off[], eoff[], edge records and the CSR entries of both
-//                 sides of each edge
+//                 sides of each edge, found in the neighbour's slots
+//   k_rt_end      compares the few edges that emit cannot decide, folds the
+//                 flags into the sticky word
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -58,6 +60,16 @@ static_assert(kMaxFan <= 64, "a kept slot's rank fits the six upper bits of its 
 // Candidates of a cell besides the 4 mirrors of a walled box: neighbours in
 // the previous mesh, and the neighbours' neighbours that entered.
 constexpr int kSlots = 16;
+// A cell's slots 0 .. kRow-1 lie in one 32-byte row, the rest (rare) apart.
+constexpr int kRow = 8;
+// deg[i] | kLean: a cell of at most kRow edges whose edges' lengths and
+// midpoints follow from its row of neighbours to rounding far below what
+// emit and end compare, every one of them kept (lean_cell); they are computed
+// where they are needed instead of being stored and read back (24 bytes a
+// slot).  On the 2048 x 2048 wave that is every cell; writing their geometry
+// took the ring check from 371 to 666 us.
+constexpr int32_t kLean = 1 << 8;
+constexpr int kWallBits = 24;       // cnt of a lean cell, until counted: its walls from this bit on
 constexpr int32_t kDegClip = -2;    // deg[i] of a cell that the ring check left to the clip,
 constexpr int32_t kDegNear = -3;    // of one that the check of its neighbours' neighbours did
 // The cells the vertex check leaves are queued for the clip in kSeg
@@ -87,14 +99,15 @@ struct Hdr {  // first 64 bytes of the workspace
   double area_sum;
   int64_t n_wall;   // kept wall edges (each one CSR entry)
   int64_t n_clip;   // cells the vertex check left to the clip
-  int64_t pad;
+  uint32_t done;    // blocks of k_rt_end that have finished (kUnlike: one found edges unlike)
+  int32_t pad;
 };
 static_assert(sizeof(Hdr) == 64, "result header");
 
-// One classify block's sums: area of its cells, dropped edge slots, kept
-// wall edges.  Written per block and reduced in a fixed order by the scan,
-// rather than added into the header with atomics (every block's atomics on
-// one header line serialised the kernel).
+// One scan block's sums: area of its cells, dropped edge slots, kept wall
+// edges.  Written per block and reduced in a fixed order by the scan, rather
+// than added into the header with atomics (every block's atomics on one
+// header line serialised the kernel).
 struct CPart {
   double area;
   long long drop, walls, pad;
@@ -115,20 +128,23 @@ struct Args {
   int64_t cap_edges, cap_csr;
   // workspace
   Hdr* hdr;
-  int32_t* deg;        // [n]
-  int32_t* s_nb;       // [n][kMaxFan] generating point: cell | code << 28
+  int32_t* deg;        // [n] edges of the cell (| kLean), or a kDeg mark
+  double* area;        // [n] the cells' areas, packed
+  int32_t *s_nb, *s_nbx;   // [n][kRow], [n][kMaxFan - kRow] slots: cell | code << 28
+  uint32_t* chk;       // [n] owned slots whose match with the neighbour's is still to compare
+  // cells that are not lean only:
   double* s_geo;       // [n][kMaxFan][3] edge length, midpoint x, midpoint y
   uint8_t* s_flag;     // [n][kMaxFan] bit 0 kept, bit 1 owned, bits 2-6 rank among kept
-  uint8_t* s_back;     // [n][kMaxFan] owned edge: its slot in the neighbour's row
   uint32_t* cnt;       // [n] kept | owned << 16 edges of a cell; then of its scan block before it
   int64_t* bsum;       // [2][n_scan_blocks] block totals of kept / owned
-  CPart* cpart;        // [cell blocks] classify block sums, reduced by the scan
+  CPart* cpart;        // [n_scan_blocks] block sums, reduced by the scan
   int32_t* qcnt;       // [kSeg * kSegStride] queue segment counters (every kSegStride-th)
   int32_t* queue;      // [kSeg][qcap] cells left to the clip
   int32_t* nb;         // [p_n_csr] neighbour of each CSR entry of the previous mesh (or null)
   int32_t qcap;        // capacity of a segment: kThreads * ceil(cell blocks / kSeg)
   // geometry
   double x0, y0, x1, y1, Lx, Ly;
+  double size;         // largest of the box's sides and its corners' coordinates
   int32_t n, bc, n_scan_blocks;
 };
 
@@ -156,17 +172,28 @@ __device__ __forceinline__ int run_of_block(const int32_t* __restrict__ start, i
   return lo;
 }
 
-// The descriptor of this block's run and the block's index within the run.
+// The descriptor of the run of block b of a launch and the block's index
+// within the run.
 template <bool B>
 __device__ __forceinline__ const Args& block_run(const Args& one, const int32_t* start,
-                                                 const Batch& bt, int& blk) {
+                                                 const Batch& bt, int b, int& blk) {
   if (!B) {
-    blk = blockIdx.x;
+    blk = b;
     return one;
   }
-  const int r = run_of_block(start, bt.n_runs, blockIdx.x);
-  blk = blockIdx.x - start[r];
+  const int r = run_of_block(start, bt.n_runs, b);
+  blk = b - start[r];
   return bt.descs[r];
+}
+// The block of cells this block works on: each of the 8 XCDs (with an L2 of
+// its own, taking every eighth block of a launch) gets one contiguous range
+// of them, so that the neighbours' rows, points and offsets that a block
+// gathers are mostly in its XCD's L2 (2048 x 2048 wave: the ring check reads
+// 0.29 GB instead of 0.43 from beyond it; 511 x 511 tube, emit: 19.8 -> 18.6 us).
+__device__ __forceinline__ int cell_block() {
+  constexpr int kNumXcd = 8;
+  const int nb = gridDim.x, x = blockIdx.x % kNumXcd, rem = nb % kNumXcd;
+  return x * (nb / kNumXcd) + min(x, rem) + blockIdx.x / kNumXcd;
 }
 
 __device__ __forceinline__ int32_t pack(int cell, int code) {
@@ -213,7 +240,7 @@ __device__ __forceinline__ int prev_neighbour(const Args& a, int k) {
 template <bool B>
 __global__ __launch_bounds__(kThreads) void k_rt_begin(Args one, Batch bt) {
   int blk;
-  const Args& a = block_run<B>(one, bt.cstart, bt, blk);
+  const Args& a = block_run<B>(one, bt.cstart, bt, cell_block(), blk);
   if (blk == 0) {
     Hdr* h = a.hdr;
     for (int t = threadIdx.x; t < kSeg; t += kThreads) a.qcnt[t * kSegStride] = 0;
@@ -225,6 +252,7 @@ __global__ __launch_bounds__(kThreads) void k_rt_begin(Args one, Batch bt) {
       h->area_sum = 0.0;
       h->n_wall = 0;
       h->n_clip = 0;
+      h->done = 0;
     }
   }
   const int i = blk * kThreads + threadIdx.x;
@@ -277,6 +305,59 @@ struct Part {
   __device__ __forceinline__ bool live() const { return !empty && bounded() && ln * hd < hn * ld; }
 };
 
+// The vertex equidistant from r_i and the points at displacements a and b, b
+// counter-clockwise after a by less than half a turn (det = |a| |b| sin(angle),
+// by a margin); false if it is not.
+constexpr double kVertexSin = 0.05;     // least sine of a consecutive pair's angle
+__device__ __forceinline__ bool ring_vertex(double ax, double ay, double bx, double by,
+                                            double& vx, double& vy) {
+  const double ha = 0.5 * (ax * ax + ay * ay), hb = 0.5 * (bx * bx + by * by);
+  const double det = ax * by - ay * bx;
+  const bool turn = det > 0.0 && det * det > (4.0 * kVertexSin * kVertexSin) * ha * hb;
+  const double inv = 1.0 / (turn ? det : 1.0);
+  vx = (ha * by - hb * ay) * inv;
+  vy = (ax * hb - ha * bx) * inv;
+  return turn;
+}
+// Length and midpoint of the edge from vertex u to vertex w about (xi, yi).
+__device__ __forceinline__ void edge_geometry(double xi, double yi, double ux, double uy, double wx,
+                                              double wy, double& len, double& mx, double& my) {
+  const double ex = wx - ux, ey = wy - uy;
+  len = sqrt(ex * ex + ey * ey);
+  mx = xi + 0.5 * (ux + wx);
+  my = yi + 0.5 * (uy + wy);
+}
+// Displacement of the point that slot `id` of the cell at (xi, yi) names (p
+// its cell's, or for a wall the cell's own).
+__device__ __forceinline__ void slot_displacement(const Args& a, double xi, double yi, int32_t id,
+                                                  double2 p, double& dx, double& dy) {
+  dx = p.x - xi;
+  dy = p.y - yi;
+  const int code = (int)((uint32_t)id >> kShift);
+  if (code >= kWallX0) {   // the mirror image
+    dx = code == kWallX0 ? 2.0 * (a.x0 - xi) : code == kWallX1 ? 2.0 * (a.x1 - xi) : 0.0;
+    dy = code == kWallY0 ? 2.0 * (a.y0 - yi) : code == kWallY1 ? 2.0 * (a.y1 - yi) : 0.0;
+  } else if (code != 0) {
+    int sx, sy;
+    code_shift(code, sx, sy);
+    dx += sx * a.Lx;
+    dy += sy * a.Ly;
+  }
+}
+// Whether a cell whose consecutive neighbours all turn by ring_vertex's
+// margin is lean: its shortest edge (squared length l2) is above the cut for
+// dropping one whatever the neighbour's area (2e-12 box radii); and rounding,
+// of the vertices (about 1e-14 of the largest distance, squared r2) and of the
+// coordinates (4e-15 of their size a.size), stays below half of the
+// tolerance of k_rt_end's comparison, 1e-9 cell radii.
+__device__ __forceinline__ bool lean_cell(const Args& a, double l2, double r2, double area) {
+  return l2 >= 4e-24 / kPi * a.Lx * a.Ly && r2 <= 3e5 * area && area >= 2e-10 * a.size * a.size;
+}
+__device__ __forceinline__ int32_t& slot_nb(const Args& a, int i, int q) {
+  return q < kRow ? a.s_nb[(size_t)i * kRow + q]
+                  : a.s_nbx[(size_t)i * (kMaxFan - kRow) + (q - kRow)];
+}
+
 // The cells of a queue, kClipLanes lanes each: lane l holds candidates l and
 // l + kClipLanes, so the trials of every candidate against every other one,
 // a serial chain of hundreds of operations and loads for one lane, run side
@@ -300,6 +381,7 @@ struct ClipSlots {
   double c[NS], sx[NS], sy[NS];   // shoelace terms of the live ones
   int32_t id[NS];
   int32_t row[kClipLanes], pre[kClipLanes];   // ring members' CSR rows, entries before each
+  int32_t place[kMaxFan];   // slot of the edge at each place
 };
 
 // The lanes of one wave read what others of it wrote.
@@ -405,7 +487,7 @@ __device__ void clip_cell(const Args& a, int i, ClipSlots<kSlots + (WALLS ? 4 : 
   // first pass: the polygon of the bounds and the first ring, and the
   // largest distance of its vertices
   uint32_t em = 0;
-  double r2 = 0.0;
+  double reach2 = 0.0;
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const int u = l + h * kClipLanes;
@@ -423,7 +505,7 @@ __device__ void clip_cell(const Args& a, int i, ClipSlots<kSlots + (WALLS ? 4 : 
       if (live) {
         const double t = p.hn / p.hd;
         const double px = 0.5 * dux - t * duy, py = 0.5 * duy + t * dux;
-        r2 = fmax(r2, px * px + py * py);
+        reach2 = fmax(reach2, px * px + py * py);
       } else if (!p.bounded()) {
         bad |= RICH_RETESS_CLIP;
       }
@@ -431,7 +513,7 @@ __device__ void clip_cell(const Args& a, int i, ClipSlots<kSlots + (WALLS ? 4 : 
     em |= clip_bits(live) << (h * kClipLanes);
   }
   for (int o = kClipLanes / 2; o > 0; o >>= 1) {
-    r2 = fmax(r2, __shfl_xor(r2, o));
+    reach2 = fmax(reach2, __shfl_xor(reach2, o));
     bad |= __shfl_xor(bad, o);
   }
 
@@ -464,7 +546,7 @@ __device__ void clip_cell(const Args& a, int i, ClipSlots<kSlots + (WALLS ? 4 : 
     for (int h = 0; h < CH; ++h) {
       double dx, dy;
       const int32_t id = displacement(cc[h], cp[h].x, cp[h].y, dx, dy);
-      bool on = cc[h] >= 0 && !(4.0 * r2 <= dx * dx + dy * dy);
+      bool on = cc[h] >= 0 && !(4.0 * reach2 <= dx * dx + dy * dy);
       for (int v = BASE; v < nv; ++v) on = on && S.id[v] != id;
       if (clip_bits(on) == 0u) continue;
       Part p(dx, dy);
@@ -558,26 +640,26 @@ __device__ void clip_cell(const Args& a, int i, ClipSlots<kSlots + (WALLS ? 4 : 
   }
   const int deg = __popc(fm);
   if (deg < 3) bad |= RICH_RETESS_CLIP;
+  // the edges' places; rounding that ranks two of them alike fails the cell
+  int q[2];
+  uint32_t taken = 0;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    q[h] = (fm >> (l + h * kClipLanes)) & 1u
+               ? rank[h] - __popc(holes & ((1u << rank[h]) - 1u))   // < NS <= kMaxFan
+               : kMaxFan;
+    taken |= 1u << q[h];
+  }
+  for (int o = kClipLanes / 2; o > 0; o >>= 1) taken |= __shfl_xor(taken, o);
+  if ((taken & ((1u << kMaxFan) - 1u)) != (1u << deg) - 1u) bad |= RICH_RETESS_CLIP;
   if (bad) {
     if (l == 0) {
       atomicOr(&a.hdr->flags, bad);
       a.deg[i] = 0;
+      a.area[i] = 0.0;
       a.cells[i] = cr;
     }
     return;
-  }
-  const size_t s0 = (size_t)i * kMaxFan;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int u = l + h * kClipLanes;
-    if ((fm >> u) & 1u) {
-      const int q = rank[h] - __popc(holes & ((1u << rank[h]) - 1u));   // < NS <= kMaxFan
-      a.s_nb[s0 + q] = S.id[u];
-      double* g = a.s_geo + 3 * (s0 + q);
-      g[0] = len_[h];
-      g[1] = mx[h];
-      g[2] = my[h];
-    }
   }
   wave_sync();
   double A2 = 0.0, cx = 0.0, cy = 0.0;
@@ -588,8 +670,53 @@ __device__ void clip_cell(const Args& a, int i, ClipSlots<kSlots + (WALLS ? 4 : 
     cx += S.sx[v] * cv;
     cy += S.sy[v] * cv;
   }
+  // the edges in their places
+  double l2 = INFINITY;
+  bool plain = deg <= kRow;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int u = l + h * kClipLanes;
+    if (q[h] < kMaxFan) {
+      slot_nb(a, i, q[h]) = S.id[u];
+      S.place[q[h]] = u;   // (all of 0 .. deg - 1 are taken)
+      l2 = fmin(l2, len_[h] * len_[h]);
+    }
+  }
+  wave_sync();
+  // lean if every consecutive pair turns enough, and the rest of lean_cell
+  double r2 = 0.0;
+  if (l < deg) {
+    const int u = S.place[l], v = S.place[l + 1 < deg ? l + 1 : 0];
+    double vx, vy;
+    const bool turn = ring_vertex(S.dx[u], S.dy[u], S.dx[v], S.dy[v], vx, vy);
+    plain = plain && turn;
+    r2 = vx * vx + vy * vy;
+  }
+  for (int o = kClipLanes / 2; o > 0; o >>= 1) {
+    r2 = fmax(r2, __shfl_xor(r2, o));
+    l2 = fmin(l2, __shfl_xor(l2, o));
+  }
+  const bool lean = clip_bits(!plain) == 0u && lean_cell(a, l2, r2, 0.5 * A2);
+  const int32_t at = l < deg ? S.id[S.place[l]] : pack(0, 0);
+  const bool wall = (int)((uint32_t)at >> kShift) >= kWallX0;
+  const uint32_t walls = clip_bits(wall);
+  const uint32_t own = clip_bits(wall || (l < deg && i < (int)((uint32_t)at & kMask)));
+  if (!lean) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (q[h] < kMaxFan) {
+        double* g = a.s_geo + 3 * ((size_t)i * kMaxFan + q[h]);
+        g[0] = len_[h];
+        g[1] = mx[h];
+        g[2] = my[h];
+      }
+    }
+  }
   if (l == 0) {
-    a.deg[i] = deg;
+    a.deg[i] = deg | (lean ? kLean : 0);
+    // (if lean: deg <= kRow)
+    a.cnt[i] = (uint32_t)deg | (uint32_t)__popc(own) << 16 | (uint32_t)__popc(walls) << kWallBits;
+    a.area[i] = 0.5 * A2;
     cr.area = 0.5 * A2;
     cr.sx = xi + cx / (3.0 * A2);
     cr.sy = yi + cy / (3.0 * A2);
@@ -605,7 +732,7 @@ template <bool B, bool WALLS, bool TIERED>
 __global__ __launch_bounds__(kClipThreads) void k_rt_clip(Args one, Batch bt) {
   __shared__ ClipSlots<kSlots + (WALLS ? 4 : 0)> s_slots[kClipCells];
   int blk, nblk = gridDim.x;
-  const Args& a = block_run<B>(one, bt.cstart, bt, blk);
+  const Args& a = block_run<B>(one, bt.cstart, bt, blockIdx.x, blk);
   if ((a.bc == (int)RICH_BOUNDARY_PERIODIC) == WALLS) return;  // the other launch's run
   if (B) nblk = (a.n + kThreads - 1) / kThreads;
   const int seg = blk % kSeg;
@@ -666,7 +793,6 @@ __global__ __launch_bounds__(kClipThreads) void k_rt_clip(Args one, Batch bt) {
 // read are 360 at the rate of a large copy, and 309 us.  64 x 64 tube: a
 // chain of 24 dependent loads, 38 -> 10 us in one launch.)
 constexpr double kVertexMargin = 1e-9;  // relative margin of every vertex test
-constexpr double kVertexSin = 0.05;     // least sine of a consecutive pair's angle
 constexpr int kGroup = 8;               // lanes (and ring entries) of a cell
 constexpr int kGroupThreads = kThreads * kGroup;
 static_assert(64 % kGroup == 0, "groups do not straddle waves");
@@ -761,13 +887,7 @@ __device__ __forceinline__ bool load_ring(const Args& a, int i, bool live, Ring&
   const int l1 = l + 1 < n ? l + 1 : 0, l2 = l1 + 1 < n ? l1 + 1 : 0, lp = l > 0 ? l - 1 : n - 1;
   const double ax = r.dx, ay = r.dy;
   const double bx = __shfl(ax, l1, kGroup), by = __shfl(ay, l1, kGroup);
-  const double ha = 0.5 * (ax * ax + ay * ay), hb = 0.5 * (bx * bx + by * by);
-  const double det = ax * by - ay * bx;
-  // det = |a| |b| sin(angle); a turn of less than half a turn, by a margin
-  const bool turn = det > 0.0 && det * det > (4.0 * kVertexSin * kVertexSin) * ha * hb;
-  const double inv = 1.0 / (turn ? det : 1.0);
-  r.vx = (ha * by - hb * ay) * inv;
-  r.vy = (ax * hb - ha * bx) * inv;
+  const bool turn = ring_vertex(ax, ay, bx, by, r.vx, r.vy);
   r.r2 = group_max(l < n ? r.vx * r.vx + r.vy * r.vy : 0.0);
   ok = ok && (l >= n || turn);
   // the ring winds once: exactly one step passes angle 0
@@ -898,7 +1018,7 @@ template <bool B, bool WALLS, bool RING>
 __global__ __launch_bounds__(kGroupThreads) void k_rt_vertex(Args one, Batch bt) {
   __shared__ Fan s_fan[RING ? 1 : kThreads];
   int blk;
-  const Args& a = block_run<B>(one, bt.cstart, bt, blk);
+  const Args& a = block_run<B>(one, bt.cstart, bt, cell_block(), blk);
   if ((a.bc == (int)RICH_BOUNDARY_PERIODIC) == WALLS) return;  // the other launch's run
   const int l = (int)threadIdx.x & (kGroup - 1);
   const int i = blk * kThreads + (int)threadIdx.x / kGroup;
@@ -915,22 +1035,24 @@ __global__ __launch_bounds__(kGroupThreads) void k_rt_vertex(Args one, Batch bt)
   const int lp = l > 0 ? l - 1 : r.n - 1;
   const double ux = __shfl(r.vx, lp, kGroup), uy = __shfl(r.vy, lp, kGroup);
   const double wx = r.vx, wy = r.vy;
-  double cr = ux * wy - uy * wx;
-  const size_t s0 = (size_t)i * kMaxFan;
-  if (l < r.n) {
-    const double ex = wx - ux, ey = wy - uy;
-    const int rank = l >= r.start ? l - r.start : l - r.start + r.n;
-    a.s_nb[s0 + rank] = r.id;
-    double* g = a.s_geo + 3 * (s0 + rank);
-    g[0] = sqrt(ex * ex + ey * ey);
-    g[1] = r.xi + 0.5 * (ux + wx);
-    g[2] = r.yi + 0.5 * (uy + wy);
-  } else {
-    cr = 0.0;
-  }
+  const double ex = wx - ux, ey = wy - uy;
+  const int rank = l >= r.start ? l - r.start : l - r.start + r.n;
+  const double cr = l < r.n ? ux * wy - uy * wx : 0.0;
+  if (l < r.n) a.s_nb[(size_t)i * kRow + rank] = r.id;
   const double A2 = group_sum(cr);
   const double sx = group_sum(cr * (ux + wx)), sy = group_sum(cr * (uy + wy));
-  if (l == 0) a.deg[i] = r.n;
+  const double l2 = -group_max(l < r.n ? -(ex * ex + ey * ey) : -INFINITY);
+  const bool lean = lean_cell(a, l2, r.r2, 0.5 * A2);
+  const uint32_t own = group_bits(l < r.n && i < r.c);
+  if (l == 0) {
+    a.deg[i] = r.n | (lean ? kLean : 0);
+    a.cnt[i] = (uint32_t)r.n | (uint32_t)__popc(own) << 16;   // (if lean)
+    a.area[i] = 0.5 * A2;
+  }
+  if (!lean && l < r.n) {
+    double* g = a.s_geo + 3 * ((size_t)i * kMaxFan + rank);
+    edge_geometry(r.xi, r.yi, ux, uy, wx, wy, g[0], g[1], g[2]);
+  }
   // the cell record, a 16-byte part per lane
   double2* cell = reinterpret_cast<double2*>(a.cells + i);
   if (l == 0) cell[0] = make_double2(r.xi, r.yi);
@@ -950,7 +1072,7 @@ __global__ __launch_bounds__(kThreads) void k_rt_near(Args one, Batch bt) {
   __shared__ int s_list[kThreads];
   static_assert(kThreads == 64, "a block is one wave");
   int blk;
-  const Args& a = block_run<B>(one, bt.cstart, bt, blk);
+  const Args& a = block_run<B>(one, bt.cstart, bt, cell_block(), blk);
   if ((a.bc == (int)RICH_BOUNDARY_PERIODIC) == WALLS) return;  // the other launch's run
   const int lane = (int)threadIdx.x;
   bool near = false;
@@ -979,138 +1101,10 @@ __global__ __launch_bounds__(kThreads) void k_rt_near(Args one, Batch bt) {
 }
 
 // ---------------------------------------------------------------------------
-// keep / own, certification, counts.  This kernel and emit give each cell a
-// group of kGroup lanes too, one per slot; a block still covers kThreads
-// cells.
-// ---------------------------------------------------------------------------
-template <bool B>
-__global__ __launch_bounds__(kGroupThreads) void k_rt_classify(Args one, Batch bt) {
-  int blk;
-  const Args& a = block_run<B>(one, bt.cstart, bt, blk);
-  constexpr int NW = kGroupThreads / 64;
-  __shared__ double s_area[NW];
-  __shared__ long long s_drop[NW], s_wall[NW];
-  const int l = (int)threadIdx.x % kGroup;
-  const int i = blk * kThreads + (int)threadIdx.x / kGroup;
-  double area = 0.0;
-  long long drop = 0, walls = 0;
-  int n_keep = 0, n_own = 0, bad = 0;
-  if (i < a.n) {
-    const int d = a.deg[i];
-    const double Ai = a.cells[i].area;
-    if (l == 0) {
-      area = Ai;
-      if (d == 0 || !(Ai > 0.0)) bad |= RICH_RETESS_CLIP;
-    }
-    const double Ri = sqrt(Ai / kPi);
-    const size_t s0 = (size_t)i * kMaxFan;
-    int kept_before = 0;   // kept slots of the group's earlier rounds
-    for (int q = l; q < d; q += kGroup) {
-      const int32_t id = a.s_nb[s0 + q];
-      const int j = (int)((uint32_t)id & kMask);
-      const int code = (int)((uint32_t)id >> kShift);
-      const double Rj = sqrt(a.cells[j].area / kPi);
-      const double* g = a.s_geo + 3 * (s0 + q);
-      const double L = g[0];
-      const bool keep = L >= 1e-12 * 0.5 * (Ri + Rj);
-      bool own;
-      if (code >= kWallX0) own = true;
-      else if (j != i) own = i < j;
-      else own = code >= 5;
-      // a kept slot's rank among the cell's kept slots (its CSR position)
-      const uint32_t km = group_bits(keep);
-      const int rank = kept_before + __popc(km & ((1u << l) - 1u));
-      kept_before += __popc(km);
-      a.s_flag[s0 + q] = (uint8_t)((keep ? 1 : 0) | (keep && own ? 2 : 0) | (rank << 2));
-      if (!keep) {
-        ++drop;
-        continue;
-      }
-      ++n_keep;
-      if (own) ++n_own;
-      if (code >= kWallX0) {
-        ++walls;
-        continue;
-      }
-      // the owner finds the same edge in the neighbour's slots; that every
-      // other kept slot is such a match follows from the counts (checked
-      // once they are summed: kept = 2 owned - walls)
-      if (!own) continue;
-      const int32_t want = pack(i, back_code(code));
-      const int dj = a.deg[j];
-      const size_t t0 = (size_t)j * kMaxFan;
-      // the first match among the neighbour's slots: its first eight in two
-      // 16-byte loads (a row holds kMaxFan slots, so they are in bounds;
-      // those past its degree are ignored), the rest one at a time
-      static_assert(kMaxFan >= 8 && (kMaxFan * 4) % 16 == 0, "rows of 16-byte chunks");
-      const int4* rowv = reinterpret_cast<const int4*>(a.s_nb + t0);
-      const int4 v0 = rowv[0], v1 = rowv[1];
-      const int32_t ids[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
-      int found = -1;
-#pragma unroll
-      for (int t = 7; t >= 0; --t)
-        if (t < dj && ids[t] == want) found = t;
-      for (int t = 8; found < 0 && t < dj; ++t)
-        if (a.s_nb[t0 + t] == want) found = t;
-      if (found < 0) { bad |= RICH_RETESS_ASYM; continue; }
-      a.s_back[s0 + q] = (uint8_t)found;
-      const double* gj = a.s_geo + 3 * (t0 + found);
-      const double Lj = gj[0];
-      double fxj = gj[1], fyj = gj[2];
-      if (code != 0) {  // the neighbour sees the edge one image away
-        int sx, sy;
-        code_shift(code, sx, sy);
-        fxj += sx * a.Lx;
-        fyj += sy * a.Ly;
-      }
-      const double tol = 1e-9 * (Ri + Rj);
-      if (!(Lj >= 1e-12 * 0.5 * (Ri + Rj)) || fabs(L - Lj) > tol ||
-          fabs(g[1] - fxj) > tol || fabs(g[2] - fyj) > tol)
-        bad |= RICH_RETESS_ASYM;
-    }
-  }
-  // the cell's counts and flags over its group
-  for (int o = kGroup / 2; o > 0; o >>= 1) {
-    n_keep += __shfl_xor(n_keep, o);
-    n_own += __shfl_xor(n_own, o);
-    bad |= __shfl_xor(bad, o);
-  }
-  if (i < a.n && l == 0) {
-    if (bad) atomicOr(&a.hdr->flags, bad);
-    a.cnt[i] = (uint32_t)n_keep | (uint32_t)n_own << 16;  // the scan makes them offsets
-  }
-  // block sums of the areas and of the dropped edges
-  for (int o = 32; o > 0; o >>= 1) {
-    area += __shfl_xor(area, o);
-    drop += __shfl_xor(drop, o);
-    walls += __shfl_xor(walls, o);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    s_area[threadIdx.x >> 6] = area;
-    s_drop[threadIdx.x >> 6] = drop;
-    s_wall[threadIdx.x >> 6] = walls;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    CPart c;
-    c.area = 0.0;
-    c.drop = 0;
-    c.walls = 0;
-    c.pad = 0;
-    for (int w = 0; w < NW; ++w) {
-      c.area += s_area[w];
-      c.drop += s_drop[w];
-      c.walls += s_wall[w];
-    }
-    a.cpart[blk] = c;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// prefix sums of the kept / owned counts.  Offsets are kept as a cell's
-// prefix within its scan block (cnt, both counts in one word) plus the
-// block's own offset (bsum); emit adds the two and writes off[] and eoff[],
-// which spares a launch and a pass over the cells.
+// kept and owned edges of each cell, and their prefix sums.  Offsets are kept
+// as a cell's prefix within its scan block (cnt, both counts in one word)
+// plus the block's own offset (bsum); emit adds the two and writes off[] and
+// eoff[], which spares a launch and a pass over the cells.
 // ---------------------------------------------------------------------------
 static_assert(kScanThreads * kMaxFan < (1 << 16), "a scan block's counts fit 16 bits");
 
@@ -1137,39 +1131,88 @@ __device__ __forceinline__ T block_scan(T v, T* s, T& total) {
   return v + before;
 }
 
+// One thread per cell: the counts (of a lean cell they are there already),
+// their scan over the block and the block's sums.  A slot is kept unless its
+// edge is shorter than 1e-12 of the two cells' mean radius; a kept edge is
+// owned by its lower cell (by its image code where a cell meets itself), a
+// wall's by its cell.
 template <bool B>
-__global__ __launch_bounds__(kScanThreads) void k_rt_scan_local(Args one, Batch bt) {
+__global__ __launch_bounds__(kScanThreads) void k_rt_count(Args one, Batch bt) {
   int blk;
-  const Args& a = block_run<B>(one, bt.sstart, bt, blk);
-  __shared__ uint32_t s[kScanThreads / 64];
+  const Args& a = block_run<B>(one, bt.sstart, bt, blockIdx.x, blk);
+  constexpr int NW = kScanThreads / 64;
+  __shared__ uint32_t s[NW];
+  __shared__ double s_area[NW];
+  __shared__ int s_drop[NW], s_wall[NW];
   const int i = blk * kScanThreads + threadIdx.x;
-  const uint32_t v = i < a.n ? a.cnt[i] : 0u;
+  uint32_t v = 0;
+  double area = 0.0;
+  int drop = 0, walls = 0;
+  if (i < a.n) {
+    const int di = max(a.deg[i], 0);
+    area = a.area[i];
+    v = a.cnt[i];
+    if (di == 0 || !(area > 0.0)) atomicOr(&a.hdr->flags, RICH_RETESS_CLIP);
+    if (!(di & kLean)) {
+      const double Ri = sqrt(area / kPi);
+      const size_t s0 = (size_t)i * kMaxFan;
+      int n_keep = 0, n_own = 0;
+      for (int q = 0; q < di; ++q) {
+        const int32_t id = slot_nb(a, i, q);
+        const int j = (int)((uint32_t)id & kMask);
+        const int code = (int)((uint32_t)id >> kShift);
+        const bool keep = a.s_geo[3 * (s0 + q)] >= 1e-12 * 0.5 * (Ri + sqrt(a.area[j] / kPi));
+        const bool own = code >= kWallX0 || (j != i ? i < j : code >= 5);
+        // (a kept slot's rank among the cell's kept ones is its CSR position)
+        a.s_flag[s0 + q] = (uint8_t)((keep ? 1 : 0) | (keep && own ? 2 : 0) | (n_keep << 2));
+        if (keep) {
+          ++n_keep;
+          if (own) ++n_own;
+          if (code >= kWallX0) ++walls;
+        } else {
+          ++drop;
+        }
+      }
+      v = (uint32_t)n_keep | (uint32_t)n_own << 16;
+    } else {
+      walls = (int)(v >> kWallBits);
+      v &= (1u << kWallBits) - 1u;
+    }
+  }
+  for (int o = 32; o > 0; o >>= 1) area += __shfl_xor(area, o);
+  if (__any(drop != 0 || walls != 0)) {
+    for (int o = 32; o > 0; o >>= 1) {
+      drop += __shfl_xor(drop, o);
+      walls += __shfl_xor(walls, o);
+    }
+  }
+  if ((threadIdx.x & 63) == 0) {
+    s_area[threadIdx.x >> 6] = area;
+    s_drop[threadIdx.x >> 6] = drop;
+    s_wall[threadIdx.x >> 6] = walls;
+  }
   uint32_t total;
-  const uint32_t inc = block_scan(v, s, total);
+  const uint32_t inc = block_scan(v, s, total);   // (its barrier also publishes the sums)
   if (i < a.n) a.cnt[i] = inc - v;   // (no borrow: both halves grow along the block)
   if (threadIdx.x == 0) {
+    CPart c;
+    c.area = 0.0;
+    c.drop = 0;
+    c.walls = 0;
+    c.pad = 0;
+    for (int w = 0; w < NW; ++w) {
+      c.area += s_area[w];
+      c.drop += s_drop[w];
+      c.walls += s_wall[w];
+    }
+    a.cpart[blk] = c;
     a.bsum[blk] = total & 0xFFFFu;
     a.bsum[a.n_scan_blocks + blk] = total >> 16;
   }
-  // the sums of the classify blocks of this block's cells, in order, into
-  // the first of them (the scan of the block totals reads only those)
-  constexpr int CPB = kScanThreads / kThreads;
-  const int nc = (a.n + kThreads - 1) / kThreads;
-  if (threadIdx.x == 0) {
-    CPart c = a.cpart[blk * CPB];
-    for (int t = 1; t < CPB && blk * CPB + t < nc; ++t) {
-      const CPart p = a.cpart[blk * CPB + t];
-      c.area += p.area;
-      c.drop += p.drop;
-      c.walls += p.walls;
-    }
-    a.cpart[blk * CPB] = c;
-  }
 }
 
-// One block: exclusive scan of the block totals, totals, the checks that
-// need every cell (areas, capacities) and the finished result header (the
-// flags folded into the sticky word, the cells queued for the clip counted).
+// One block: exclusive scan of the block totals, totals, the cells queued for
+// the clip counted, and the checks that need every cell (areas, capacities).
 // The totals go through one scan over the block's threads (each thread's
 // run of scan blocks first); a single thread adding 1024 of them took 22 of
 // this kernel's 25 us, the same for every mesh size.
@@ -1181,17 +1224,15 @@ __global__ __launch_bounds__(kScanThreads) void k_rt_scan_blocks(Args one, Batch
   __shared__ double s_area[NW];
   __shared__ long long s_drop[NW], s_wall[NW];
   __shared__ int s_clip;
-  // the classify blocks' sums (those of each scan block gathered by
-  // k_rt_scan_local): each thread every kScanThreads-th scan block, a fixed
-  // xor tree over each wave, then thread 0 over the waves in order (a fixed
-  // order throughout, so the area sum is reproducible)
+  // the blocks' sums: each thread every kScanThreads-th block, a fixed xor
+  // tree over each wave, then thread 0 over the waves in order (a fixed order
+  // throughout, so the area sum is reproducible)
   const int nb = a.n_scan_blocks;
   {
-    constexpr int CPB = kScanThreads / kThreads;   // classify blocks per scan block
     double ar = 0.0;
     long long dr = 0, wl = 0;
     for (int c = threadIdx.x; c < nb; c += kScanThreads) {
-      const CPart p = a.cpart[c * CPB];
+      const CPart p = a.cpart[c];
       ar += p.area;
       dr += p.drop;
       wl += p.walls;
@@ -1251,18 +1292,55 @@ __global__ __launch_bounds__(kScanThreads) void k_rt_scan_blocks(Args one, Batch
     if (t0 != 2 * t1 - wl) h.flags |= RICH_RETESS_ASYM;   // an unmatched kept slot
     const double box = a.Lx * a.Ly;
     if (!(fabs(ar - box) <= 1e-10 * box)) h.flags |= RICH_RETESS_AREA;
-    h.sticky |= h.flags;
     *a.hdr = h;
-    if (B) {
-      bt.hdr_out[blockIdx.x] = h;
-      bt.flags_out[blockIdx.x] = h.flags;
-    }
   }
 }
 
 // ---------------------------------------------------------------------------
-// edge records and CSR entries
+// edge records and CSR entries, certification
 // ---------------------------------------------------------------------------
+// Length and midpoint of the edge at slot q of cell c (degree word d).
+__device__ __forceinline__ void slot_geometry(const Args& a, int c, int d, int q, double& len,
+                                              double& mx, double& my) {
+  if (!(d & kLean)) {
+    const double* g = a.s_geo + 3 * ((size_t)c * kMaxFan + q);
+    len = g[0];
+    mx = g[1];
+    my = g[2];
+    return;
+  }
+  const int n = d & (kLean - 1);
+  const double2 pc = a.xy[c];
+  double x[3], y[3];   // the slots before, at and after q
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const int t = q + k - 1;
+    const int32_t id = a.s_nb[(size_t)c * kRow + (t < 0 ? n - 1 : t < n ? t : 0)];
+    slot_displacement(a, pc.x, pc.y, id, a.xy[(uint32_t)id & kMask], x[k], y[k]);
+  }
+  double ux, uy, wx, wy;
+  ring_vertex(x[0], y[0], x[1], y[1], ux, uy);
+  ring_vertex(x[1], y[1], x[2], y[2], wx, wy);
+  edge_geometry(pc.x, pc.y, ux, uy, wx, wy, len, mx, my);
+}
+
+// Whether the neighbour at image `to` seen from a cell, its neighbour at
+// image `then` and the cell's own neighbour at image `both` are one point (or
+// the two cells' mirror images across one wall: the bisector of the cells
+// meets the wall in one point).
+__device__ __forceinline__ bool same_point(int32_t to, int32_t then, int32_t both) {
+  const int c0 = (int)((uint32_t)to >> kShift), c1 = (int)((uint32_t)then >> kShift),
+            c2 = (int)((uint32_t)both >> kShift);
+  if (c1 >= kWallX0 || c2 >= kWallX0) return c1 == c2;
+  if (((uint32_t)(then ^ both) & kMask) != 0u) return false;
+  if ((c0 | c1 | c2) == 0) return true;
+  int s[3][2] = {};
+  if (c0) code_shift(c0, s[0][0], s[0][1]);
+  if (c1) code_shift(c1, s[1][0], s[1][1]);
+  if (c2) code_shift(c2, s[2][0], s[2][1]);
+  return s[0][0] + s[1][0] == s[2][0] && s[0][1] + s[1][1] == s[2][1];
+}
+
 // First CSR entry / first owned edge of cell c: its scan block's offset plus
 // its own within the block.
 __device__ __forceinline__ int csr_offset(const Args& a, int c) {
@@ -1272,60 +1350,213 @@ __device__ __forceinline__ int edge_offset(const Args& a, int c) {
   return (int)a.bsum[a.n_scan_blocks + c / kScanThreads] + (int)(a.cnt[c] >> 16);
 }
 
+// Slot of cell j (of n edges) that names `want`, or -1: its row in two
+// 16-byte loads (what lies past its edges is ignored), the rest one at a time.
+__device__ __forceinline__ int find_slot(const Args& a, int j, int n, int32_t want) {
+  const int4* row = reinterpret_cast<const int4*>(a.s_nb + (size_t)j * kRow);
+  const int4 v0 = row[0], v1 = row[1];
+  const int32_t ids[kRow] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+  int found = -1;
+#pragma unroll
+  for (int t = kRow - 1; t >= 0; --t) found = t < n && ids[t] == want ? t : found;
+  for (int t = kRow; found < 0 && t < n; ++t)
+    if (slot_nb(a, j, t) == want) found = t;
+  return found;
+}
+
 // Each cell writes, for every edge it owns (its owned slots in slot order
 // from eoff[i]): the edge record, its own CSR entry 2 e at the slot's rank
 // among its kept slots, and, unless the edge is a wall, the neighbour's entry
 // 2 e + 1 at the rank among the neighbour's kept slots of the slot that sees
-// the edge (classify stored each kept slot's rank in its flag byte).  A certified mesh has every kept slot the owned or the other side
-// of exactly one owned edge (classify matched each owned edge to one slot of
-// the neighbour, and kept = 2 owned - walls), so each CSR entry is written
-// once, and each cell's entries run counter-clockwise (slot order).  A
-// failed re-tessellation leaves a mesh without edges.
+// the edge.  In a certified mesh every kept slot is the owned or the other
+// side of exactly one owned edge (each owned edge is found in one slot of the
+// neighbour, and kept = 2 owned - walls), so each CSR entry is written once,
+// and each cell's entries run counter-clockwise (slot order).
+//
+// Both cells must see the same edge.  Between two lean cells that is so when
+// the two points beside the other in both rows are the same ones: the edge
+// runs between the same two circumcentres then, and what rounding can put
+// between two computations of them is below the tolerance (lean_cell).  Any
+// other pair is marked for k_rt_end to compare.
+//
+// A lane per slot; the geometry of lean cells' edges is computed from the
+// points here.  (One kernel compared the stored geometry of every pair and
+// another read it again for the records: 550 + 415 us on the 2048 x 2048
+// wave, this 470.)
 template <bool B>
 __global__ __launch_bounds__(kGroupThreads) void k_rt_emit(Args one, Batch bt) {
   int blk;
-  const Args& a = block_run<B>(one, bt.cstart, bt, blk);
+  const Args& a = block_run<B>(one, bt.cstart, bt, cell_block(), blk);
   const int l = (int)threadIdx.x % kGroup;
   const int i = blk * kThreads + (int)threadIdx.x / kGroup;
   if (i >= a.n) return;  // whole groups
-  const bool failed = a.hdr->flags != 0;
+  const bool failed = a.hdr->flags != 0;   // (offsets may be past the buffers)
   const int k = csr_offset(a, i);
   int e = edge_offset(a, i);
+  const int di = max(a.deg[i], 0);
+  const int d = di & (kLean - 1);
   if (l == 0) {
-    a.off[i] = failed ? 0 : k;
-    a.eoff[i] = failed ? 0 : e;
+    a.off[i] = k;
+    a.eoff[i] = e;
     if (i == a.n - 1) {   // the totals close the offsets
-      a.off[a.n] = failed ? 0 : (int32_t)a.hdr->n_csr;
-      a.eoff[a.n] = failed ? 0 : (int32_t)a.hdr->n_edges;
+      a.off[a.n] = (int32_t)a.hdr->n_csr;
+      a.eoff[a.n] = (int32_t)a.hdr->n_edges;
     }
   }
-  if (failed) return;
-  const int d = a.deg[i];
-  const size_t s0 = (size_t)i * kMaxFan;
-  for (int base = 0; base < d; base += kGroup) {
-    const int q = base + l;
-    const uint8_t f = q < d ? a.s_flag[s0 + q] : (uint8_t)0;
-    const uint32_t mo = group_bits((f & 3) == 3);
-    const uint32_t below = (1u << l) - 1u;
-    if ((f & 3) == 3) {
-      const int ee = e + __popc(mo & below);
-      const int32_t id = a.s_nb[s0 + q];
-      const double* g = a.s_geo + 3 * (s0 + q);
-      rich_edge r;
-      r.fx = g[1];
-      r.fy = g[2];
-      r.len = g[0];
-      r.i = i;
-      r.j = id;
-      a.edges[ee] = r;
-      a.idx[k + (f >> 2)] = 2 * ee;
-      if ((int)((uint32_t)id >> kShift) < kWallX0) {
-        const int j = (int)((uint32_t)id & kMask);
-        const int t = a.s_back[s0 + q];
-        a.idx[csr_offset(a, j) + (a.s_flag[(size_t)j * kMaxFan + t] >> 2)] = 2 * ee + 1;
+  // slot q's match in the neighbour and, if it has one, edge ee: the record
+  // and both cells' CSR entries
+  bool bad = false, later = false;
+  auto put = [&](int q, int rank, int ee, int32_t id, int32_t prev, int32_t next, double len,
+                 double mx, double my) {
+    const int code = (int)((uint32_t)id >> kShift);
+    const int j = (int)((uint32_t)id & kMask);
+    int entry = -1;   // of the neighbour
+    if (code < kWallX0) {
+      const int dj = max(a.deg[j], 0);
+      const int nj = dj & (kLean - 1);
+      const int t = find_slot(a, j, nj, pack(i, back_code(code)));
+      if (t < 0) {
+        bad = true;
+        return;
+      }
+      int place = t;
+      later = true;
+      if (dj & kLean) {
+        const int32_t* row = a.s_nb + (size_t)j * kRow;   // (just loaded: cached)
+        if (di & kLean)
+          later = !(same_point(id, row[t > 0 ? t - 1 : nj - 1], next) &&
+                    same_point(id, row[t + 1 < nj ? t + 1 : 0], prev));
+      } else {
+        const uint8_t f = a.s_flag[(size_t)j * kMaxFan + t];
+        if (!(f & 1)) {   // the neighbour drops it
+          bad = true;
+          return;
+        }
+        place = f >> 2;
+      }
+      entry = csr_offset(a, j) + place;
+    }
+    if (failed) return;
+    rich_edge r;
+    r.fx = mx;
+    r.fy = my;
+    r.len = len;
+    r.i = i;
+    r.j = id;
+    a.edges[ee] = r;
+    a.idx[k + rank] = 2 * ee;
+    if (entry >= 0) a.idx[entry] = 2 * ee + 1;
+  };
+  const uint32_t below = (1u << l) - 1u;
+  uint32_t chk = 0;
+  if (di & kLean) {   // every slot kept; no image of the cell itself
+    static_assert(kGroup == kRow, "a lane per slot of a row");
+    const int32_t id = l < d ? a.s_nb[(size_t)i * kRow + l] : 0;
+    const int j = (int)((uint32_t)id & kMask);
+    const double2 pi = a.xy[i];
+    double dx, dy;
+    slot_displacement(a, pi.x, pi.y, id, a.xy[j], dx, dy);
+    const int ln = l + 1 < d ? l + 1 : 0, lp = l > 0 ? l - 1 : d - 1;
+    const int32_t next = __shfl(id, ln, kGroup), prev = __shfl(id, lp, kGroup);
+    const double bx = __shfl(dx, ln, kGroup), by = __shfl(dy, ln, kGroup);
+    double wx, wy;
+    ring_vertex(dx, dy, bx, by, wx, wy);
+    const double ux = __shfl(wx, lp, kGroup), uy = __shfl(wy, lp, kGroup);
+    const bool own = l < d && (i < j || (int)((uint32_t)id >> kShift) >= kWallX0);
+    const uint32_t mo = group_bits(own);
+    if (own) {
+      double len, mx, my;
+      edge_geometry(pi.x, pi.y, ux, uy, wx, wy, len, mx, my);
+      put(l, l, e + __popc(mo & below), id, prev, next, len, mx, my);
+    }
+    chk = group_bits(later);
+  } else {
+    const size_t s0 = (size_t)i * kMaxFan;
+    for (int base = 0; base < d; base += kGroup) {
+      const int q = base + l;
+      const uint8_t f = q < d ? a.s_flag[s0 + q] : (uint8_t)0;
+      const bool own = (f & 3) == 3;
+      const uint32_t mo = group_bits(own);
+      later = false;
+      if (own) {
+        const double* g = a.s_geo + 3 * (s0 + q);
+        put(q, f >> 2, e + __popc(mo & below), slot_nb(a, i, q), 0, 0, g[0], g[1], g[2]);
+      }
+      chk |= group_bits(later) << base;
+      e += __popc(mo);
+    }
+  }
+  if (l == 0) a.chk[i] = chk;
+  if (bad) atomicOr(&a.hdr->flags, RICH_RETESS_ASYM);
+}
+
+// Compares the edges that emit left (a thread per cell), and closes the
+// rebuild: the last block to finish folds the flags into the sticky word,
+// and leaves a failed re-tessellation without edges.  A block's verdict and
+// its count go to one word, verdict first, so that the block that completes
+// the count holds every verdict without a fence (a device fence writes back
+// the L2: 960 us with one in each wave of the 2048 x 2048 wave, 12 without).
+constexpr uint32_t kUnlike = 1u << 31;
+constexpr int kEndMaxBlocks = 256;   // of one run: the counts meet on one address, 12 ns each
+static_assert(kMask / kScanThreads < kUnlike, "the count of a run's blocks stays below the verdict");
+template <bool B>
+__global__ __launch_bounds__(kScanThreads) void k_rt_end(Args one, Batch bt) {
+  int blk;
+  const int run = B ? run_of_block(bt.sstart, bt.n_runs, blockIdx.x) : 0;
+  const Args& a = block_run<B>(one, bt.sstart, bt, blockIdx.x, blk);
+  __shared__ int s_bad, s_flags;   // s_flags: of a finished rebuild, else 0
+  if (threadIdx.x == 0) s_bad = s_flags = 0;
+  __syncthreads();
+  const int blocks = B ? a.n_scan_blocks : gridDim.x;   // of this run
+  for (int i = blk * kScanThreads + threadIdx.x; i < a.n; i += blocks * kScanThreads)
+  for (uint32_t chk = a.chk[i]; chk != 0u; chk &= chk - 1u) {
+    const int q = __ffs(chk) - 1;
+    const int32_t id = slot_nb(a, i, q);
+    const int j = (int)((uint32_t)id & kMask), code = (int)((uint32_t)id >> kShift);
+    const int di = a.deg[i], dj = a.deg[j];
+    const int t = find_slot(a, j, dj & (kLean - 1), pack(i, back_code(code)));   // (emit found it)
+    if (t < 0) {
+      s_bad = 1;
+      continue;
+    }
+    double L, fx, fy, Lj, fxj, fyj;
+    slot_geometry(a, i, di, q, L, fx, fy);
+    slot_geometry(a, j, dj, t, Lj, fxj, fyj);
+    if (code != 0) {  // the neighbour sees the edge one image away
+      int sx, sy;
+      code_shift(code, sx, sy);
+      fxj += sx * a.Lx;
+      fyj += sy * a.Ly;
+    }
+    const double Ri = sqrt(a.area[i] / kPi), Rj = sqrt(a.area[j] / kPi);
+    const double tol = 1e-9 * (Ri + Rj);
+    if (!(Lj >= 1e-12 * 0.5 * (Ri + Rj)) || fabs(L - Lj) > tol ||
+        fabs(fx - fxj) > tol || fabs(fy - fyj) > tol)
+      s_bad = 1;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (s_bad) atomicOr(&a.hdr->done, kUnlike);
+    const uint32_t w = atomicAdd(&a.hdr->done, 1u);
+    if ((w & ~kUnlike) == (uint32_t)blocks - 1u) {
+      Hdr h = *a.hdr;   // (nobody else writes the rest of it in this launch)
+      if (w & kUnlike) h.flags |= RICH_RETESS_ASYM;
+      h.sticky |= h.flags;
+      a.hdr->flags = h.flags;
+      a.hdr->sticky = h.sticky;
+      s_flags = h.flags;
+      if (B) {
+        bt.hdr_out[run] = h;
+        bt.flags_out[run] = h.flags;
       }
     }
-    e += __popc(mo);
+  }
+  __syncthreads();
+  if (s_flags != 0) {
+    for (int c = threadIdx.x; c <= a.n; c += kScanThreads) {
+      a.off[c] = 0;
+      a.eoff[c] = 0;
+    }
   }
 }
 
@@ -1351,7 +1582,7 @@ void rt_capacity(int64_t n, int64_t* ce, int64_t* cc) {
 }
 
 struct RtLayout {
-  size_t deg, s_nb, s_geo, s_flag, s_back, cnt, bsum, cpart, qcnt, queue, xy, nbr, total;
+  size_t deg, area, s_nb, s_nbx, s_geo, s_flag, cnt, chk, bsum, cpart, qcnt, queue, xy, nbr, total;
   int64_t nbr_cap;
   int nb, qcap;
 };
@@ -1362,15 +1593,17 @@ RtLayout rt_layout(int64_t n) {
   L.nb = (int)((n + retess::kScanThreads - 1) / retess::kScanThreads);
   size_t o = 256;  // result header
   L.deg = o;    o += rt_align(4 * (size_t)n);
-  L.s_nb = o;   o += rt_align(4 * slots);
+  const size_t row = (size_t)n * retess::kRow, rest = slots - row;
+  L.area = o;   o += rt_align(8 * (size_t)n);
+  L.s_nb = o;   o += rt_align(4 * row);
+  L.s_nbx = o;  o += rt_align(4 * rest);
   L.s_geo = o;  o += rt_align(24 * slots);
   L.s_flag = o; o += rt_align(slots);
-  L.s_back = o; o += rt_align(slots);
   L.cnt = o;    o += rt_align(4 * (size_t)n);
+  L.chk = o;    o += rt_align(4 * (size_t)n);
   L.bsum = o;   o += rt_align(16 * (size_t)L.nb);
-  L.cpart = o;
+  L.cpart = o;  o += rt_align(sizeof(retess::CPart) * (size_t)L.nb);
   const int64_t blocks = (n + retess::kThreads - 1) / retess::kThreads;
-  o += rt_align(sizeof(retess::CPart) * (size_t)blocks);
   L.qcnt = o;   o += rt_align(4 * (size_t)retess::kSeg * retess::kSegStride);
   L.qcap = (int)(retess::kThreads * ((blocks + retess::kSeg - 1) / retess::kSeg));
   L.queue = o;  o += rt_align(4 * (size_t)retess::kSeg * (size_t)L.qcap);
@@ -1428,7 +1661,9 @@ int make_args(const rich_mesh* prev, const double* x, const double* y,
   a.s_nb = reinterpret_cast<int32_t*>(w + L.s_nb);
   a.s_geo = reinterpret_cast<double*>(w + L.s_geo);
   a.s_flag = reinterpret_cast<uint8_t*>(w + L.s_flag);
-  a.s_back = reinterpret_cast<uint8_t*>(w + L.s_back);
+  a.area = reinterpret_cast<double*>(w + L.area);
+  a.s_nbx = reinterpret_cast<int32_t*>(w + L.s_nbx);
+  a.chk = reinterpret_cast<uint32_t*>(w + L.chk);
   a.cnt = reinterpret_cast<uint32_t*>(w + L.cnt);
   a.bsum = reinterpret_cast<int64_t*>(w + L.bsum);
   a.cpart = reinterpret_cast<retess::CPart*>(w + L.cpart);
@@ -1444,6 +1679,8 @@ int make_args(const rich_mesh* prev, const double* x, const double* y,
   a.y1 = prev->box[3];
   a.Lx = a.x1 - a.x0;
   a.Ly = a.y1 - a.y0;
+  a.size = std::max(a.Lx, a.Ly);
+  for (int k = 0; k < 4; ++k) a.size = std::max(a.size, std::fabs(prev->box[k]));
   a.n = (int32_t)n;
   a.bc = (int32_t)prev->bc;
   a.n_scan_blocks = L.nb;
@@ -1475,10 +1712,11 @@ void launch_all(const retess::Args& a, const retess::Batch& bt, int gc, int gs, 
   hipLaunchKernelGGL(k_rt_begin<B>, dim3(gc), dim3(kThreads), 0, st, a, bt);
   if (walls) launch_cells<B, true>(a, bt, gc, gq, tiered, st);
   if (periodic) launch_cells<B, false>(a, bt, gc, gq, tiered, st);
-  hipLaunchKernelGGL(k_rt_classify<B>, dim3(gc), dim3(kGroupThreads), 0, st, a, bt);
-  hipLaunchKernelGGL(k_rt_scan_local<B>, dim3(gs), dim3(kScanThreads), 0, st, a, bt);
+  hipLaunchKernelGGL(k_rt_count<B>, dim3(gs), dim3(kScanThreads), 0, st, a, bt);
   hipLaunchKernelGGL(k_rt_scan_blocks<B>, dim3(n_runs), dim3(kScanThreads), 0, st, a, bt);
   hipLaunchKernelGGL(k_rt_emit<B>, dim3(gc), dim3(kGroupThreads), 0, st, a, bt);
+  hipLaunchKernelGGL(k_rt_end<B>, dim3(B ? gs : std::min(gs, kEndMaxBlocks)), dim3(kScanThreads),
+                     0, st, a, bt);
 }
 
 // Batch workspace: descriptors, the two start tables, result headers, flags.

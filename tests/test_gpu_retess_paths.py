@@ -76,3 +76,35 @@ def test_both_paths_give_the_same_mesh(name, k, move):
     st1, info1 = R.rich_retess_result(ws[1])
     assert (st1, info1) == res[1]
     assert _bytes(alone[1], info1) == _bytes(both[1], info1)
+
+
+@pytest.mark.parametrize("name,k", [("wave", 40), ("sod", 41), ("random_walls", 40)])
+def test_stored_and_recomputed_geometry_agree(name, k):
+    """In a box whose coordinates are large against its cells the cells' edges
+    are stored and compared; elsewhere they are recomputed from the points.
+    The same points (on a grid of 2^-30, so that the shift by 2048 is exact)
+    give the same indices either way, and lengths and midpoints to rounding:
+    1e-13 of a unit box for values computed alike up to the order of a few
+    operations, plus the 2.3e-13 that a coordinate near 2048 is rounded by."""
+    import torch
+    from paper_1410_3219_amd import rich as R
+    grid = 2.0 ** -30
+    m = _mesh(name, k)
+    pts = np.round(np.stack([m.px, m.py]) / grid) * grid
+    new = np.round(_moved(m, 0.0 if name.startswith("random") else 0.02) / grid) * grid
+    out = []
+    for s in (0.0, 2048.0):
+        h = T.rich_tess_build(pts[0] + s, pts[1] + s, [v + s for v in m.box], m.bc)
+        X = torch.from_numpy(new + s).cuda()
+        b, ws = R.DeviceMeshBufs(h.n_cells, h.box, h.bc), R.retess_workspace(h.n_cells)
+        R.rich_retess(R.DeviceMesh.from_host(h), X, b, ws)
+        st, info = R.rich_retess_result(ws)
+        assert st == R.RICH_OK, info
+        t = {q: v.cpu().numpy() for q, v in b.t.items()}
+        e = t["edges"][:32 * info["n_edges"]].view(np.float64).reshape(-1, 4)
+        out.append((t["off"], t["eoff"], t["idx"][:info["n_csr"]],
+                    e.view(np.int32).reshape(-1, 8)[:, 6:], e[:, :2] - s, e[:, 2]))
+    for a, b in zip(out[0][:4], out[1][:4]):
+        assert np.array_equal(a, b)
+    assert np.abs(out[0][5] - out[1][5]).max() < 1e-13
+    assert np.abs(out[0][4] - out[1][4]).max() < 1e-13 + 2.3e-13
