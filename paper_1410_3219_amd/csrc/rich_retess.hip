@@ -260,6 +260,71 @@ __global__ __launch_bounds__(kThreads) void k_rt_begin(Args one, Batch bt) {
 }
 
 // ---------------------------------------------------------------------------
+// groups of lanes
+// ---------------------------------------------------------------------------
+// kGroup lanes work on a cell: one per neighbour, candidate or slot.
+constexpr int kGroup = 8;               // lanes (and ring entries) of a cell
+constexpr int kGroupThreads = kThreads * kGroup;
+static_assert(64 % kGroup == 0, "groups do not straddle waves");
+
+// The group's bits of a wave-wide ballot.
+__device__ __forceinline__ uint32_t group_bits(bool v) {
+  const unsigned long long m = __ballot(v);
+  const int first = (int)(threadIdx.x & 63) & ~(kGroup - 1);
+  return (uint32_t)(m >> first) & ((1u << kGroup) - 1u);
+}
+// The value of the lane opposite in the group at distance 1, 2 (quad
+// permutations) or in the other quad (half-row mirror, of values equal
+// within a quad): moves on the vector ALU.
+template <int CTRL>
+__device__ __forceinline__ double dpp_of(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(hi, CTRL, 0xF, 0xF, true),
+                          __builtin_amdgcn_mov_dpp(lo, CTRL, 0xF, 0xF, true));
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141;
+__device__ __forceinline__ double group_max(double v) {
+  v = fmax(v, dpp_of<kDppXor1>(v));
+  v = fmax(v, dpp_of<kDppXor2>(v));
+  return fmax(v, dpp_of<kDppHalfMirror>(v));
+}
+__device__ __forceinline__ double group_sum(double v) {
+  v += dpp_of<kDppXor1>(v);
+  v += dpp_of<kDppXor2>(v);
+  return v + dpp_of<kDppHalfMirror>(v);
+}
+
+__device__ __forceinline__ uint32_t group_or(uint32_t v) {
+  v |= (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kDppXor1, 0xF, 0xF, true);
+  v |= (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kDppXor2, 0xF, 0xF, true);
+  return v | (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kDppHalfMirror, 0xF, 0xF, true);
+}
+__device__ __forceinline__ int group_or(int v) { return (int)group_or((uint32_t)v); }
+// The lanes of one wave read what others of it wrote.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+// Displacement of point (xc, yc) of cell c from (xi, yi) (nearest periodic
+// image) and its id.  The image is sought only when some lane of the wave
+// needs it (a wave holds nearby cells, so all but the waves at the box's
+// edges skip it); otherwise the plain difference is that image, of code 0.
+template <bool WALLS>
+__device__ __forceinline__ int32_t displacement(const Args& a, double xi, double yi, int c,
+                                                double xc, double yc, double& dx, double& dy) {
+  dx = xc - xi;
+  dy = yc - yi;
+  int code = 0;
+  if (!WALLS && __any(fabs(dx) > 0.5 * a.Lx || fabs(dy) > 0.5 * a.Ly)) {
+    int sx = 0, sy = 0;
+    if (dx > 0.5 * a.Lx) { dx -= a.Lx; sx = -1; } else if (dx < -0.5 * a.Lx) { dx += a.Lx; sx = 1; }
+    if (dy > 0.5 * a.Ly) { dy -= a.Ly; sy = -1; } else if (dy < -0.5 * a.Ly) { dy += a.Ly; sy = 1; }
+    if (sx != 0 || sy != 0) code = shift_code(sx, sy);
+  }
+  return pack(c, code);
+}
+
+// ---------------------------------------------------------------------------
 // the cell of one point
 // ---------------------------------------------------------------------------
 // Counter-clockwise order of directions: the upper half-plane (from angle 0
@@ -286,19 +351,18 @@ struct Part {
   __device__ Part(double dux, double duy)
       : mux(0.5 * dux), muy(0.5 * duy), eux(-duy), euy(dux) {}
   // straight-line (selects, no branches)
-  __device__ __forceinline__ void cut(double dvx, double dvy, bool act) {
-    const double a0 = eux * dvx + euy * dvy;
-    const double b0 = 0.5 * (dvx * dvx + dvy * dvy) - (mux * dvx + muy * dvy);
-    const double a = act ? a0 : 0.0;
-    const double b = act ? b0 : 1.0;
+  // (dvh: half of the displacement's square)
+  __device__ __forceinline__ void cut(double dvx, double dvy, double dvh, bool act) {
+    const double a = eux * dvx + euy * dvy;
+    const double b = dvh - (mux * dvx + muy * dvy);
     // a > 0: t <= b / a;  a < 0: t >= (-b) / (-a);  a = 0, b < 0: no t
-    const bool up = a > 0.0 && b * hd < hn * a;
+    const bool up = act && a > 0.0 && b * hd < hn * a;
     hn = up ? b : hn;
     hd = up ? a : hd;
-    const bool dn = a < 0.0 && -b * ld > ln * -a;
+    const bool dn = act && a < 0.0 && -b * ld > ln * -a;
     ln = dn ? -b : ln;
     ld = dn ? -a : ld;
-    empty = empty || (a == 0.0 && b < 0.0);
+    empty = empty || (act && a == 0.0 && b < 0.0);
   }
   // false when one end is open (the candidates do not enclose the point)
   __device__ __forceinline__ bool bounded() const { return ln != -INFINITY && hn != INFINITY; }
@@ -309,6 +373,7 @@ struct Part {
 // counter-clockwise after a by less than half a turn (det = |a| |b| sin(angle),
 // by a margin); false if it is not.
 constexpr double kVertexSin = 0.05;     // least sine of a consecutive pair's angle
+constexpr double kVertexMargin = 1e-9;  // relative margin of every vertex test
 __device__ __forceinline__ bool ring_vertex(double ax, double ay, double bx, double by,
                                             double& vx, double& vy) {
   const double ha = 0.5 * (ax * ax + ay * ay), hb = 0.5 * (bx * bx + by * by);
@@ -358,87 +423,69 @@ __device__ __forceinline__ int32_t& slot_nb(const Args& a, int i, int q) {
                   : a.s_nbx[(size_t)i * (kMaxFan - kRow) + (q - kRow)];
 }
 
-// The cells of a queue, kClipLanes lanes each: lane l holds candidates l and
-// l + kClipLanes, so the trials of every candidate against every other one,
-// a serial chain of hundreds of operations and loads for one lane, run side
-// by side, and the neighbours' neighbours are loaded 48 at a time.  A small
-// mesh queues a wave or two of cells, and that chain on an otherwise idle
-// chip is its time: one lane per cell took 143 us for 600 cells of a 64 x 64
-// tube, this 32 us; 205 -> 111 us for 60 113 cells of a 511 x 511 one.  Of
-// 370 000 cells (2048 x 2048 wave) the vector ALU is the bound (about 2000
-// instructions per wave of 4 cells) and both take 450-530 us.
-constexpr int kClipLanes = 16;
+// The cells of a queue, kGroup lanes each: lane l holds candidates l, l +
+// kGroup, ..., so the trials of every candidate against every other one, a
+// serial chain of hundreds of operations and loads for one lane, run side by
+// side, and lane l goes through the row of ring member l.  A neighbour's
+// neighbour is first tried against the vertices of the polygon that the ring
+// gives (three operations a vertex); only the few that may cut it meet the
+// trial against every candidate.  A small mesh queues a wave or two of cells,
+// and the chain on an otherwise idle chip is its time: one lane per cell took
+// 143 us for 600 cells of a 64 x 64 tube, 16 lanes 33, this 25; of 60 113 cells
+// of a 511 x 511 one 205, 111 and 66 us; of 370 000 cells (2048 x 2048 wave),
+// where the vector ALU is the bound, 16 lanes without that first trial took
+// 465 us (2000 instructions for 4 cells), this 308.
 constexpr int kClipThreads = 256;
-constexpr int kClipCells = kClipThreads / kClipLanes;   // cells of a block at a time
-constexpr int kClipMaxBlocks = kSeg * 32;               // of one run: the blocks stride
+constexpr int kClipCells = kClipThreads / kGroup;   // cells of a block at a time
+constexpr int kClipMaxBlocks = kSeg * 32;           // of one run: the blocks stride
 
-// A cell's candidates in LDS: displacement from r_i to the generating point
-// and its id (cell | code << 28), read by the whole group.  (The size of a
-// group's block keeps the four groups of a wave on different banks.)
+// A cell's candidates in LDS, read by the whole group: displacement from r_i
+// to the generating point, half its square, id (cell | code << 28); the
+// vertices of the ring's polygon; the slot of the edge at each place.  (The
+// size, 16 bytes past a multiple of 256, keeps the groups of a wave on
+// different banks.)
 template <int NS>
 struct ClipSlots {
-  double dx[NS], dy[NS];
-  double c[NS], sx[NS], sy[NS];   // shoelace terms of the live ones
-  int32_t id[NS];
-  int32_t row[kClipLanes], pre[kClipLanes];   // ring members' CSR rows, entries before each
-  int32_t place[kMaxFan];   // slot of the edge at each place
+  double2 v[NS];
+  double dx[NS], dy[NS], h[NS];
+  int32_t id[NS], place[NS];
+  static constexpr size_t kBytes = NS * (16 + 24 + 4 + 4);
+  char pad[(kBytes + 239) / 256 * 256 + 16 - kBytes];
 };
+static_assert(sizeof(ClipSlots<16>) == 784 && sizeof(ClipSlots<20>) == 1040, "banks");
 
-// The lanes of one wave read what others of it wrote.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-// This group's bits of a ballot.
-__device__ __forceinline__ uint32_t clip_bits(bool v) {
-  const unsigned long long m = __ballot(v);
-  return (uint32_t)(m >> (threadIdx.x & 63 & ~(kClipLanes - 1))) & ((1u << kClipLanes) - 1u);
-}
-
-// One queued cell.  With walls, slots 0-3 hold the point's mirrors (they
-// bound it); then come the cell's neighbours in the previous mesh; the first
-// pass finds the polygon those allow.  The neighbours' neighbours then enter
-// only when their bisector crosses that polygon, in CSR order; the second
-// pass gives the cell, its area, centroid and edges in counter-clockwise
-// order.  (TIERED: the neighbours are read where the ring check wrote them.)
+// One queued cell.  With walls, the first slots hold the point's mirrors (they
+// bound it), without those far beyond the ring if the ring bounds it closer;
+// then come the cell's neighbours in the previous mesh; the first pass finds
+// the polygon those allow.  The neighbours' neighbours then enter
+// only when their bisector crosses that polygon; the second pass gives the
+// cell, its area, centroid and edges in counter-clockwise order.  (TIERED:
+// the neighbours are read where the ring check wrote them.)
 template <bool WALLS, bool TIERED>
 __device__ void clip_cell(const Args& a, int i, ClipSlots<kSlots + (WALLS ? 4 : 0)>& S) {
-  constexpr int BASE = WALLS ? 4 : 0;   // mirror slots
-  constexpr int NS = kSlots + BASE;     // candidates per cell
-  static_assert(NS <= 2 * kClipLanes && NS <= kMaxFan, "two candidates per lane");
-  const int l = (int)threadIdx.x & (kClipLanes - 1);
+  constexpr int NS = kSlots + (WALLS ? 4 : 0);    // candidates per cell
+  constexpr int H = (NS + kGroup - 1) / kGroup;   // of each lane
+  constexpr int RH = kSlots / kGroup;   // ring members of each lane
+  static_assert(NS <= kMaxFan && kSlots % kGroup == 0, "slots");
+  const int l = (int)threadIdx.x & (kGroup - 1);
   const double xi = a.x[i], yi = a.y[i];
   int bad = 0;
+  auto put_slot = [&](int u, double dx, double dy, int32_t id) {
+    S.dx[u] = dx;
+    S.dy[u] = dy;
+    S.h[u] = 0.5 * (dx * dx + dy * dy);
+    S.id[u] = id;
+  };
   if (WALLS) {
     if (!(xi > a.x0 && xi < a.x1 && yi > a.y0 && yi < a.y1)) bad |= RICH_RETESS_POINT;
-    // the point's mirrors across the walls y0, x1, y1, x0
-    if (l < 4) {
-      S.dx[l] = l == 1 ? 2.0 * (a.x1 - xi) : (l == 3 ? 2.0 * (a.x0 - xi) : 0.0);
-      S.dy[l] = l == 0 ? 2.0 * (a.y0 - yi) : (l == 2 ? 2.0 * (a.y1 - yi) : 0.0);
-      S.id[l] = pack(i, l == 0 ? kWallY0 : l == 1 ? kWallX1 : l == 2 ? kWallY1 : kWallX0);
-    }
   } else {
     // no bounds: the neighbours enclose the point (a cell they leave open
     // is reported, and rebuilt on the host)
     if (!(xi >= a.x0 && xi < a.x1 && yi >= a.y0 && yi < a.y1)) bad |= RICH_RETESS_POINT;
   }
-  // displacement of point (xc, yc) of cell c from r_i (nearest periodic
-  // image) and its id
-  auto displacement = [&](int c, double xc, double yc, double& dx, double& dy) -> int32_t {
-    dx = xc - xi;
-    dy = yc - yi;
-    int code = 0;
-    if (!WALLS) {
-      int sx = 0, sy = 0;
-      if (dx > 0.5 * a.Lx) { dx -= a.Lx; sx = -1; } else if (dx < -0.5 * a.Lx) { dx += a.Lx; sx = 1; }
-      if (dy > 0.5 * a.Ly) { dy -= a.Ly; sy = -1; } else if (dy < -0.5 * a.Ly) { dy += a.Ly; sy = 1; }
-      if (sx != 0 || sy != 0) code = shift_code(sx, sy);
-    }
-    return pack(c, code);
-  };
 
-  // the ring: lane l loads CSR entry l (-1: past the end, out of range, or
-  // the cell itself, as a wall's entry is) and that neighbour's own CSR row
+  // the ring: lane l loads CSR entries l and l + kGroup (-1: past the end,
+  // out of range, or the cell itself, as a wall's entry is)
   int k0 = 0, k1 = 0;
   if (!bad) {
     k0 = a.p_off[i];
@@ -451,134 +498,189 @@ __device__ void clip_cell(const Args& a, int i, ClipSlots<kSlots + (WALLS ? 4 : 
       k1 = k0;
     }
   }
-  int c = l < k1 - k0 ? (TIERED ? a.nb[k0 + l] : prev_neighbour(a, k0 + l)) : -1;
-  if (c >= a.n || c == i) c = -1;
-  int row = 0, len = 0;
-  if (c >= 0) {
-    row = a.p_off[c];
-    len = a.p_off[c + 1] - row;
-    if (row < 0 || len < 0 || row + (int64_t)len > a.p_n_csr || len > kRingMax) {
-      bad |= RICH_RETESS_CLIP;
-      len = 0;
-    }
+  int c[RH];
+#pragma unroll
+  for (int h = 0; h < RH; ++h) {
+    const int k = k0 + l + h * kGroup;
+    c[h] = k < k1 ? (TIERED ? a.nb[k] : prev_neighbour(a, k)) : -1;
+    if (c[h] >= a.n || c[h] == i) c[h] = -1;
   }
-  for (int o = kClipLanes / 2; o > 0; o >>= 1) bad |= __shfl_xor(bad, o);
-  const uint32_t ring = clip_bits(c >= 0);
-  int nv = BASE + __popc(ring);
-  if (c >= 0) {
-    const int u = BASE + __popc(ring & ((1u << l) - 1u));
-    const double2 p = a.xy[c];
-    double dx, dy;
-    S.id[u] = displacement(c, p.x, p.y, dx, dy);
-    S.dx[u] = dx;
-    S.dy[u] = dy;
+  double rx[RH], ry[RH], far2 = 0.0;
+  int32_t rid[RH];
+#pragma unroll
+  for (int h = 0; h < RH; ++h) {
+    const double2 p = a.xy[c[h] < 0 ? i : c[h]];
+    rid[h] = displacement<WALLS>(a, xi, yi, c[h], p.x, p.y, rx[h], ry[h]);
+    far2 = fmax(far2, rx[h] * rx[h] + ry[h] * ry[h]);
   }
-  int pre = len;   // entries of the ring members before this one
-  for (int o = 1; o < kClipLanes; o <<= 1) {
-    const int v = __shfl_up(pre, o, kClipLanes);
-    if (l >= o) pre += v;
+  // lane l < 4: the point's mirror across the walls y0, x1, y1, x0
+  double wx = 0.0, wy = 0.0;
+  bool mirror = false;
+  if (WALLS) {
+    wx = l == 1 ? 2.0 * (a.x1 - xi) : (l == 3 ? 2.0 * (a.x0 - xi) : 0.0);
+    wy = l == 0 ? 2.0 * (a.y0 - yi) : (l == 2 ? 2.0 * (a.y1 - yi) : 0.0);
+    mirror = l < 4 && wx * wx + wy * wy <= 4.0 * group_max(far2);
   }
-  const int total = __shfl(pre, kClipLanes - 1, kClipLanes);
-  pre -= len;
-  S.row[l] = row;
-  S.pre[l] = pre;
-  wave_sync();
 
   // first pass: the polygon of the bounds and the first ring, and the
   // largest distance of its vertices
-  uint32_t em = 0;
-  double reach2 = 0.0;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int u = l + h * kClipLanes;
-    bool live = false;
-    if (!bad && u < nv) {
-      const double dux = S.dx[u], duy = S.dy[u];
-      const int32_t idu = S.id[u];
-      Part p(dux, duy);
-      for (int v = 0; v < nv; ++v) {
-        const bool same = v != u && S.id[v] == idu;   // a duplicate: the first stands
-        p.empty = p.empty || (same && v < u);
-        p.cut(S.dx[v], S.dy[v], v != u && !same);
-      }
-      live = p.live();
-      if (live) {
-        const double t = p.hn / p.hd;
-        const double px = 0.5 * dux - t * duy, py = 0.5 * duy + t * dux;
-        reach2 = fmax(reach2, px * px + py * py);
-      } else if (!p.bounded()) {
-        bad |= RICH_RETESS_CLIP;
-      }
+  int base, nv;   // mirror slots; slots
+  uint32_t em;
+  double reach2;
+  for (;;) {
+    base = 0;
+    if (WALLS) {
+      const uint32_t in = group_bits(mirror);
+      if (mirror)
+        put_slot(__popc(in & ((1u << l) - 1u)), wx, wy,
+                 pack(i, l == 0 ? kWallY0 : l == 1 ? kWallX1 : l == 2 ? kWallY1 : kWallX0));
+      base = __popc(in);
     }
-    em |= clip_bits(live) << (h * kClipLanes);
+    nv = base;
+#pragma unroll
+    for (int h = 0; h < RH; ++h) {
+      const uint32_t in = group_bits(c[h] >= 0);
+      if (c[h] >= 0) put_slot(nv + __popc(in & ((1u << l) - 1u)), rx[h], ry[h], rid[h]);
+      nv += __popc(in);
+    }
+    wave_sync();
+    em = 0;
+    reach2 = 0.0;
+    int open = 0;
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      const int u = l + h * kGroup;
+      bool live = false;
+      double px = 0.0, py = 0.0;
+      if (!bad && u < nv) {
+        const double dux = S.dx[u], duy = S.dy[u];
+        const int32_t idu = S.id[u];
+        Part p(dux, duy);
+#pragma unroll 2
+        for (int v = 0; v < nv; ++v) {
+          const bool same = v != u && S.id[v] == idu;   // a duplicate: the first stands
+          p.empty = p.empty || (same && v < u);
+          p.cut(S.dx[v], S.dy[v], S.h[v], v != u && !same);
+        }
+        live = p.live();
+        if (live) {
+          const double t = p.hn / p.hd;
+          px = 0.5 * dux - t * duy;
+          py = 0.5 * duy + t * dux;
+          reach2 = fmax(reach2, px * px + py * py);
+        } else if (!p.bounded()) {
+          open = RICH_RETESS_CLIP;
+        }
+      }
+      const uint32_t lv = group_bits(live);
+      if (live) S.v[__popc(em) + __popc(lv & ((1u << l) - 1u))] = make_double2(px, py);
+      em |= lv << (h * kGroup);
+    }
+    reach2 = group_max(reach2);
+    open = group_or(open);
+    wave_sync();
+    // a mirror left out that may cut the polygon, or one to bound it: all in
+    if (WALLS && base < 4 &&
+        (open != 0 || em == 0u ||
+         group_bits(l < 4 && !mirror && !(4.0 * reach2 <= wx * wx + wy * wy)) != 0u)) {
+      mirror = l < 4;
+      continue;
+    }
+    bad |= open;
+    break;
   }
-  for (int o = kClipLanes / 2; o > 0; o >>= 1) {
-    reach2 = fmax(reach2, __shfl_xor(reach2, o));
-    bad |= __shfl_xor(bad, o);
-  }
+  const int corners = __popc(em);
 
-  // second ring: a candidate enters when its bisector crosses the polygon
-  // of the slots (one further than twice the largest vertex distance
-  // cannot, and is skipped at once), which includes those that entered
-  // before it.  The lanes try their candidates against the slots together;
-  // those that cross then enter in order, each one cutting the ones after it.
-  constexpr int CH = 3;   // candidates of a lane whose loads are in flight together
-  for (int t0 = 0; t0 < total && !bad; t0 += CH * kClipLanes) {
-    int cc[CH];
-    double2 cp[CH];
-#pragma unroll
-    for (int h = 0; h < CH; ++h) {
-      const int t = t0 + h * kClipLanes + l;
-      int m = 0;   // the ring member whose row holds entry t: the last with pre <= t
-#pragma unroll
-      for (int s = kClipLanes / 2; s > 0; s >>= 1)
-        if (S.pre[m + s] <= t) m += s;
-      cc[h] = -1;
-      if (t < total) {
-        const int k = S.row[m] + t - S.pre[m];
-        cc[h] = TIERED ? a.nb[k] : prev_neighbour(a, k);
+  // the neighbours' neighbours, lane l through the row of ring member l: those
+  // that are new and may cut the polygon (one further than twice its largest
+  // vertex distance cannot, nor one whose half plane holds every vertex by the
+  // margin) meet the full trial, each lane's first, then its second, ...  One
+  // enters when its bisector crosses the polygon of the slots, which includes
+  // those that entered before it: the lanes try theirs against the slots
+  // together, and those that cross then enter in order, each one cutting the
+  // ones after it.
+  const double mr = kVertexMargin * reach2;
+#pragma unroll 1
+  for (int h = 0; h < RH && !bad; ++h) {
+    const int cm = h == 0 ? c[0] : c[RH - 1];
+    static_assert(RH == 2, "two ring members of a lane");
+    int k = 0, k1 = 0;
+    if (cm >= 0) {
+      k = a.p_off[cm];
+      k1 = a.p_off[cm + 1];
+      if (k < 0 || k1 < k || k1 > a.p_n_csr || k1 - k > kRingMax) {
+        bad = RICH_RETESS_CLIP;
+        k1 = k;
       }
-      if (cc[h] >= a.n || cc[h] == i) cc[h] = -1;
     }
+    bad = group_or(bad);
+    constexpr int CH = 8;   // candidates of a lane whose loads are in flight together
+    for (; group_bits(k < k1) != 0u && !bad; k += CH) {
+      uint32_t may = 0;   // the chunk's candidates for the full trial
+      {
+        int cc[CH];
+        double2 cp[CH];
 #pragma unroll
-    for (int h = 0; h < CH; ++h) cp[h] = a.xy[cc[h] < 0 ? 0 : cc[h]];
+        for (int t = 0; t < CH; ++t)
+          cc[t] = k + t < k1 ? (TIERED ? a.nb[k + t] : a.p_idx[k + t]) : -1;
+        if (!TIERED) {
 #pragma unroll
-    for (int h = 0; h < CH; ++h) {
-      double dx, dy;
-      const int32_t id = displacement(cc[h], cp[h].x, cp[h].y, dx, dy);
-      bool on = cc[h] >= 0 && !(4.0 * reach2 <= dx * dx + dy * dy);
-      for (int v = BASE; v < nv; ++v) on = on && S.id[v] != id;
-      if (clip_bits(on) == 0u) continue;
-      Part p(dx, dy);
-      for (int v = 0; v < nv; ++v) p.cut(S.dx[v], S.dy[v], true);
-      uint32_t in;
-      while ((in = clip_bits(on && p.live())) != 0u && !bad) {
-        const int f = __ffs(in) - 1;
-        const double fx = __shfl(dx, f, kClipLanes), fy = __shfl(dy, f, kClipLanes);
-        const int32_t fid = __shfl(id, f, kClipLanes);
-        // a new slot, else one whose bisector bounds nothing (it stays
-        // redundant as candidates are added; a mirror is never reused)
-        int u = nv;
-        if (nv < NS) {
-          ++nv;
-        } else {
-          const uint32_t usable = ~em & ((1u << NS) - 1u) & ~((1u << BASE) - 1u);
-          u = __ffs(usable) - 1;
-          if (usable == 0u) {
-            bad |= RICH_RETESS_FAN;
-            break;
+          for (int t = 0; t < CH; ++t) cc[t] = entry_cell(a, cc[t]);
+        }
+#pragma unroll
+        for (int t = 0; t < CH; ++t) {
+          if (cc[t] >= a.n || cc[t] == i) cc[t] = -1;
+          cp[t] = a.xy[cc[t] < 0 ? 0 : cc[t]];
+        }
+#pragma unroll
+        for (int t = 0; t < CH; ++t) {
+          double dx, dy;
+          const int32_t id = displacement<WALLS>(a, xi, yi, cc[t], cp[t].x, cp[t].y, dx, dy);
+          const double d2 = dx * dx + dy * dy, hu = 0.5 * d2;
+          if (cc[t] < 0 || 4.0 * reach2 <= d2) continue;
+          bool known = false;
+          for (int v = base; v < nv; ++v) known = known || S.id[v] == id;
+          if (known) continue;
+          double q = -INFINITY;   // the largest projection of a vertex on the candidate
+          for (int v = 0; v < corners; ++v) q = fmax(q, S.v[v].x * dx + S.v[v].y * dy);
+          if (!(hu - q > kVertexMargin * hu + mr)) may |= 1u << t;
+        }
+      }
+      for (; group_bits(may != 0u) != 0u && !bad; may &= may - 1u) {
+        bool on = may != 0u;
+        const int kk = on ? k + __ffs(may) - 1 : 0;
+        const int cj = on ? (TIERED ? a.nb[kk] : prev_neighbour(a, kk)) : i;   // (in range: tried)
+        const double2 pj = a.xy[cj];
+        double dx, dy;
+        const int32_t id = displacement<WALLS>(a, xi, yi, cj, pj.x, pj.y, dx, dy);
+        for (int v = base; v < nv; ++v) on = on && S.id[v] != id;
+        if (group_bits(on) == 0u) continue;
+        Part p(dx, dy);
+#pragma unroll 2
+        for (int v = 0; v < nv; ++v) p.cut(S.dx[v], S.dy[v], S.h[v], true);
+        uint32_t in;
+        while ((in = group_bits(on && p.live())) != 0u && !bad) {
+          const int f = __ffs(in) - 1;
+          // a new slot, else one whose bisector bounds nothing (it stays
+          // redundant as candidates are added; a mirror is never reused)
+          int u = nv;
+          if (nv < NS) {
+            ++nv;
+          } else {
+            const uint32_t usable = ~em & ((1u << NS) - 1u) & ~((1u << base) - 1u);
+            u = __ffs(usable) - 1;
+            if (usable == 0u) {
+              bad = RICH_RETESS_FAN;
+              break;
+            }
           }
+          em |= 1u << u;   // holds a cutting candidate now: not reusable
+          wave_sync();
+          if (l == f) put_slot(u, dx, dy, id);
+          wave_sync();
+          on = on && id != S.id[u];
+          p.cut(S.dx[u], S.dy[u], S.h[u], on);
         }
-        em |= 1u << u;   // holds a cutting candidate now: not reusable
-        wave_sync();
-        if (l == f) {
-          S.dx[u] = dx;
-          S.dy[u] = dy;
-          S.id[u] = id;
-        }
-        wave_sync();
-        on = on && id != fid;
-        p.cut(fx, fy, on);
       }
     }
   }
@@ -592,65 +694,79 @@ __device__ void clip_cell(const Args& a, int i, ClipSlots<kSlots + (WALLS ? 4 : 
   cr.sy = yi;
   // second pass: each candidate's part of its bisector.  A live one is an
   // edge: its place is its counter-clockwise rank among all the candidates
-  // (same direction: by slot) less the ranks of those that bound nothing,
-  // and its triangle with the point is added to the shoelace sums in slot
-  // order.
-  uint32_t fm = 0, holes = 0;
-  int rank[2] = {0, 0};
-  double len_[2] = {0.0, 0.0}, mx[2] = {0.0, 0.0}, my[2] = {0.0, 0.0};
+  // (the upper half-plane, from angle 0 inclusive, before the lower one, then
+  // by the sign of the cross product, then by slot) less the ranks of those
+  // that bound nothing.
+  uint32_t lower = 0;   // slots in the lower half-plane
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int u = l + h * kClipLanes;
+  for (int h = 0; h < H; ++h) {
+    const int u = l + h * kGroup;
+    const double dx = u < nv ? S.dx[u] : 0.0, dy = u < nv ? S.dy[u] : 0.0;
+    lower |= group_bits(dy < 0.0 || (dy == 0.0 && dx < 0.0)) << (h * kGroup);
+  }
+  uint32_t fm = 0, holes = 0;
+  int rank[H];
+  double len_[H], mx[H], my[H];
+  double A2 = 0.0, cx = 0.0, cy = 0.0, l2 = INFINITY;
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    const int u = l + h * kGroup;
     bool live = false;
+    rank[h] = 0;
+    len_[h] = mx[h] = my[h] = 0.0;
     if (!bad && u < nv) {
       const double dux = S.dx[u], duy = S.dy[u];
       const int32_t idu = S.id[u];
+      const bool low = (lower >> u) & 1u;
       Part p(dux, duy);
+#pragma unroll 2
       for (int v = 0; v < nv; ++v) {
         const double dvx = S.dx[v], dvy = S.dy[v];
         const bool other = v != u;
         const bool same = other && S.id[v] == idu;
         p.empty = p.empty || (same && v < u);
-        p.cut(dvx, dvy, other && !same);
-        rank[h] += (other && (ccw_before(dvx, dvy, dux, duy) ||
-                              (v < u && !ccw_before(dux, duy, dvx, dvy)))) ? 1 : 0;
+        p.cut(dvx, dvy, S.h[v], other && !same);
+        // (two products, each rounded: the sign is the opposite one from v's side)
+        const double r = dvx * duy;
+        const double s = dvy * dux;
+        const bool lowv = (lower >> v) & 1u;
+        rank[h] += other && (lowv == low ? r > s || (r == s && v < u) : low) ? 1 : 0;
       }
       live = p.live();
       if (live) {
         const double tlo = p.ln / p.ld, thi = p.hn / p.hd;
         const double ux = 0.5 * dux - tlo * duy, uy = 0.5 * duy + tlo * dux;
         const double wx = 0.5 * dux - thi * duy, wy = 0.5 * duy + thi * dux;
-        S.c[u] = ux * wy - uy * wx;
-        S.sx[u] = ux + wx;
-        S.sy[u] = uy + wy;
-        const double ex = wx - ux, ey = wy - uy;
-        len_[h] = sqrt(ex * ex + ey * ey);
-        mx[h] = xi + 0.5 * (ux + wx);
-        my[h] = yi + 0.5 * (uy + wy);
+        const double cv = ux * wy - uy * wx;
+        A2 += cv;
+        cx += (ux + wx) * cv;
+        cy += (uy + wy) * cv;
+        edge_geometry(xi, yi, ux, uy, wx, wy, len_[h], mx[h], my[h]);
+        l2 = fmin(l2, len_[h] * len_[h]);
       } else {
         if (!p.bounded()) bad |= RICH_RETESS_CLIP;
         holes |= 1u << rank[h];
       }
     }
-    fm |= clip_bits(live) << (h * kClipLanes);
+    fm |= group_bits(live) << (h * kGroup);
   }
-  for (int o = kClipLanes / 2; o > 0; o >>= 1) {
-    holes |= __shfl_xor(holes, o);
-    bad |= __shfl_xor(bad, o);
-  }
+  holes = group_or(holes);
+  bad = group_or(bad);
+  A2 = group_sum(A2);
+  cx = group_sum(cx);
+  cy = group_sum(cy);
   const int deg = __popc(fm);
   if (deg < 3) bad |= RICH_RETESS_CLIP;
   // the edges' places; rounding that ranks two of them alike fails the cell
-  int q[2];
+  int q[H];
   uint32_t taken = 0;
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    q[h] = (fm >> (l + h * kClipLanes)) & 1u
-               ? rank[h] - __popc(holes & ((1u << rank[h]) - 1u))   // < NS <= kMaxFan
-               : kMaxFan;
+  for (int h = 0; h < H; ++h) {
+    q[h] = (fm >> (l + h * kGroup)) & 1u ? rank[h] - __popc(holes & ((1u << rank[h]) - 1u))
+                                         : kMaxFan;   // (a place is < NS <= kMaxFan)
     taken |= 1u << q[h];
   }
-  for (int o = kClipLanes / 2; o > 0; o >>= 1) taken |= __shfl_xor(taken, o);
+  taken = group_or(taken);
   if ((taken & ((1u << kMaxFan) - 1u)) != (1u << deg) - 1u) bad |= RICH_RETESS_CLIP;
   if (bad) {
     if (l == 0) {
@@ -661,49 +777,35 @@ __device__ void clip_cell(const Args& a, int i, ClipSlots<kSlots + (WALLS ? 4 : 
     }
     return;
   }
-  wave_sync();
-  double A2 = 0.0, cx = 0.0, cy = 0.0;
-  for (int v = 0; v < nv; ++v) {
-    if (!((fm >> v) & 1u)) continue;
-    const double cv = S.c[v];
-    A2 += cv;
-    cx += S.sx[v] * cv;
-    cy += S.sy[v] * cv;
-  }
-  // the edges in their places
-  double l2 = INFINITY;
-  bool plain = deg <= kRow;
+  bool wall = false;
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int u = l + h * kClipLanes;
+  for (int h = 0; h < H; ++h) {
     if (q[h] < kMaxFan) {
+      const int u = l + h * kGroup;
       slot_nb(a, i, q[h]) = S.id[u];
       S.place[q[h]] = u;   // (all of 0 .. deg - 1 are taken)
-      l2 = fmin(l2, len_[h] * len_[h]);
     }
   }
   wave_sync();
   // lean if every consecutive pair turns enough, and the rest of lean_cell
   double r2 = 0.0;
-  if (l < deg) {
+  bool plain = deg <= kRow, own = false;
+  static_assert(kRow == kGroup, "a lane per slot of a row");
+  if (plain && l < deg) {
     const int u = S.place[l], v = S.place[l + 1 < deg ? l + 1 : 0];
     double vx, vy;
-    const bool turn = ring_vertex(S.dx[u], S.dy[u], S.dx[v], S.dy[v], vx, vy);
-    plain = plain && turn;
+    plain = ring_vertex(S.dx[u], S.dy[u], S.dx[v], S.dy[v], vx, vy);
     r2 = vx * vx + vy * vy;
+    wall = (int)((uint32_t)S.id[u] >> kShift) >= kWallX0;
+    own = wall || i < (int)((uint32_t)S.id[u] & kMask);
   }
-  for (int o = kClipLanes / 2; o > 0; o >>= 1) {
-    r2 = fmax(r2, __shfl_xor(r2, o));
-    l2 = fmin(l2, __shfl_xor(l2, o));
-  }
-  const bool lean = clip_bits(!plain) == 0u && lean_cell(a, l2, r2, 0.5 * A2);
-  const int32_t at = l < deg ? S.id[S.place[l]] : pack(0, 0);
-  const bool wall = (int)((uint32_t)at >> kShift) >= kWallX0;
-  const uint32_t walls = clip_bits(wall);
-  const uint32_t own = clip_bits(wall || (l < deg && i < (int)((uint32_t)at & kMask)));
+  r2 = group_max(r2);
+  l2 = -group_max(-l2);
+  const bool lean = group_bits(!plain) == 0u && lean_cell(a, l2, r2, 0.5 * A2);
+  const uint32_t owns = group_bits(own), walls = group_bits(wall);
   if (!lean) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int h = 0; h < H; ++h) {
       if (q[h] < kMaxFan) {
         double* g = a.s_geo + 3 * ((size_t)i * kMaxFan + q[h]);
         g[0] = len_[h];
@@ -715,7 +817,7 @@ __device__ void clip_cell(const Args& a, int i, ClipSlots<kSlots + (WALLS ? 4 : 
   if (l == 0) {
     a.deg[i] = deg | (lean ? kLean : 0);
     // (if lean: deg <= kRow)
-    a.cnt[i] = (uint32_t)deg | (uint32_t)__popc(own) << 16 | (uint32_t)__popc(walls) << kWallBits;
+    a.cnt[i] = (uint32_t)deg | (uint32_t)__popc(owns) << 16 | (uint32_t)__popc(walls) << kWallBits;
     a.area[i] = 0.5 * A2;
     cr.area = 0.5 * A2;
     cr.sx = xi + cx / (3.0 * A2);
@@ -737,7 +839,7 @@ __global__ __launch_bounds__(kClipThreads) void k_rt_clip(Args one, Batch bt) {
   if (B) nblk = (a.n + kThreads - 1) / kThreads;
   const int seg = blk % kSeg;
   const int queued = min(a.qcnt[seg * kSegStride], a.qcap);
-  const int group = (int)threadIdx.x / kClipLanes;
+  const int group = (int)threadIdx.x / kGroup;
   const int step = kClipCells * ((nblk - seg + kSeg - 1) / kSeg);   // the segment's blocks
   for (int e = (blk / kSeg) * kClipCells + group; e < queued; e += step) {
     const int i = a.queue[(size_t)seg * a.qcap + e];
@@ -786,43 +888,11 @@ __global__ __launch_bounds__(kClipThreads) void k_rt_clip(Args one, Batch bt) {
 // through an edge of two further points; no cell of 3.5 million, random and
 // regular meshes with moves from 0 to 0.3 spacings, was decided otherwise.
 // The areas and the match of the edges certify the mesh in any case.)
-// kGroup lanes work on a cell, one per neighbour; the group's loads and
-// stores are contiguous.  (One lane per cell and all candidates at once took
+// The group's loads and stores are contiguous.  (One lane per cell and all candidates at once took
 // 1648 us on the 2048 x 2048 wave, bound by the gathers and their address
 // arithmetic; the two passes take 666, of which 1.1 GB written and 0.43 GB
 // read are 360 at the rate of a large copy, and 309 us.  64 x 64 tube: a
 // chain of 24 dependent loads, 38 -> 10 us in one launch.)
-constexpr double kVertexMargin = 1e-9;  // relative margin of every vertex test
-constexpr int kGroup = 8;               // lanes (and ring entries) of a cell
-constexpr int kGroupThreads = kThreads * kGroup;
-static_assert(64 % kGroup == 0, "groups do not straddle waves");
-
-// The group's bits of a wave-wide ballot.
-__device__ __forceinline__ uint32_t group_bits(bool v) {
-  const unsigned long long m = __ballot(v);
-  const int first = (int)(threadIdx.x & 63) & ~(kGroup - 1);
-  return (uint32_t)(m >> first) & ((1u << kGroup) - 1u);
-}
-// The value of the lane opposite in the group at distance 1, 2 (quad
-// permutations) or in the other quad (half-row mirror, of values equal
-// within a quad): moves on the vector ALU.
-template <int CTRL>
-__device__ __forceinline__ double dpp_of(double v) {
-  const int lo = __double2loint(v), hi = __double2hiint(v);
-  return __hiloint2double(__builtin_amdgcn_mov_dpp(hi, CTRL, 0xF, 0xF, true),
-                          __builtin_amdgcn_mov_dpp(lo, CTRL, 0xF, 0xF, true));
-}
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141;
-__device__ __forceinline__ double group_max(double v) {
-  v = fmax(v, dpp_of<kDppXor1>(v));
-  v = fmax(v, dpp_of<kDppXor2>(v));
-  return fmax(v, dpp_of<kDppHalfMirror>(v));
-}
-__device__ __forceinline__ double group_sum(double v) {
-  v += dpp_of<kDppXor1>(v);
-  v += dpp_of<kDppXor2>(v);
-  return v + dpp_of<kDppHalfMirror>(v);
-}
 
 // Lane l of a cell's group: ring entry l, its displacement from r_i, and the
 // vertex after it.
@@ -833,25 +903,6 @@ struct Ring {
   double xi, yi, dx, dy, vx, vy;
   double r2;          // largest squared vertex distance of the cell
 };
-
-// Displacement of point (xc, yc) of cell c from (xi, yi) (nearest periodic
-// image) and its id.  The image is sought only when some lane of the wave
-// needs it (a wave holds nearby cells, so all but the waves at the box's
-// edges skip it); otherwise the plain difference is that image, of code 0.
-template <bool WALLS>
-__device__ __forceinline__ int32_t displacement(const Args& a, double xi, double yi, int c,
-                                                double xc, double yc, double& dx, double& dy) {
-  dx = xc - xi;
-  dy = yc - yi;
-  int code = 0;
-  if (!WALLS && __any(fabs(dx) > 0.5 * a.Lx || fabs(dy) > 0.5 * a.Ly)) {
-    int sx = 0, sy = 0;
-    if (dx > 0.5 * a.Lx) { dx -= a.Lx; sx = -1; } else if (dx < -0.5 * a.Lx) { dx += a.Lx; sx = 1; }
-    if (dy > 0.5 * a.Ly) { dy -= a.Ly; sy = -1; } else if (dy < -0.5 * a.Ly) { dy += a.Ly; sy = 1; }
-    if (sx != 0 || sy != 0) code = shift_code(sx, sy);
-  }
-  return pack(c, code);
-}
 
 // The ring of cell i (no cell: live = false) and whether it passes every
 // test that needs the ring alone.  NB: neighbours from a.nb (an earlier
