@@ -1401,15 +1401,31 @@ __device__ __forceinline__ int edge_offset(const Args& a, int c) {
   return (int)a.bsum[a.n_scan_blocks + c / kScanThreads] + (int)(a.cnt[c] >> 16);
 }
 
-// Slot of cell j (of n edges) that names `want`, or -1: its row in two
-// 16-byte loads (what lies past its edges is ignored), the rest one at a time.
-__device__ __forceinline__ int find_slot(const Args& a, int j, int n, int32_t want) {
+// What an edge's owner needs of the neighbour, loaded together: its degree
+// word, its row and its first CSR entry.
+struct Other {
+  int d;
+  int32_t id[kRow];
+  int k;
+};
+__device__ __forceinline__ Other load_other(const Args& a, int j) {
+  Other o;
+  o.d = max(a.deg[j], 0);
   const int4* row = reinterpret_cast<const int4*>(a.s_nb + (size_t)j * kRow);
   const int4 v0 = row[0], v1 = row[1];
-  const int32_t ids[kRow] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+  const int32_t id[kRow] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+#pragma unroll
+  for (int t = 0; t < kRow; ++t) o.id[t] = id[t];
+  o.k = csr_offset(a, j);
+  return o;
+}
+// Its slot that names `want`, or -1 (what its row holds past its edges is
+// ignored).
+__device__ __forceinline__ int find_slot(const Args& a, int j, const Other& o, int32_t want) {
+  const int n = o.d & (kLean - 1);
   int found = -1;
 #pragma unroll
-  for (int t = kRow - 1; t >= 0; --t) found = t < n && ids[t] == want ? t : found;
+  for (int t = kRow - 1; t >= 0; --t) found = t < n && o.id[t] == want ? t : found;
   for (int t = kRow; found < 0 && t < n; ++t)
     if (slot_nb(a, j, t) == want) found = t;
   return found;
@@ -1433,7 +1449,7 @@ __device__ __forceinline__ int find_slot(const Args& a, int j, int n, int32_t wa
 // A lane per slot; the geometry of lean cells' edges is computed from the
 // points here.  (One kernel compared the stored geometry of every pair and
 // another read it again for the records: 550 + 415 us on the 2048 x 2048
-// wave, this 470.)
+// wave, this 372, with its loads in two dependent levels.)
 template <bool B>
 __global__ __launch_bounds__(kGroupThreads) void k_rt_emit(Args one, Batch bt) {
   int blk;
@@ -1441,10 +1457,14 @@ __global__ __launch_bounds__(kGroupThreads) void k_rt_emit(Args one, Batch bt) {
   const int l = (int)threadIdx.x % kGroup;
   const int i = blk * kThreads + (int)threadIdx.x / kGroup;
   if (i >= a.n) return;  // whole groups
-  const bool failed = a.hdr->flags != 0;   // (offsets may be past the buffers)
+  // the cell's own loads go out together (a row holds kRow slots, read or not)
+  const int di = max(a.deg[i], 0);
+  static_assert(kGroup == kRow, "a lane per slot of a row");
+  const int32_t id0 = a.s_nb[(size_t)i * kRow + l];
+  const double2 pi = a.xy[i];
   const int k = csr_offset(a, i);
   int e = edge_offset(a, i);
-  const int di = max(a.deg[i], 0);
+  const bool failed = a.hdr->flags != 0;   // (offsets may be past the buffers)
   const int d = di & (kLean - 1);
   if (l == 0) {
     a.off[i] = k;
@@ -1457,26 +1477,31 @@ __global__ __launch_bounds__(kGroupThreads) void k_rt_emit(Args one, Batch bt) {
   // slot q's match in the neighbour and, if it has one, edge ee: the record
   // and both cells' CSR entries
   bool bad = false, later = false;
-  auto put = [&](int q, int rank, int ee, int32_t id, int32_t prev, int32_t next, double len,
-                 double mx, double my) {
+  auto put = [&](int q, int rank, int ee, int32_t id, const Other& o, int32_t prev, int32_t next,
+                 double len, double mx, double my) {
     const int code = (int)((uint32_t)id >> kShift);
     const int j = (int)((uint32_t)id & kMask);
     int entry = -1;   // of the neighbour
     if (code < kWallX0) {
-      const int dj = max(a.deg[j], 0);
-      const int nj = dj & (kLean - 1);
-      const int t = find_slot(a, j, nj, pack(i, back_code(code)));
+      const int t = find_slot(a, j, o, pack(i, back_code(code)));
       if (t < 0) {
         bad = true;
         return;
       }
       int place = t;
       later = true;
-      if (dj & kLean) {
-        const int32_t* row = a.s_nb + (size_t)j * kRow;   // (just loaded: cached)
-        if (di & kLean)
-          later = !(same_point(id, row[t > 0 ? t - 1 : nj - 1], next) &&
-                    same_point(id, row[t + 1 < nj ? t + 1 : 0], prev));
+      if (o.d & kLean) {
+        if (di & kLean) {
+          const int nj = o.d & (kLean - 1);
+          const int tb = t > 0 ? t - 1 : nj - 1, ta = t + 1 < nj ? t + 1 : 0;
+          int32_t before = o.id[0], after = o.id[0];
+#pragma unroll
+          for (int m = 1; m < kRow; ++m) {
+            before = m == tb ? o.id[m] : before;
+            after = m == ta ? o.id[m] : after;
+          }
+          later = !(same_point(id, before, next) && same_point(id, after, prev));
+        }
       } else {
         const uint8_t f = a.s_flag[(size_t)j * kMaxFan + t];
         if (!(f & 1)) {   // the neighbour drops it
@@ -1485,7 +1510,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_rt_emit(Args one, Batch bt) {
         }
         place = f >> 2;
       }
-      entry = csr_offset(a, j) + place;
+      entry = o.k + place;
     }
     if (failed) return;
     rich_edge r;
@@ -1501,24 +1526,25 @@ __global__ __launch_bounds__(kGroupThreads) void k_rt_emit(Args one, Batch bt) {
   const uint32_t below = (1u << l) - 1u;
   uint32_t chk = 0;
   if (di & kLean) {   // every slot kept; no image of the cell itself
-    static_assert(kGroup == kRow, "a lane per slot of a row");
-    const int32_t id = l < d ? a.s_nb[(size_t)i * kRow + l] : 0;
+    const int32_t id = l < d ? id0 : 0;
     const int j = (int)((uint32_t)id & kMask);
-    const double2 pi = a.xy[i];
+    const bool own = l < d && (i < j || (int)((uint32_t)id >> kShift) >= kWallX0);
+    const double2 pj = a.xy[j];
+    Other o;
+    if (own) o = load_other(a, j);
     double dx, dy;
-    slot_displacement(a, pi.x, pi.y, id, a.xy[j], dx, dy);
+    slot_displacement(a, pi.x, pi.y, id, pj, dx, dy);
     const int ln = l + 1 < d ? l + 1 : 0, lp = l > 0 ? l - 1 : d - 1;
     const int32_t next = __shfl(id, ln, kGroup), prev = __shfl(id, lp, kGroup);
     const double bx = __shfl(dx, ln, kGroup), by = __shfl(dy, ln, kGroup);
     double wx, wy;
     ring_vertex(dx, dy, bx, by, wx, wy);
     const double ux = __shfl(wx, lp, kGroup), uy = __shfl(wy, lp, kGroup);
-    const bool own = l < d && (i < j || (int)((uint32_t)id >> kShift) >= kWallX0);
     const uint32_t mo = group_bits(own);
     if (own) {
       double len, mx, my;
       edge_geometry(pi.x, pi.y, ux, uy, wx, wy, len, mx, my);
-      put(l, l, e + __popc(mo & below), id, prev, next, len, mx, my);
+      put(l, l, e + __popc(mo & below), id, o, prev, next, len, mx, my);
     }
     chk = group_bits(later);
   } else {
@@ -1531,7 +1557,9 @@ __global__ __launch_bounds__(kGroupThreads) void k_rt_emit(Args one, Batch bt) {
       later = false;
       if (own) {
         const double* g = a.s_geo + 3 * (s0 + q);
-        put(q, f >> 2, e + __popc(mo & below), slot_nb(a, i, q), 0, 0, g[0], g[1], g[2]);
+        const int32_t id = slot_nb(a, i, q);
+        const Other o = load_other(a, (int)((uint32_t)id & kMask));
+        put(q, f >> 2, e + __popc(mo & below), id, o, 0, 0, g[0], g[1], g[2]);
       }
       chk |= group_bits(later) << base;
       e += __popc(mo);
@@ -1565,7 +1593,7 @@ __global__ __launch_bounds__(kScanThreads) void k_rt_end(Args one, Batch bt) {
     const int32_t id = slot_nb(a, i, q);
     const int j = (int)((uint32_t)id & kMask), code = (int)((uint32_t)id >> kShift);
     const int di = a.deg[i], dj = a.deg[j];
-    const int t = find_slot(a, j, dj & (kLean - 1), pack(i, back_code(code)));   // (emit found it)
+    const int t = find_slot(a, j, load_other(a, j), pack(i, back_code(code)));   // (emit found it)
     if (t < 0) {
       s_bad = 1;
       continue;
