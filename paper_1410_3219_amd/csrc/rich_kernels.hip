@@ -64,7 +64,18 @@ namespace rich {
 #ifndef RICH_FLUX_TILE
 #define RICH_FLUX_TILE 256
 #endif
-constexpr int kTile = RICH_FLUX_TILE;          // k_flux: default cells per tile = threads per block
+constexpr int kTile = RICH_FLUX_TILE;          // k_flux: cells per tile = threads per block
+// Small launches take tiles of kSmallTile cells and four threads per cell:
+// every edge of a tile has a thread of its own (about 190 owned edges and 40
+// of its border for 256 threads), where a thread of the large tile computes
+// about four one after another, a chain that is the pass's whole time while
+// the chip is not full.  The border's share of the edges is larger, so from
+// kSmallCells cells the large tile is the faster one.  Stage of a tube with
+// the small and with the large tile: 17.6 and 24.2 us for 4096 cells, 25.8
+// and 28.4 for 65 536, 43.5 and 41.1 for 131 044; with the exact solver 31
+// and 60, 58 and 62, 97 and 86 us.
+constexpr int kSmallTile = 64;
+constexpr int64_t kSmallCells = 81920;
 constexpr int kCellThreads = 256;   // k_cell: threads per block
 constexpr int kLpc = RICH_LPC;      // k_cell: lanes per cell
 constexpr int kNumXcd = 8;
@@ -597,14 +608,16 @@ __global__ __launch_bounds__(256) void k_edge_bits(RunDesc d, uint8_t* bits) {
   bits[e] = b;
 }
 
-template <int RIEMANN, bool BATCH, int TILE = kTile>
-__global__ __launch_bounds__(TILE, RIEMANN == 0 ? RICH_FLUX_WAVES : 1) void k_flux(RunDesc one, const RunDesc* __restrict__ descs,
-                                                const int2* __restrict__ tile_run,
-                                                int n_tiles) {
+template <int RIEMANN, bool BATCH, int TILE = kTile, int THREADS = TILE>
+__global__ __launch_bounds__(THREADS, RIEMANN == 0 ? RICH_FLUX_WAVES : 1) void k_flux(
+    RunDesc one, const RunDesc* __restrict__ descs, const int2* __restrict__ tile_run,
+    int n_tiles) {
+  static_assert(THREADS >= TILE, "a thread per cell sums its fluxes");
   // LDS capacities in proportion to the tile: fluxes of the owned edges
   // (about 3 per cell), of other edges the tile's cells need (its border),
   // and the classification of the tile's CSR entries (about 6 per cell)
-  constexpr int kEdgeCap = TILE * 25 / 8, kForCap = TILE * 3 / 4, kMapCap = TILE * 9;
+  constexpr int kEdgeCap = TILE * 25 / 8, kMapCap = TILE * 9;
+  constexpr int kForCap = TILE == kSmallTile ? TILE * 3 / 2 : TILE * 3 / 4;
   __shared__ double sF[4][kEdgeCap + kForCap];
   __shared__ int s_forE[kForCap];
   __shared__ short s_map[kMapCap];  // (flux slot << 1) | side, or -1
@@ -624,20 +637,20 @@ __global__ __launch_bounds__(TILE, RIEMANN == 0 ? RICH_FLUX_WAVES : 1) void k_fl
     const int Sm = min(S, kMapCap);
     bool ok = true;
     if (tid == 0) s_nfor = 0;
-    for (int c = tid; c <= c1 - c0; c += TILE) s_off[c] = d.off[c0 + c];
+    for (int c = tid; c <= c1 - c0; c += THREADS) s_off[c] = d.off[c0 + c];
     __syncthreads();
     // all of a lane's CSR entries are loaded first (independent loads in
     // flight together), then classified
-    constexpr int MPT = kMapCap / TILE;
+    constexpr int MPT = (kMapCap + THREADS - 1) / THREADS;
     int ent[MPT];
 #pragma unroll
     for (int r = 0; r < MPT; ++r) {
-      const int s = tid + r * TILE;
+      const int s = tid + r * THREADS;
       ent[r] = s < Sm ? d.idx[kb + s] : -1;
     }
 #pragma unroll
     for (int r = 0; r < MPT; ++r) {
-      const int s = tid + r * TILE;
+      const int s = tid + r * THREADS;
       if (s >= Sm) break;
       const int entry = ent[r];
       const int e = entry >> 1;
@@ -655,7 +668,7 @@ __global__ __launch_bounds__(TILE, RIEMANN == 0 ? RICH_FLUX_WAVES : 1) void k_fl
     }
     __syncthreads();
     const int nfor = min(s_nfor, kForCap);
-    for (int w = tid; w < ne + nfor; w += TILE) {
+    for (int w = tid; w < ne + nfor; w += THREADS) {
       const int e = w < ne ? e0 + w : s_forE[w - ne];
       const int pos = w < ne ? w : kEdgeCap + (w - ne);
       double LF[4];
@@ -665,7 +678,7 @@ __global__ __launch_bounds__(TILE, RIEMANN == 0 ? RICH_FLUX_WAVES : 1) void k_fl
     }
     __syncthreads();
     const int i = c0 + tid;
-    if (i < c1) {
+    if (tid < TILE && i < c1) {
       double acc[4] = {0.0, 0.0, 0.0, 0.0};
       int k0 = s_off[tid], k1 = s_off[tid + 1];
       if (k0 < kb || k1 < k0 || k1 > kb + S) {
@@ -1007,8 +1020,9 @@ void prof_end(int k, hipStream_t st) {
 
 int launch_stage(const RunDesc& d, int riemann, hipStream_t st, uint8_t* dbg_cell = nullptr,
                  uint8_t* dbg_edge = nullptr) {
-  constexpr int T = rich::kTile;
-  const int n_tiles = (d.n + T - 1) / T;
+  constexpr int T = rich::kTile, TS = rich::kSmallTile;
+  const bool small = d.n < rich::kSmallCells;
+  const int n_tiles = small ? (d.n + TS - 1) / TS : (d.n + T - 1) / T;
   constexpr int CPB = rich::kCellThreads / rich::kLpc;
   const int n_ctiles = (d.n + CPB - 1) / CPB;
   hipLaunchKernelGGL(rich::k_clear, dim3(1), dim3(64), 0, st, d.flag, d.cfl_min);
@@ -1034,12 +1048,10 @@ int launch_stage(const RunDesc& d, int riemann, hipStream_t st, uint8_t* dbg_cel
                        (const double*)d.cfl_blocks, n_ctiles, d.cfl_min, d.cfl,
                        const_cast<double*>(d.h_dev), d.flag);
   int pf = prof_begin("k_flux", st);
-  if (riemann == 1)
-    hipLaunchKernelGGL((rich::k_flux<1, false>), dim3(n_tiles), dim3(T), 0, st, d,
-                       (const RunDesc*)nullptr, (const int2*)nullptr, n_tiles);
-  else
-    hipLaunchKernelGGL((rich::k_flux<0, false>), dim3(n_tiles), dim3(T), 0, st, d,
-                       (const RunDesc*)nullptr, (const int2*)nullptr, n_tiles);
+  auto flux = riemann == 1 ? (small ? rich::k_flux<1, false, TS, T> : rich::k_flux<1, false>)
+                           : (small ? rich::k_flux<0, false, TS, T> : rich::k_flux<0, false>);
+  hipLaunchKernelGGL(flux, dim3(n_tiles), dim3(T), 0, st, d, (const RunDesc*)nullptr,
+                     (const int2*)nullptr, n_tiles);
   prof_end(pf, st);
   return hip_status(hipGetLastError());
 }
@@ -1072,12 +1084,12 @@ BatchLayout batch_layout(int32_t n, const int64_t* n_cells) {
   o += align_up((size_t)n * sizeof(double), 256);
   L.rec = o;
   L.rec_off.resize(n);
-  size_t tiles = 0, flux_tiles = 0;   // flux tiles: at most those of the smallest tile, 128
+  size_t tiles = 0, flux_tiles = 0;   // flux tiles: at most those of the smallest tile
   for (int32_t r = 0; r < n; ++r) {
     L.rec_off[r] = o;
     o += align_up((size_t)n_cells[r] * rich::kRecDoubles * sizeof(double), 256);
     tiles += (size_t)((n_cells[r] + CPB - 1) / CPB);
-    flux_tiles += (size_t)((n_cells[r] + 127) / 128);
+    flux_tiles += (size_t)((n_cells[r] + rich::kSmallTile - 1) / rich::kSmallTile);
   }
   L.cflb = o;
   o += align_up(tiles * sizeof(double), 256);
@@ -1178,14 +1190,18 @@ bool plan_is_current(const void* ws, int64_t s) {
 // The batched flux kernel of solver k (0 HLLC, 1 exact) with tiles of `tile` cells.
 void launch_flux_batch(int k, int tile, int grid, hipStream_t st, const RunDesc& dummy,
                        const RunDesc* dd, const int2* tab, int n_tiles) {
-  switch (k * 4 + (tile == 128 ? 0 : tile == 256 ? 1 : 2)) {
-    case 0: hipLaunchKernelGGL((rich::k_flux<0, true, 128>), dim3(grid), dim3(128), 0, st, dummy, dd, tab, n_tiles); break;
-    case 1: hipLaunchKernelGGL((rich::k_flux<0, true, 256>), dim3(grid), dim3(256), 0, st, dummy, dd, tab, n_tiles); break;
-    case 2: hipLaunchKernelGGL((rich::k_flux<0, true, 512>), dim3(grid), dim3(512), 0, st, dummy, dd, tab, n_tiles); break;
-    case 4: hipLaunchKernelGGL((rich::k_flux<1, true, 128>), dim3(grid), dim3(128), 0, st, dummy, dd, tab, n_tiles); break;
-    case 5: hipLaunchKernelGGL((rich::k_flux<1, true, 256>), dim3(grid), dim3(256), 0, st, dummy, dd, tab, n_tiles); break;
-    default: hipLaunchKernelGGL((rich::k_flux<1, true, 512>), dim3(grid), dim3(512), 0, st, dummy, dd, tab, n_tiles); break;
-  }
+  constexpr int TS = rich::kSmallTile, T = rich::kTile;
+  auto flux = [&](auto small, auto t128, auto t256, auto t512) {
+    auto kernel = tile == TS ? small : tile == 128 ? t128 : tile == 256 ? t256 : t512;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(tile == TS ? T : tile), 0, st, dummy, dd, tab,
+                       n_tiles);
+  };
+  if (k == 0)
+    flux(rich::k_flux<0, true, TS, T>, rich::k_flux<0, true, 128>, rich::k_flux<0, true, 256>,
+         rich::k_flux<0, true, 512>);
+  else
+    flux(rich::k_flux<1, true, TS, T>, rich::k_flux<1, true, 128>, rich::k_flux<1, true, 256>,
+         rich::k_flux<1, true, 512>);
 }
 
 
@@ -1622,13 +1638,23 @@ int rich_batch_workspace_size(int32_t n, const int64_t* n_cells, size_t* bytes) 
   return RICH_OK;
 }
 
+namespace {
+constexpr int32_t kTileByCells = 0;   // the flux tile that suits the batch's cells
+int batch_prepare(int32_t n, const rich_mesh* const* meshes, const rich_state* const* src,
+                  const rich_state* const* base, rich_state* const* out, const double* h,
+                  const rich_params* const* params, const double* const* ax,
+                  const double* const* ay, int32_t tile, void* ws, size_t ws_bytes,
+                  void* stream, rich_batch_plan* plan, int courant = 0,
+                  const void* dt_ws = nullptr);
+}  // namespace
+
 int rich_stage_batch_prepare(int32_t n, const rich_mesh* const* meshes,
                              const rich_state* const* src, const rich_state* const* base,
                              rich_state* const* out, const double* h,
                              const rich_params* const* params, void* ws, size_t ws_bytes,
                              void* stream, rich_batch_plan* plan) {
-  return rich_stage_batch_prepare_tile(n, meshes, src, base, out, h, params, rich::kTile, ws,
-                                       ws_bytes, stream, plan);
+  return batch_prepare(n, meshes, src, base, out, h, params, nullptr, nullptr, kTileByCells, ws,
+                       ws_bytes, stream, plan);
 }
 
 namespace {
@@ -1642,8 +1668,7 @@ int batch_prepare(int32_t n, const rich_mesh* const* meshes, const rich_state* c
                   const rich_state* const* base, rich_state* const* out, const double* h,
                   const rich_params* const* params, const double* const* ax,
                   const double* const* ay, int32_t tile, void* ws, size_t ws_bytes,
-                  void* stream, rich_batch_plan* plan, int courant = 0,
-                  const void* dt_ws = nullptr) {
+                  void* stream, rich_batch_plan* plan, int courant, const void* dt_ws) {
   if (n <= 0 || !meshes || !src || !base || !out || !h || !params || !ws || !plan)
     return RICH_E_INVAL;
   if (courant < 0 || courant > 2 || (courant == 2) != (dt_ws != nullptr)) return RICH_E_INVAL;
@@ -1652,9 +1677,10 @@ int batch_prepare(int32_t n, const rich_mesh* const* meshes, const rich_state* c
   if (ax)
     for (int32_t r = 0; r < n; ++r)
       if ((ax[r] == nullptr) != (ay[r] == nullptr)) return RICH_E_INVAL;
-  if (tile != 128 && tile != 256 && tile != 512) return RICH_E_INVAL;
+  if (tile != kTileByCells && tile != 128 && tile != 256 && tile != 512) return RICH_E_INVAL;
   std::memset(plan, 0, sizeof(*plan));
   std::vector<int64_t> nc(n);
+  int64_t cells = 0;
   for (int32_t r = 0; r < n; ++r) {
     const rich_mesh* m = meshes[r];
     if (!valid_mesh(m) || !valid_params(params[r])) return RICH_E_INVAL;
@@ -1669,7 +1695,9 @@ int batch_prepare(int32_t n, const rich_mesh* const* meshes, const rich_state* c
     // stage's Courant minimum exists
     if (courant == 1 && params[r]->integrator == 1) return RICH_E_INVAL;
     nc[r] = cnt;
+    cells += cnt;
   }
+  if (tile == kTileByCells) tile = cells < rich::kSmallCells ? rich::kSmallTile : rich::kTile;
   if (reinterpret_cast<uintptr_t>(ws) & 255) return RICH_E_NOMEM;
   BatchLayout L = batch_layout(n, nc.data());
   if (ws_bytes < L.total) return RICH_E_NOMEM;
@@ -1895,7 +1923,7 @@ int rich_stage_batch_accel(int32_t n, const rich_mesh* const* meshes,
                            const double* const* ay, void* ws, size_t ws_bytes, void* stream) {
   if (!ax || !ay) return RICH_E_INVAL;
   rich_batch_plan plan;
-  const int rc = batch_prepare(n, meshes, src, base, out, h, params, ax, ay, rich::kTile, ws,
+  const int rc = batch_prepare(n, meshes, src, base, out, h, params, ax, ay, kTileByCells, ws,
                                ws_bytes, stream, &plan);
   if (rc) return rc;
   return rich_stage_batch_launch(&plan, ws, stream);
@@ -2188,7 +2216,7 @@ int step_batch_impl(int32_t n, rich_ctx* const* ctxs, rich_state* const* states,
     rich_batch_plan plan;
     int e = batch_prepare((int32_t)m, mp.data(), sp.data(), bp.data(), op.data(), h.data(),
                           pp.data(), ax ? axk.data() : nullptr, ax ? ayk.data() : nullptr,
-                          rich::kTile, ws, ws_bytes, stream, &plan);
+                          kTileByCells, ws, ws_bytes, stream, &plan);
     if (!e) e = rich_stage_batch_launch(&plan, ws, stream);
     if (e) return e;
     std::vector<int32_t> fl(m, 0);
