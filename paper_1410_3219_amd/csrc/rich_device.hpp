@@ -42,6 +42,7 @@ struct RunDesc {
   double *oM, *oPx, *oPy, *oE, *ox, *oy;          // result
   // workspace of this run
   double* rec;       // [n][16] records
+  uint8_t* bad;      // the cell pass's verdicts, one per wave's cells
   double* cfl_blocks;   // Courant minimum of each cell-kernel block, or null
   const double* h_dev;  // if set, the step is h_factor * (*h_dev) (device dt)
   double h_factor;

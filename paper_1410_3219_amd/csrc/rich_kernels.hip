@@ -106,21 +106,22 @@ __device__ __forceinline__ int xcd_tile_rev(int b, int nb) {
 // block finds its run with one load.
 
 // ---------------------------------------------------------------------------
-// workspace header: flag word and Courant minimum
+// The flag word of a run's workspace header is cleared by the run's first
+// block of the cell pass, while no block of that pass touches it: a wave of
+// the pass leaves its verdict in its own byte of d.bad (one per kFlagCells
+// cells, always written), and the pass that follows folds the bytes of its
+// cells into the flag word.  (A launch that cleared the word took 2 us of a
+// 30 x 30 stage's 15.)
 // ---------------------------------------------------------------------------
-__global__ void k_clear(int32_t* flag, unsigned long long* cfl_min) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    *flag = 0;
-    *cfl_min = 0x7FF0000000000000ull;  // +inf
-  }
+constexpr int kFlagCells = 64 / kLpc;   // the cells of a wave of the cell pass
+__device__ __forceinline__ void clear_header(const RunDesc& d) {
+  *d.flag = 0;
+  *d.cfl_min = 0x7FF0000000000000ull;  // +inf
 }
-
-__global__ void k_clear_batch(const RunDesc* __restrict__ descs, int n_runs) {
-  int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r < n_runs) {
-    *descs[r].flag = 0;
-    *descs[r].cfl_min = 0x7FF0000000000000ull;
-  }
+// Whether the cell pass found anything wrong among the kFlagCells cells that
+// cell i is the first of.
+__device__ __forceinline__ bool cells_bad(const RunDesc& d, int i) {
+  return d.bad[i / kFlagCells] != 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -486,7 +487,13 @@ __global__ __launch_bounds__(kCellThreads, RICH_CELL_WAVES) void k_cell(RunDesc 
 #pragma unroll
       for (int q = 0; q < 4; ++q) alpha[q] = group_min<LPC>(alpha[q]);
     }
-    const int bad_any = group_or<LPC>(bad ? 1 : 0);
+    {
+      static_assert(64 / LPC == kFlagCells, "a byte per wave");
+      const unsigned long long wrong = __ballot(bad);
+      const int first = i0 - cl % kFlagCells;   // the wave's first cell
+      if ((threadIdx.x & 63) == 0 && first < d.n) d.bad[first / kFlagCells] = wrong != 0ull;
+      if (threadIdx.x == 0 && tt == tr.y) clear_header(d);
+    }
     if (active) {
       double rec[kRecDoubles];
 #pragma unroll
@@ -535,7 +542,6 @@ __global__ __launch_bounds__(kCellThreads, RICH_CELL_WAVES) void k_cell(RunDesc 
           }
         dst[k] = make_double2(a0, a1);
       }
-      if (bad_any && lane == 0) atomicOr(d.flag, RICH_FLAG_DOMAIN);
       if constexpr (DBG) {
         if (lane == 0) {
           int bits = (shock ? 1 : 0) | (rounded ? 2 : 0);
@@ -637,6 +643,8 @@ __global__ __launch_bounds__(THREADS, RIEMANN == 0 ? RICH_FLUX_WAVES : 1) void k
     const int Sm = min(S, kMapCap);
     bool ok = true;
     if (tid == 0) s_nfor = 0;
+    if (tid < TILE / kFlagCells && c0 + tid * kFlagCells < d.n && cells_bad(d, c0 + tid * kFlagCells))
+      ok = false;
     for (int c = tid; c <= c1 - c0; c += THREADS) s_off[c] = d.off[c0 + c];
     __syncthreads();
     // all of a lane's CSR entries are loaded first (independent loads in
@@ -786,7 +794,7 @@ __global__ __launch_bounds__(kCflThreads) void k_adot(RunDesc d, double* adot) {
   const double* ri = d.rec + (size_t)i * kRecDoubles;
   const double wix = ri[R_WX], wiy = ri[R_WY];
   int k0 = d.off[i], k1 = d.off[i + 1];
-  bool bad = false;
+  bool bad = i % kFlagCells == 0 && cells_bad(d, i);
   if (k0 < 0 || k1 < k0 || k1 > d.n_csr) {
     bad = true;
     k1 = k0;
@@ -912,9 +920,14 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 constexpr int64_t kCellsPerBlock = rich::kCellThreads / rich::kLpc;
 constexpr size_t kDtOffset = 16;  // header: flag @0, Courant minimum @8, dt @16
 
+// the cell pass's verdicts: a byte per kFlagCells cells, at the workspace's end
+constexpr size_t bad_bytes(int64_t n) {
+  return ((size_t)((n + rich::kFlagCells - 1) / rich::kFlagCells) + 255) / 256 * 256;
+}
 constexpr size_t run_ws_size(int64_t n) {
   return rich::kHeader + ((size_t)n * rich::kRecDoubles * sizeof(double) + 255) / 256 * 256 +
-         ((size_t)((n + kCellsPerBlock - 1) / kCellsPerBlock) * sizeof(double) + 255) / 256 * 256;
+         ((size_t)((n + kCellsPerBlock - 1) / kCellsPerBlock) * sizeof(double) + 255) / 256 * 256 +
+         bad_bytes(n);
 }
 size_t run_ws_bytes(int64_t n) { return run_ws_size(n); }
 
@@ -959,6 +972,7 @@ RunDesc make_desc(const rich_mesh* m, const rich_state* src, const rich_state* b
   d.flag = reinterpret_cast<int32_t*>(ws);
   d.cfl_min = reinterpret_cast<unsigned long long*>(ws + 8);
   d.rec = reinterpret_cast<double*>(ws + rich::kHeader);
+  d.bad = reinterpret_cast<uint8_t*>(ws + run_ws_bytes(m->n_cells) - bad_bytes(m->n_cells));
   d.x0 = m->box[0]; d.y0 = m->box[1]; d.x1 = m->box[2]; d.y1 = m->box[3];
   d.Lx = m->box[2] - m->box[0];
   d.Ly = m->box[3] - m->box[1];
@@ -1025,7 +1039,6 @@ int launch_stage(const RunDesc& d, int riemann, hipStream_t st, uint8_t* dbg_cel
   const int n_tiles = small ? (d.n + TS - 1) / TS : (d.n + T - 1) / T;
   constexpr int CPB = rich::kCellThreads / rich::kLpc;
   const int n_ctiles = (d.n + CPB - 1) / CPB;
-  hipLaunchKernelGGL(rich::k_clear, dim3(1), dim3(64), 0, st, d.flag, d.cfl_min);
   int pc = prof_begin("k_cell", st);
   if (dbg_cell != nullptr)
     hipLaunchKernelGGL((rich::k_cell<rich::kLpc, false, true>), dim3(n_ctiles),
@@ -1060,12 +1073,12 @@ int launch_stage(const RunDesc& d, int riemann, hipStream_t st, uint8_t* dbg_cel
 
 // ---------------------------------------------------------------------------
 // batch workspace:  [descriptors][plans][flags][Courant minima][steps]
-//                   [records...][Courant block minima][tile -> run tables]
+//                   [records, verdicts...][Courant block minima][tile -> run tables]
 // Everything before the records depends on the number of runs only.
 // ---------------------------------------------------------------------------
 struct BatchLayout {
   size_t desc, plan, flags, cfl, dt, rec, cflb, tab, total;
-  std::vector<size_t> rec_off;
+  std::vector<size_t> rec_off, bad_off;
 };
 
 BatchLayout batch_layout(int32_t n, const int64_t* n_cells) {
@@ -1084,10 +1097,13 @@ BatchLayout batch_layout(int32_t n, const int64_t* n_cells) {
   o += align_up((size_t)n * sizeof(double), 256);
   L.rec = o;
   L.rec_off.resize(n);
+  L.bad_off.resize(n);
   size_t tiles = 0, flux_tiles = 0;   // flux tiles: at most those of the smallest tile
   for (int32_t r = 0; r < n; ++r) {
     L.rec_off[r] = o;
     o += align_up((size_t)n_cells[r] * rich::kRecDoubles * sizeof(double), 256);
+    L.bad_off[r] = o;
+    o += bad_bytes(n_cells[r]);
     tiles += (size_t)((n_cells[r] + CPB - 1) / CPB);
     flux_tiles += (size_t)((n_cells[r] + rich::kSmallTile - 1) / rich::kSmallTile);
   }
@@ -1593,7 +1609,6 @@ int rich_area_rate(const rich_mesh* m, const rich_state* s, const rich_params* p
   constexpr int CPB = rich::kCellThreads / rich::kLpc;
   const int n_ctiles = (d.n + CPB - 1) / CPB;
   // the cell pass writes the point velocities into the records
-  hipLaunchKernelGGL(rich::k_clear, dim3(1), dim3(64), 0, st, d.flag, d.cfl_min);
   hipLaunchKernelGGL((rich::k_cell<rich::kLpc, false>), dim3(n_ctiles),
                      dim3(rich::kCellThreads),
                      0, st, d, (const RunDesc*)nullptr, (const int2*)nullptr, n_ctiles,
@@ -1719,6 +1734,7 @@ int batch_prepare(int32_t n, const rich_mesh* const* meshes, const rich_state* c
     d.flag = reinterpret_cast<int32_t*>(w + L.flags) + r;
     d.cfl_min = reinterpret_cast<unsigned long long*>(w + L.cfl) + r;
     d.rec = reinterpret_cast<double*>(w + L.rec_off[r]);
+    d.bad = reinterpret_cast<uint8_t*>(w + L.bad_off[r]);
     if (courant == 1) {
       d.cfl_blocks = reinterpret_cast<double*>(w + L.cflb);   // indexed by batch cell tile
       d.h_dev = reinterpret_cast<double*>(w + L.dt) + r;
@@ -1841,7 +1857,6 @@ int rich_stage_batch_launch(const rich_batch_plan* plan, void* ws, void* stream)
   const int32_t* dpc = dplan;   // cell plan: run tile prefix, descriptor indices
   RunDesc dummy;
   std::memset(&dummy, 0, sizeof(dummy));
-  hipLaunchKernelGGL(rich::k_clear_batch, dim3((n + 255) / 256), dim3(256), 0, st, dd, n);
   int pcl = prof_begin("k_cell", st);
   const int2* tab = reinterpret_cast<const int2*>(w + plan->table_offset);
   hipLaunchKernelGGL((rich::k_cell<rich::kLpc, true>), dim3(plan->grid_cell),
