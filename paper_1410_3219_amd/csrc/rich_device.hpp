@@ -374,13 +374,17 @@ __device__ __forceinline__ void pfun(double g, double ps, double rk, double pk, 
                                      double& f, double& fd) {
   if (ps > pk) {
     const double A = 2.0 / ((g + 1.0) * rk), B = (g - 1.0) / (g + 1.0) * pk;
-    const double q = sqrt(A / (ps + B));
+    const double r = 1.0 / (ps + B);
+    const double q = sqrt(A * r);
     f = (ps - pk) * q;
-    fd = q * (1.0 - 0.5 * (ps - pk) / (B + ps));
+    fd = q * (1.0 - 0.5 * (ps - pk) * r);
   } else {
+    // f = 2 c / (g - 1) (x^b - 1) and f' = x^(-(g + 1) / (2 g)) / (rho c), with
+    // x = p / p_k, b = (g - 1) / (2 g): the second power is x^b / x
     const double pr = ps / pk;
-    f = 2.0 * ck / (g - 1.0) * (pow(pr, (g - 1.0) / (2.0 * g)) - 1.0);
-    fd = 1.0 / (rk * ck) * pow(pr, -(g + 1.0) / (2.0 * g));
+    const double xb = pow(pr, (g - 1.0) / (2.0 * g));
+    f = 2.0 * ck / (g - 1.0) * (xb - 1.0);
+    fd = xb / (pr * (rk * ck));
   }
 }
 
@@ -399,19 +403,29 @@ __device__ inline bool exact_flux(double g, double rgm1, const double* WL, const
   const double tiny = 1e-14;
   double ps = 0.5 * (pl + pr) - 0.125 * (ur - ul) * (rl + rr) * (cl + cr);
   if (ps < tiny) ps = tiny;
-  for (int it = 1; it <= 50; ++it) {
-    double fl, fld, fr, frd;
+  // The functions at the last iterate come from those at the one before it
+  // and their slopes: the last change is below 1e-14 of the pressure, so its
+  // square is far below rounding (evaluating them once more took a quarter of
+  // the pass's powers; with the shared power above, 512 x 512 tube: 142 -> 114 us
+  // for the stage).  Without convergence they are evaluated.
+  double fl = 0.0, fr = 0.0;
+  bool converged = false;
+  for (int it = 1; it <= 50 && !converged; ++it) {
+    double fld, frd;
     pfun(g, ps, rl, pl, cl, fl, fld);
     pfun(g, ps, rr, pr, cr, fr, frd);
     double pn = ps - (fl + fr + ur - ul) / (fld + frd);
     if (pn < tiny) pn = tiny;
-    const double change = 2.0 * fabs(pn - ps) / (pn + ps);
+    converged = 2.0 * fabs(pn - ps) / (pn + ps) < 1e-14;
+    fl += fld * (pn - ps);
+    fr += frd * (pn - ps);
     ps = pn;
-    if (change < 1e-14) break;
   }
-  double fl, fld, fr, frd;
-  pfun(g, ps, rl, pl, cl, fl, fld);
-  pfun(g, ps, rr, pr, cr, fr, frd);
+  if (!converged) {
+    double fld, frd;
+    pfun(g, ps, rl, pl, cl, fl, fld);
+    pfun(g, ps, rr, pr, cr, fr, frd);
+  }
   const double us = 0.5 * (ul + ur) + 0.5 * (fr - fl);
   if (br != nullptr) *br = (uint8_t)(0.0 <= us ? 2 : 0);
   // sample at x/t = 0
