@@ -215,6 +215,17 @@ int rich_cfl_dt(const rich_mesh* m, const rich_state* s, const rich_params* p,
                 double* dt, void* ws, size_t ws_bytes, void* stream);
 
 /*
+ * rich_cfl_dt of n runs at once: dt[r] for each (host array).  ws is a batch
+ * workspace of runs of these sizes (rich_batch_workspace_size); plans prepared
+ * on it are stale afterwards.  Synchronises `stream`.  RICH_E_DOMAIN when some
+ * run's step is not a positive number.  At most 65535 runs.
+ */
+int rich_cfl_dt_batch(int32_t n, const rich_mesh* const* meshes,
+                      const rich_state* const* states, const rich_params* const* params,
+                      double* dt, void* ws, size_t ws_bytes, void* stream);
+
+
+/*
  * Area change rate of every cell that the moving edges imply (section 5, eq.
  * areachange): adot[i] = dA_i/dt with the point velocities w of state s on
  * mesh m (section 6).  The actual change of a cell's area over a step differs

@@ -825,8 +825,8 @@ __global__ __launch_bounds__(kCflThreads) void k_adot(RunDesc d, double* adot) {
   if (bad) atomicOr(d.flag, RICH_FLAG_DOMAIN);
 }
 
-__global__ __launch_bounds__(kCflThreads) void k_cfl(RunDesc d, double* block_out) {
-  __shared__ double smin[kCflThreads / 64];
+// The smallest Courant ratio among this thread's cells of a run.
+__device__ __forceinline__ double cfl_of_cells(const RunDesc& d) {
   double t = INFINITY;
   for (int i = blockIdx.x * kCflThreads + threadIdx.x; i < d.n; i += gridDim.x * kCflThreads) {
     double pxi, pyi, A, sxi, syi;
@@ -837,7 +837,11 @@ __global__ __launch_bounds__(kCflThreads) void k_cfl(RunDesc d, double* block_ou
     const double ti = courant_ratio(kin, vx, vy);
     t = fmin(t, ti);
   }
-  const double m = block_min(t, smin);
+  return t;
+}
+__global__ __launch_bounds__(kCflThreads) void k_cfl(RunDesc d, double* block_out) {
+  __shared__ double smin[kCflThreads / 64];
+  const double m = block_min(cfl_of_cells(d), smin);
   if (threadIdx.x == 0) block_out[blockIdx.x] = m;
 }
 
@@ -904,6 +908,67 @@ __global__ __launch_bounds__(kCflBatchThreads) void k_cfl_final_batch(
                                const_cast<double*>(d.h_dev), d.flag);
 }
 
+// Courant minima of many runs: block (x, y) reduces its share of run y's
+// cells to one value, block_out[y * gridDim.x + x].
+__global__ __launch_bounds__(kCflThreads) void k_cfl_runs(const RunDesc* __restrict__ descs,
+                                                          double* block_out) {
+  __shared__ double smin[kCflThreads / 64];
+  const double m = block_min(cfl_of_cells(descs[blockIdx.y]), smin);
+  if (threadIdx.x == 0) block_out[blockIdx.y * gridDim.x + blockIdx.x] = m;
+}
+// ... and of each run's nb block minima the run's minimum, as a number.
+__global__ __launch_bounds__(64) void k_cfl_runs_final(const double* block_in, int nb,
+                                                       double* out) {
+  double t = INFINITY;
+  for (int b = threadIdx.x; b < nb; b += 64) t = fmin(t, block_in[blockIdx.x * nb + b]);
+  for (int o = 32; o > 0; o >>= 1) t = fmin(t, __shfl_xor(t, o));
+  if (threadIdx.x == 0) out[blockIdx.x] = t;
+}
+
+// The end of a step whose stages and rebuilds were all enqueued without a
+// look at their outcome: the new state becomes the caller's if every flag is
+// zero, and the host reads flags and counts from one report (in its pinned
+// memory).
+struct Report {
+  int32_t stage[2];    // flag words of the two stages
+  int32_t retess[2];   // flags of the two rebuilds
+  int64_t n_edges, n_csr;   // of the second rebuild
+};
+struct Commit {
+  const double* src[6];
+  double* dst[6];
+  const int32_t *stage[2], *retess[2];   // (null: not run)
+  const rich_retess_info* info;          // the second rebuild's counts, or null
+  Report* report;
+  int32_t n;
+};
+__device__ __forceinline__ void commit_run(const Commit& c) {
+  Report r;
+  int any = 0;
+  for (int k = 0; k < 2; ++k) {
+    r.stage[k] = c.stage[k] ? *c.stage[k] : 0;
+    r.retess[k] = c.retess[k] ? *c.retess[k] : 0;
+    any |= r.stage[k] | r.retess[k];
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    r.n_edges = c.info ? c.info->n_edges : 0;
+    r.n_csr = c.info ? c.info->n_csr : 0;
+    *c.report = r;
+  }
+  if (any) return;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < c.n; i += gridDim.x * blockDim.x) {
+    double v[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) v[k] = c.src[k][i];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) c.dst[k][i] = v[k];
+  }
+}
+__global__ __launch_bounds__(256) void k_commit(Commit one) { commit_run(one); }
+__global__ __launch_bounds__(256) void k_commit_runs(const Commit* __restrict__ runs) {
+  commit_run(runs[blockIdx.y]);
+}
+
 }  // namespace rich
 
 // ===========================================================================
@@ -911,11 +976,32 @@ __global__ __launch_bounds__(kCflBatchThreads) void k_cfl_final_batch(
 // ===========================================================================
 using rich::RunDesc;
 
+// (rich_retess.hip) a rebuild that also leaves its flags and its counts where
+// later launches read them
+namespace rich_host {
+int retess_reported(const rich_mesh* prev, const double* x, const double* y,
+                    const rich_mesh_bufs* out, void* ws, size_t ws_bytes, int32_t* flags,
+                    rich_retess_info* info, hipStream_t st);
+int retess_batch_reported(int32_t n, const rich_mesh* const* prev, const double* const* x,
+                          const double* const* y, const rich_mesh_bufs* const* out,
+                          void* const* ws, const size_t* ws_bytes, int32_t* const* flags,
+                          rich_retess_info* const* info, void* bws, size_t bws_bytes,
+                          hipStream_t st);
+}  // namespace rich_host
+
 namespace {
 
 int hip_status(hipError_t e) { return e == hipSuccess ? RICH_OK : RICH_E_DEVICE; }
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
+
+// What the stream has left at `src` when it gets there, on the host.
+int read_back(void* dst, const void* src, size_t bytes, hipStream_t st) {
+  return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, st) == hipSuccess &&
+                 hipStreamSynchronize(st) == hipSuccess
+             ? RICH_OK
+             : RICH_E_DEVICE;
+}
 
 constexpr int64_t kCellsPerBlock = rich::kCellThreads / rich::kLpc;
 constexpr size_t kDtOffset = 16;  // header: flag @0, Courant minimum @8, dt @16
@@ -1073,11 +1159,11 @@ int launch_stage(const RunDesc& d, int riemann, hipStream_t st, uint8_t* dbg_cel
 
 // ---------------------------------------------------------------------------
 // batch workspace:  [descriptors][plans][flags][Courant minima][steps]
-//                   [records, verdicts...][Courant block minima][tile -> run tables]
+//                   [first stage's flags][records, verdicts...][Courant block minima][tile -> run tables]
 // Everything before the records depends on the number of runs only.
 // ---------------------------------------------------------------------------
 struct BatchLayout {
-  size_t desc, plan, flags, cfl, dt, rec, cflb, tab, total;
+  size_t desc, plan, flags, cfl, first, dt, rec, cflb, tab, total;
   std::vector<size_t> rec_off, bad_off;
 };
 
@@ -1093,6 +1179,8 @@ BatchLayout batch_layout(int32_t n, const int64_t* n_cells) {
   o += align_up((size_t)n * sizeof(int32_t), 256);
   L.cfl = o;
   o += align_up((size_t)n * sizeof(unsigned long long), 256);
+  L.first = o;   // flag word and minimum of each run's first stage, in a step that keeps both
+  o += align_up((size_t)n * 16, 256);
   L.dt = o;
   o += align_up((size_t)n * sizeof(double), 256);
   L.rec = o;
@@ -1308,6 +1396,15 @@ struct DevMesh {
   }
 };
 
+// What the stages and rebuilds of one step leave on the device.
+struct Outcome {
+  int32_t stage1, retess[2], pad;
+  unsigned long long cfl1;      // (stage1's Courant word, unused)
+  int32_t stage2, pad2;
+  unsigned long long cfl2;
+  rich_retess_info info[2];
+};
+
 struct rich_ctx {
   DevMesh cur, spare, third;
   DevBuf Qh, Xh, Qn, Xn, ws;
@@ -1317,6 +1414,10 @@ struct rich_ctx {
   bool device_tess = false;
   DevBuf rws;                 // rich_retess workspace (header zeroed at allocation)
   DevBuf bws;                 // descriptors of a batched rebuild this context leads
+  DevBuf bws2;                // ... of the second rebuild of a step
+  DevBuf outcome;             // flags and counts of a step that is read at its end (struct Outcome)
+  rich::Report* reports = nullptr;   // pinned: the outcome of the runs of a call this context leads
+  size_t n_reports = 0;
   int64_t n_device = 0, n_fallback = 0;
 };
 
@@ -1356,6 +1457,55 @@ int retess_prepare(rich_ctx* c, int64_t n, DevMesh& dst, hipStream_t st, rich_me
   out.eoff = (int32_t*)dst.b[4].p;
   dst.set = false;
   return RICH_OK;
+}
+
+// Room for n reports in the context's pinned memory.
+int ensure_reports(rich_ctx* c, size_t n) {
+  if (c->n_reports >= n) return RICH_OK;
+  if (c->reports) (void)hipHostFree(c->reports);
+  c->reports = nullptr;
+  c->n_reports = 0;
+  if (hipHostMalloc(reinterpret_cast<void**>(&c->reports), n * sizeof(rich::Report), 0) !=
+      hipSuccess)
+    return RICH_E_NOMEM;
+  c->n_reports = n;
+  return RICH_OK;
+}
+
+// A mesh that a rebuild will leave in dst's buffers: its offsets say how much
+// of them is in use (none, if the rebuild fails).
+rich_mesh pending_view(const rich_mesh& prev, const rich_mesh_bufs& b) {
+  rich_mesh m;
+  (void)rich_retess_view(&b, prev.box, prev.bc, &m);
+  return m;
+}
+
+// Where a step's stages and rebuilds leave the outcome, and the state to
+// commit when all of it is zero.
+rich::Commit make_commit(const rich_ctx* c, const rich_state& next, const rich_state& state,
+                         bool two, bool motion, rich::Report* report) {
+  Outcome* o = static_cast<Outcome*>(c->outcome.p);
+  rich::Commit m;
+  std::memset(&m, 0, sizeof(m));
+  const double* src[6] = {next.M, next.Px, next.Py, next.E, next.x, next.y};
+  double* dst[6] = {state.M, state.Px, state.Py, state.E, state.x, state.y};
+  for (int k = 0; k < 6; ++k) {
+    m.src[k] = src[k];
+    m.dst[k] = dst[k];
+  }
+  m.stage[0] = two ? &o->stage1 : nullptr;
+  m.stage[1] = &o->stage2;
+  if (motion) {
+    m.retess[0] = two ? &o->retess[0] : nullptr;
+    m.retess[1] = &o->retess[1];
+    m.info = &o->info[1];
+  }
+  m.report = report;
+  m.n = (int32_t)next.n_cells;
+  return m;
+}
+bool clean(const rich::Report& r) {
+  return (r.stage[0] | r.stage[1] | r.retess[0] | r.retess[1]) == 0;
 }
 
 // Take a certified rebuilt mesh (counts in info) into dst.
@@ -1592,10 +1742,7 @@ int rich_stage_dt(void* ws, void* stream, double* dt) {
 int rich_stage_flags(void* ws, void* stream, int32_t* flags) {
   if (!ws || !flags) return RICH_E_INVAL;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (hipStreamSynchronize(st) != hipSuccess) return RICH_E_DEVICE;
-  if (hipMemcpy(flags, ws, sizeof(int32_t), hipMemcpyDeviceToHost) != hipSuccess)
-    return RICH_E_DEVICE;
-  return RICH_OK;
+  return read_back(flags, ws, sizeof(int32_t), st);
 }
 
 int rich_area_rate(const rich_mesh* m, const rich_state* s, const rich_params* p, double* adot,
@@ -1635,13 +1782,56 @@ int rich_cfl_dt(const rich_mesh* m, const rich_state* s, const rich_params* p, d
                      (int32_t*)nullptr);
   if (hipGetLastError() != hipSuccess) return RICH_E_DEVICE;
   unsigned long long bits = 0;
-  if (hipStreamSynchronize(st) != hipSuccess) return RICH_E_DEVICE;
-  if (hipMemcpy(&bits, d.cfl_min, sizeof(bits), hipMemcpyDeviceToHost) != hipSuccess)
-    return RICH_E_DEVICE;
+  if (read_back(&bits, d.cfl_min, sizeof(bits), st)) return RICH_E_DEVICE;
   double mn;
   std::memcpy(&mn, &bits, sizeof(mn));
   *dt = p->cfl * mn;
   return (std::isfinite(*dt) && *dt > 0.0) ? RICH_OK : RICH_E_DOMAIN;
+}
+
+int rich_cfl_dt_batch(int32_t n, const rich_mesh* const* meshes, const rich_state* const* states,
+                      const rich_params* const* params, double* dt, void* ws, size_t ws_bytes,
+                      void* stream) {
+  if (n <= 0 || n > 65535 || !meshes || !states || !params || !dt || !ws) return RICH_E_INVAL;
+  std::vector<int64_t> nc(n);
+  int64_t most = 0;
+  for (int32_t r = 0; r < n; ++r) {
+    if (!valid_mesh(meshes[r]) || !valid_params(params[r]) ||
+        !valid_state(states[r], meshes[r]->n_cells, false))
+      return RICH_E_INVAL;
+    nc[r] = meshes[r]->n_cells;
+    most = std::max(most, nc[r]);
+  }
+  const BatchLayout L = batch_layout(n, nc.data());
+  if (ws_bytes < L.total || (reinterpret_cast<uintptr_t>(ws) & 255)) return RICH_E_NOMEM;
+  char* w = static_cast<char*>(ws);
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  std::vector<RunDesc> descs(n);
+  for (int32_t r = 0; r < n; ++r)
+    descs[r] = make_desc(meshes[r], states[r], nullptr, nullptr, 0.0, params[r], w);
+  register_plan(ws);   // (an earlier plan's descriptors are gone)
+  const int up = upload_staged({{w + L.desc, {descs.data(), (size_t)n * sizeof(RunDesc)}}}, st);
+  if (up) return up;
+  // a block per kCflThreads cells of the largest run, 65 536 in all at most:
+  // the n * nb minima fit the place of the records (16 doubles a cell) for any
+  // mix of sizes (nb - 1 <= most / kCflThreads, and nb < 16 from 4097 runs on)
+  const int nb = (int)std::min<int64_t>((most + rich::kCflThreads - 1) / rich::kCflThreads,
+                                        std::max(1, 65536 / n));
+  double* minima = reinterpret_cast<double*>(w + L.rec);
+  double* out = reinterpret_cast<double*>(w + L.cfl);
+  static_assert(rich::kRecDoubles >= 16 && rich::kCflThreads >= 256, "room for the minima");
+  hipLaunchKernelGGL(rich::k_cfl_runs, dim3(nb, n), dim3(rich::kCflThreads), 0, st,
+                     reinterpret_cast<const RunDesc*>(w + L.desc), minima);
+  hipLaunchKernelGGL(rich::k_cfl_runs_final, dim3(n), dim3(64), 0, st, (const double*)minima, nb,
+                     out);
+  if (hipGetLastError() != hipSuccess) return RICH_E_DEVICE;
+  if (read_back(dt, out, (size_t)n * sizeof(double), st)) return RICH_E_DEVICE;
+  int rc = RICH_OK;
+  for (int32_t r = 0; r < n; ++r) {
+    dt[r] *= params[r]->cfl;
+    if (!std::isfinite(dt[r]) || !(dt[r] > 0.0)) rc = RICH_E_DOMAIN;
+  }
+  return rc;
 }
 
 
@@ -1660,7 +1850,7 @@ int batch_prepare(int32_t n, const rich_mesh* const* meshes, const rich_state* c
                   const rich_params* const* params, const double* const* ax,
                   const double* const* ay, int32_t tile, void* ws, size_t ws_bytes,
                   void* stream, rich_batch_plan* plan, int courant = 0,
-                  const void* dt_ws = nullptr);
+                  const void* dt_ws = nullptr, bool first = false);
 }  // namespace
 
 int rich_stage_batch_prepare(int32_t n, const rich_mesh* const* meshes,
@@ -1679,11 +1869,13 @@ namespace {
 // courant: 0 host steps h[r]; 1 each run's step computed in this stage
 // (Courant condition on src) and h = h[r] * step; 2 h = h[r] * the step of
 // run r that an earlier Courant stage left in the batch workspace dt_ws.
+// first: the runs' flag words go to the layout's `first` words.
 int batch_prepare(int32_t n, const rich_mesh* const* meshes, const rich_state* const* src,
                   const rich_state* const* base, rich_state* const* out, const double* h,
                   const rich_params* const* params, const double* const* ax,
                   const double* const* ay, int32_t tile, void* ws, size_t ws_bytes,
-                  void* stream, rich_batch_plan* plan, int courant, const void* dt_ws) {
+                  void* stream, rich_batch_plan* plan, int courant, const void* dt_ws,
+                  bool first) {
   if (n <= 0 || !meshes || !src || !base || !out || !h || !params || !ws || !plan)
     return RICH_E_INVAL;
   if (courant < 0 || courant > 2 || (courant == 2) != (dt_ws != nullptr)) return RICH_E_INVAL;
@@ -1733,6 +1925,10 @@ int batch_prepare(int32_t n, const rich_mesh* const* meshes, const rich_state* c
     RunDesc d = make_desc(meshes[r], src[r], base[r], out[r], h[r], params[r], w);
     d.flag = reinterpret_cast<int32_t*>(w + L.flags) + r;
     d.cfl_min = reinterpret_cast<unsigned long long*>(w + L.cfl) + r;
+    if (first) {
+      d.flag = reinterpret_cast<int32_t*>(w + L.first + 16 * (size_t)r);
+      d.cfl_min = reinterpret_cast<unsigned long long*>(w + L.first + 16 * (size_t)r + 8);
+    }
     d.rec = reinterpret_cast<double*>(w + L.rec_off[r]);
     d.bad = reinterpret_cast<uint8_t*>(w + L.bad_off[r]);
     if (courant == 1) {
@@ -1948,11 +2144,8 @@ int rich_batch_flags(int32_t n, void* ws, void* stream, int32_t* flags) {
   if (n <= 0 || !ws || !flags) return RICH_E_INVAL;
   std::vector<int64_t> one(n, 1);
   BatchLayout L = batch_layout(n, one.data());
-  if (hipStreamSynchronize(static_cast<hipStream_t>(stream)) != hipSuccess) return RICH_E_DEVICE;
-  if (hipMemcpy(flags, static_cast<char*>(ws) + L.flags, (size_t)n * sizeof(int32_t),
-                hipMemcpyDeviceToHost) != hipSuccess)
-    return RICH_E_DEVICE;
-  return RICH_OK;
+  return read_back(flags, static_cast<char*>(ws) + L.flags, (size_t)n * sizeof(int32_t),
+                   static_cast<hipStream_t>(stream));
 }
 
 
@@ -2010,6 +2203,9 @@ void rich_ctx_destroy(rich_ctx* ctx) {
   ctx->third.release();
   ctx->rws.release();
   ctx->bws.release();
+  ctx->bws2.release();
+  ctx->outcome.release();
+  if (ctx->reports) (void)hipHostFree(ctx->reports);
   ctx->Qh.release(); ctx->Xh.release(); ctx->Qn.release(); ctx->Xn.release();
   ctx->ws.release();
   if (ctx->hostX) (void)hipHostFree(ctx->hostX);
@@ -2074,6 +2270,71 @@ int step_stage(const rich_mesh* m, const rich_state* src, const rich_state* base
             : rich_stage(m, src, base, out, h, p, ws, ws_bytes, stream);
 }
 
+// A whole step enqueued at once, its outcome read at its end: no wait between
+// its stages and rebuilds (there were five, each with a copy: 0.15 ms of the
+// 0.33 ms of a step of 101 x 101 cells).  RICH_OK: done, the state is
+// committed.  Any other status but RICH_E_DEVICE: something did not succeed,
+// nothing of the caller's has changed, and the step is to be taken again with
+// a look at each part.
+int step_enqueued(rich_ctx* ctx, rich_state* state, double dt, const rich_params* p,
+                  const double* ax, const double* ay, const rich_mesh& m, const rich_state& half,
+                  const rich_state& next, hipStream_t st) {
+  const bool two = p->integrator == 0, motion = p->motion != 0;
+  const int64_t n = ctx->cur.n;
+  if (!ctx->outcome.ensure(sizeof(Outcome)) || ensure_reports(ctx, 1)) return RICH_E_NOMEM;
+  Outcome* o = static_cast<Outcome*>(ctx->outcome.p);
+  int rc;
+  auto stage = [&](const rich_mesh& mesh, const rich_state& src, const rich_state& out, double h,
+                   int32_t* flag, unsigned long long* cfl) {
+    rich_state s = out;
+    RunDesc d = make_desc(&mesh, &src, state, &s, h, p, static_cast<char*>(ctx->ws.p));
+    d.flag = flag;
+    d.cfl_min = cfl;
+    d.ax = ax;
+    d.ay = ay;
+    return launch_stage(d, p->riemann, st);
+  };
+  auto rebuild = [&](const rich_mesh& prev, const rich_state& s, DevMesh& dst, int which,
+                     rich_mesh& made) {
+    rich_mesh_bufs out;
+    int e = retess_prepare(ctx, n, dst, st, out);
+    if (e) return e;
+    e = rich_host::retess_reported(&prev, s.x, s.y, &out, ctx->rws.p, ctx->rws.cap,
+                                   &o->retess[which], &o->info[which], st);
+    made = pending_view(prev, out);
+    return e;
+  };
+  rich_mesh mh = m, mn = m;
+  if (two) {
+    if ((rc = stage(m, *state, half, 0.5 * dt, &o->stage1, &o->cfl1))) return rc;
+    if (motion) {
+      if ((rc = rebuild(m, half, ctx->spare, 0, mh))) return rc;
+    }
+    if ((rc = stage(mh, half, next, dt, &o->stage2, &o->cfl2))) return rc;
+  } else if ((rc = stage(m, *state, next, dt, &o->stage2, &o->cfl2))) {
+    return rc;
+  }
+  if (motion) {
+    if ((rc = rebuild(mh, next, ctx->third, 1, mn))) return rc;
+  }
+  const rich::Commit c = make_commit(ctx, next, *state, two, motion, ctx->reports);
+  const int blocks = (int)std::min<int64_t>((n + 255) / 256, 4096);
+  hipLaunchKernelGGL(rich::k_commit, dim3(blocks), dim3(256), 0, st, c);
+  if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess)
+    return RICH_E_DEVICE;
+  if (!clean(*ctx->reports)) return RICH_E_MESH;
+  if (motion) {
+    rich_retess_info info;
+    std::memset(&info, 0, sizeof(info));
+    info.n_edges = ctx->reports->n_edges;
+    info.n_csr = ctx->reports->n_csr;
+    retess_adopt(m, info, ctx->third);
+    std::swap(ctx->cur, ctx->third);
+    ctx->n_device += two ? 2 : 1;
+  }
+  return RICH_OK;
+}
+
 int step_impl(rich_ctx* ctx, rich_state* state, double dt, const rich_params* p,
               const double* ax, const double* ay, rich_tess_fn tess,
               rich_tess_release_fn release, void* tess_user, void* stream) {
@@ -2094,6 +2355,10 @@ int step_impl(rich_ctx* ctx, rich_state* state, double dt, const rich_params* p,
   ctx->cur.view(&m);
   rich_mesh mh = m;
   int rc;
+  if (!p->motion || ctx->device_tess) {
+    rc = step_enqueued(ctx, state, dt, p, ax, ay, m, half, next, st);
+    if (rc == RICH_OK || rc == RICH_E_DEVICE) return rc;
+  }
   int32_t flags = 0;
   if (p->integrator == 1) {
     // extrapolated fluxes: one stage on the start-of-step mesh
@@ -2148,6 +2413,144 @@ int rich_step_accel(rich_ctx* ctx, rich_state* state, double dt, const rich_para
 
 namespace {
 
+// The batched step of the runs `of` (two stages each, meshes on the device)
+// enqueued at once and read at its end, as step_enqueued; done[r] is set for
+// the runs that succeeded and were committed, and nothing of the others has
+// changed.  The runs' buffers are there.
+int step_batch_enqueued(const std::vector<int32_t>& of, rich_ctx* const* ctxs,
+                        rich_state* const* states, const double* dt,
+                        const rich_params* const* params, const double* const* ax,
+                        const double* const* ay, char* done, void* ws, size_t ws_bytes,
+                        hipStream_t st) {
+  const int32_t m = (int32_t)of.size();
+  rich_ctx* lead = ctxs[of[0]];   // holds the call's descriptors and reports
+  if (ensure_reports(lead, (size_t)m)) return RICH_E_NOMEM;
+  std::vector<rich_state> half(m), next(m);
+  std::vector<rich_mesh> mesh(m);
+  std::vector<const rich_mesh*> mp(m);
+  std::vector<const rich_state*> sp(m), bp(m);
+  std::vector<rich_state*> op(m);
+  std::vector<double> h(m);
+  std::vector<const rich_params*> pp(m);
+  std::vector<const double*> axk(m, nullptr), ayk(m, nullptr);
+  std::vector<int64_t> nc(m);
+  std::vector<int32_t> moving;
+  int64_t most = 0;
+  for (int32_t k = 0; k < m; ++k) {
+    const int32_t r = of[k];
+    rich_ctx* c = ctxs[r];
+    if (!c->outcome.ensure(sizeof(Outcome))) return RICH_E_NOMEM;
+    nc[k] = c->cur.n;
+    most = std::max(most, nc[k]);
+    half[k] = state_view(c->Qh, c->Xh, nc[k]);
+    next[k] = state_view(c->Qn, c->Xn, nc[k]);
+    c->cur.view(&mesh[k]);
+    mp[k] = &mesh[k];
+    bp[k] = states[r];
+    pp[k] = params[r];
+    if (ax) {
+      axk[k] = ax[r];
+      ayk[k] = ay[r];
+    }
+    if (params[r]->motion) moving.push_back(k);
+  }
+  const BatchLayout L = batch_layout(m, nc.data());
+  if (ws_bytes < L.total) return RICH_E_NOMEM;
+  char* w = static_cast<char*>(ws);
+  auto stage = [&](bool second) -> int {
+    for (int32_t k = 0; k < m; ++k) {
+      sp[k] = second ? &half[k] : states[of[k]];
+      op[k] = second ? &next[k] : &half[k];
+      h[k] = second ? dt[of[k]] : 0.5 * dt[of[k]];
+    }
+    rich_batch_plan plan;
+    const int e = batch_prepare(m, mp.data(), sp.data(), bp.data(), op.data(), h.data(),
+                                pp.data(), ax ? axk.data() : nullptr, ax ? ayk.data() : nullptr,
+                                kTileByCells, ws, ws_bytes, st, &plan, 0, nullptr, !second);
+    return e ? e : rich_stage_batch_launch(&plan, ws, st);
+  };
+  // the meshes of points xs of the moving runs into their spare (first) or
+  // third buffers
+  auto rebuild = [&](const std::vector<rich_state>& xs, int which) -> int {
+    const size_t q = moving.size();
+    if (q == 0) return RICH_OK;
+    std::vector<rich_mesh> prev(q);
+    std::vector<rich_mesh_bufs> ob(q);
+    std::vector<const rich_mesh*> pv(q);
+    std::vector<const rich_mesh_bufs*> ov(q);
+    std::vector<const double*> xv(q), yv(q);
+    std::vector<void*> wv(q);
+    std::vector<size_t> wb(q);
+    std::vector<int32_t*> fv(q);
+    std::vector<rich_retess_info*> iv(q);
+    for (size_t j = 0; j < q; ++j) {
+      const int32_t k = moving[j];
+      rich_ctx* c = ctxs[of[k]];
+      const int e = retess_prepare(c, nc[k], which ? c->third : c->spare, st, ob[j]);
+      if (e) return e;
+      prev[j] = mesh[k];
+      mesh[k] = pending_view(prev[j], ob[j]);
+      pv[j] = &prev[j];
+      ov[j] = &ob[j];
+      xv[j] = xs[k].x;
+      yv[j] = xs[k].y;
+      wv[j] = c->rws.p;
+      wb[j] = c->rws.cap;
+      Outcome* o = static_cast<Outcome*>(c->outcome.p);
+      fv[j] = &o->retess[which];
+      iv[j] = &o->info[which];
+    }
+    size_t bb = 0;
+    DevBuf& bws = which ? lead->bws2 : lead->bws;
+    const int e = rich_retess_batch_workspace_size((int32_t)q, &bb);
+    if (e) return e;
+    if (!bws.ensure(bb)) return RICH_E_NOMEM;
+    return rich_host::retess_batch_reported((int32_t)q, pv.data(), xv.data(), yv.data(), ov.data(),
+                                            wv.data(), wb.data(), fv.data(), iv.data(), bws.p,
+                                            bws.cap, st);
+  };
+  int rc;
+  if ((rc = stage(false)) || (rc = rebuild(half, 0)) || (rc = stage(true)) ||
+      (rc = rebuild(next, 1)))
+    return rc;
+  std::vector<rich::Commit> cm(m);
+  for (int32_t k = 0; k < m; ++k) {
+    const int32_t r = of[k];
+    cm[k] = make_commit(ctxs[r], next[k], *states[r], true, params[r]->motion != 0,
+                        lead->reports + k);
+    cm[k].stage[0] = reinterpret_cast<const int32_t*>(w + L.first + 16 * (size_t)k);
+    cm[k].stage[1] = reinterpret_cast<const int32_t*>(w + L.flags) + k;
+  }
+  // (the stages' descriptors, no longer needed, make room for the commits)
+  static_assert(sizeof(rich::Commit) <= sizeof(RunDesc), "a commit fits a descriptor's place");
+  register_plan(ws);
+  if ((rc = upload_staged({{w + L.desc, {cm.data(), (size_t)m * sizeof(rich::Commit)}}}, st)))
+    return rc;
+  const int blocks = (int)std::min<int64_t>((most + 255) / 256, 256);
+  hipLaunchKernelGGL(rich::k_commit_runs, dim3(blocks, m), dim3(256), 0, st,
+                     reinterpret_cast<const rich::Commit*>(w + L.desc));
+  if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess)
+    return RICH_E_DEVICE;
+  for (int32_t k = 0; k < m; ++k) {
+    const int32_t r = of[k];
+    const rich::Report& rep = lead->reports[k];
+    if (!clean(rep)) continue;
+    done[r] = 1;
+    if (params[r]->motion) {
+      rich_mesh was;
+      ctxs[r]->cur.view(&was);
+      rich_retess_info info;
+      std::memset(&info, 0, sizeof(info));
+      info.n_edges = rep.n_edges;
+      info.n_csr = rep.n_csr;
+      retess_adopt(was, info, ctxs[r]->third);
+      std::swap(ctxs[r]->cur, ctxs[r]->third);
+      ctxs[r]->n_device += 2;
+    }
+  }
+  return RICH_OK;
+}
+
 // The batched step; ax, ay (both null, or host arrays of n device pointers)
 // hold each run's per-cell acceleration, null entries meaning none.
 int step_batch_impl(int32_t n, rich_ctx* const* ctxs, rich_state* const* states,
@@ -2181,10 +2584,11 @@ int step_batch_impl(int32_t n, rich_ctx* const* ctxs, rich_state* const* states,
         !c->Xn.ensure(16 * cn))
       status[r] = RICH_E_NOMEM;
   }
+  std::vector<char> done(n, 0);   // runs whose step is committed already
   // a failure of the call as a whole: no run still pending is committed
   auto fail_all = [&](int e) {
     for (int32_t r = 0; r < n; ++r)
-      if (!status[r]) status[r] = e;
+      if (!status[r] && !done[r]) status[r] = e;
     return e;
   };
   size_t need = 0;
@@ -2192,10 +2596,33 @@ int step_batch_impl(int32_t n, rich_ctx* const* ctxs, rich_state* const* states,
   if (rc) return fail_all(rc);
   if (ws_bytes < need) return fail_all(RICH_E_NOMEM);
 
+  // the runs that can be enqueued whole; those that succeed so are done
+  {
+    std::vector<int32_t> of;
+    for (int32_t r = 0; r < n; ++r)
+      if (!status[r] && params[r]->integrator == 0 && (!params[r]->motion || ctxs[r]->device_tess))
+        of.push_back(r);
+    if (!of.empty() && of.size() <= 65535) {
+      rc = step_batch_enqueued(of, ctxs, states, dt, params, ax, ay, done.data(), ws, ws_bytes,
+                               st);
+      // (anything else, as a run the device rebuild does not take: none is done)
+      if (rc == RICH_E_DEVICE) return fail_all(rc);
+    }
+    std::vector<int32_t> left;
+    for (int32_t r = 0; r < n; ++r)
+      if (!status[r] && !done[r]) left.push_back(r);
+    if (left.empty()) {
+      for (int32_t r = 0; r < n; ++r)
+        if (status[r]) return status[r];
+      return RICH_OK;
+    }
+  }
+  auto pending = [&](int32_t r) { return !status[r] && !done[r]; };
+
   std::vector<rich_state> half(n), next(n);
   std::vector<rich_mesh> mesh(n);
   for (int32_t r = 0; r < n; ++r) {
-    if (status[r]) continue;
+    if (!pending(r)) continue;
     half[r] = state_view(ctxs[r]->Qh, ctxs[r]->Xh, nc[r]);
     next[r] = state_view(ctxs[r]->Qn, ctxs[r]->Xn, nc[r]);
     ctxs[r]->cur.view(&mesh[r]);
@@ -2205,7 +2632,7 @@ int step_batch_impl(int32_t n, rich_ctx* const* ctxs, rich_state* const* states,
   auto stage = [&](bool second) -> int {
     std::vector<int32_t> live;
     for (int32_t r = 0; r < n; ++r)
-      if (!status[r] && !(second && params[r]->integrator == 1)) live.push_back(r);
+      if (pending(r) && !(second && params[r]->integrator == 1)) live.push_back(r);
     if (live.empty()) return RICH_OK;
     const size_t m = live.size();
     std::vector<const rich_mesh*> mp(m);
@@ -2252,7 +2679,7 @@ int step_batch_impl(int32_t n, rich_ctx* const* ctxs, rich_state* const* states,
   auto retessellate = [&](const std::vector<rich_state>& xs, bool half_step) -> int {
     std::vector<int32_t> todo, dev;
     for (int32_t r = 0; r < n; ++r)
-      if (!status[r] && params[r]->motion && !(half_step && params[r]->integrator == 1))
+      if (pending(r) && params[r]->motion && !(half_step && params[r]->integrator == 1))
         (ctxs[r]->device_tess ? dev : todo).push_back(r);
     auto dst_of = [&](int32_t r) -> DevMesh& {
       return half_step ? ctxs[r]->spare : ctxs[r]->third;
@@ -2371,11 +2798,11 @@ int step_batch_impl(int32_t n, rich_ctx* const* ctxs, rich_state* const* states,
   if ((rc = stage(false))) return fail_all(rc);
   bool any_two = false;   // runs with a second stage (time-centred fluxes)
   for (int32_t r = 0; r < n; ++r)
-    if (!status[r] && params[r]->integrator == 0) any_two = true;
+    if (pending(r) && params[r]->integrator == 0) any_two = true;
   if (any_motion && any_two) {
     if ((rc = retessellate(half, true))) return fail_all(rc);
     for (int32_t r = 0; r < n; ++r)
-      if (!status[r] && params[r]->motion && params[r]->integrator == 0)
+      if (pending(r) && params[r]->motion && params[r]->integrator == 0)
         ctxs[r]->spare.view(&mesh[r]);
   }
   if ((rc = stage(true))) return fail_all(rc);
@@ -2384,7 +2811,7 @@ int step_batch_impl(int32_t n, rich_ctx* const* ctxs, rich_state* const* states,
   // only once its whole step has succeeded
   if (any_motion && (rc = retessellate(next, false))) return fail_all(rc);
   for (int32_t r = 0; r < n; ++r) {
-    if (status[r]) continue;
+    if (!pending(r)) continue;
     const size_t b = 8 * (size_t)nc[r];
     const double* sq[6] = {next[r].M, next[r].Px, next[r].Py, next[r].E, next[r].x, next[r].y};
     double* dq[6] = {states[r]->M, states[r]->Px, states[r]->Py, states[r]->E, states[r]->x,
@@ -2395,7 +2822,7 @@ int step_batch_impl(int32_t n, rich_ctx* const* ctxs, rich_state* const* states,
   }
   if (hipStreamSynchronize(st) != hipSuccess) return fail_all(RICH_E_DEVICE);
   for (int32_t r = 0; r < n; ++r)
-    if (!status[r] && params[r]->motion) std::swap(ctxs[r]->cur, ctxs[r]->third);
+    if (pending(r) && params[r]->motion) std::swap(ctxs[r]->cur, ctxs[r]->third);
   for (int32_t r = 0; r < n; ++r)
     if (status[r]) return status[r];
   return RICH_OK;

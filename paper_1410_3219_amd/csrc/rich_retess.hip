@@ -141,6 +141,8 @@ struct Args {
   int32_t* qcnt;       // [kSeg * kSegStride] queue segment counters (every kSegStride-th)
   int32_t* queue;      // [kSeg][qcap] cells left to the clip
   int32_t* nb;         // [p_n_csr] neighbour of each CSR entry of the previous mesh (or null)
+  int32_t* flag_out;   // if set, the flags also go here, and the counts to info_out
+  rich_retess_info* info_out;
   int32_t qcap;        // capacity of a segment: kThreads * ceil(cell blocks / kSeg)
   // geometry
   double x0, y0, x1, y1, Lx, Ly;
@@ -1624,6 +1626,11 @@ __global__ __launch_bounds__(kScanThreads) void k_rt_end(Args one, Batch bt) {
       a.hdr->flags = h.flags;
       a.hdr->sticky = h.sticky;
       s_flags = h.flags;
+      if (a.flag_out != nullptr) {
+        *a.flag_out = h.flags;
+        a.info_out->n_edges = h.n_edges;
+        a.info_out->n_csr = h.n_csr;
+      }
       if (B) {
         bt.hdr_out[run] = h;
         bt.flags_out[run] = h.flags;
@@ -1809,6 +1816,96 @@ size_t batch_bytes(int32_t n) { return batch_flags_offset(n) + rt_align(4 * (siz
 
 }  // namespace
 
+namespace {
+
+// rich_retess, its flags and counts also to flag_out and info_out (device; or null)
+int retess_one(const rich_mesh* prev, const double* x, const double* y,
+               const rich_mesh_bufs* out, void* ws, size_t ws_bytes, int32_t* flag_out,
+               rich_retess_info* info_out, hipStream_t st) {
+  retess::Args a;
+  RtLayout L;
+  const int rc = make_args(prev, x, y, out, ws, ws_bytes, a, L);
+  if (rc) return rc;
+  a.flag_out = flag_out;
+  a.info_out = info_out;
+  const int64_t n = prev->n_cells;
+  const int gc = (int)((n + retess::kThreads - 1) / retess::kThreads);
+  const bool periodic = a.bc == (int)RICH_BOUNDARY_PERIODIC;
+  launch_all<false>(a, retess::Batch{}, gc, L.nb, 1, !periodic, periodic,
+                    a.nb != nullptr && n >= retess::kTieredMin, st);
+  return hipGetLastError() == hipSuccess ? RICH_OK : RICH_E_DEVICE;
+}
+
+// rich_retess_batch, likewise (flag_out, info_out: per run, or null)
+int retess_many(int32_t n, const rich_mesh* const* prev, const double* const* x,
+                const double* const* y, const rich_mesh_bufs* const* out, void* const* ws,
+                const size_t* ws_bytes, int32_t* const* flag_out,
+                rich_retess_info* const* info_out, void* bws, size_t bws_bytes, hipStream_t st) {
+  if (n <= 0 || !prev || !x || !y || !out || !ws || !ws_bytes || !bws) return RICH_E_INVAL;
+  if (bws_bytes < batch_bytes(n) || (reinterpret_cast<uintptr_t>(bws) & 255)) return RICH_E_NOMEM;
+  std::vector<retess::Args> args((size_t)n);
+  std::vector<int32_t> starts(2 * ((size_t)n + 1));
+  int64_t gc = 0, gs = 0;
+  for (int32_t r = 0; r < n; ++r) {
+    RtLayout L;
+    const int rc = make_args(prev[r], x[r], y[r], out[r], ws[r], ws_bytes[r], args[r], L);
+    if (rc) return rc;
+    if (flag_out) {
+      args[r].flag_out = flag_out[r];
+      args[r].info_out = info_out[r];
+    }
+    for (int32_t q = 0; q < r; ++q)
+      if (ws[q] == ws[r]) return RICH_E_INVAL;   // runs need workspaces of their own
+    starts[r] = (int32_t)gc;
+    starts[n + 1 + r] = (int32_t)gs;
+    gc += (prev[r]->n_cells + retess::kThreads - 1) / retess::kThreads;
+    gs += L.nb;
+    if (gc >= INT32_MAX / 2 || gs >= INT32_MAX / 2) return RICH_E_INVAL;
+  }
+  starts[n] = (int32_t)gc;
+  starts[2 * (size_t)n + 1] = (int32_t)gs;
+  char* b = static_cast<char*>(bws);
+  const size_t o_start = rt_align(sizeof(retess::Args) * (size_t)n);
+  // the host arrays die with this call: they go through the pinned staging
+  // ring, whose copies are enqueued on the stream (no wait)
+  const int up = rich_host::upload2(b, args.data(), sizeof(retess::Args) * (size_t)n,
+                                    b + o_start, starts.data(), starts.size() * sizeof(int32_t),
+                                    st);
+  if (up != RICH_OK) return up;
+  retess::Batch bt;
+  bt.descs = reinterpret_cast<const retess::Args*>(b);
+  bt.cstart = reinterpret_cast<const int32_t*>(b + o_start);
+  bt.sstart = bt.cstart + n + 1;
+  bt.hdr_out = reinterpret_cast<retess::Hdr*>(b + batch_hdr_offset(n));
+  bt.flags_out = reinterpret_cast<int32_t*>(b + batch_flags_offset(n));
+  bt.n_runs = n;
+  bool walls = false, periodic = false, tiered = gc >= retess::kTieredMin / retess::kThreads;
+  for (const retess::Args& r : args) {
+    tiered = tiered && r.nb != nullptr;
+    walls = walls || r.bc != (int)RICH_BOUNDARY_PERIODIC;
+    periodic = periodic || r.bc == (int)RICH_BOUNDARY_PERIODIC;
+  }
+  launch_all<true>(args[0], bt, (int)gc, (int)gs, n, walls, periodic, tiered, st);
+  return hipGetLastError() == hipSuccess ? RICH_OK : RICH_E_DEVICE;
+}
+
+}  // namespace
+
+namespace rich_host {
+int retess_reported(const rich_mesh* prev, const double* x, const double* y,
+                    const rich_mesh_bufs* out, void* ws, size_t ws_bytes, int32_t* flags,
+                    rich_retess_info* info, hipStream_t st) {
+  return retess_one(prev, x, y, out, ws, ws_bytes, flags, info, st);
+}
+int retess_batch_reported(int32_t n, const rich_mesh* const* prev, const double* const* x,
+                          const double* const* y, const rich_mesh_bufs* const* out,
+                          void* const* ws, const size_t* ws_bytes, int32_t* const* flags,
+                          rich_retess_info* const* info, void* bws, size_t bws_bytes,
+                          hipStream_t st) {
+  return retess_many(n, prev, x, y, out, ws, ws_bytes, flags, info, bws, bws_bytes, st);
+}
+}  // namespace rich_host
+
 extern "C" {
 
 int rich_retess_capacity(int64_t n_cells, int64_t* cap_edges, int64_t* cap_csr) {
@@ -1827,17 +1924,8 @@ int rich_retess_workspace_size(int64_t n_cells, size_t* bytes) {
 
 int rich_retess(const rich_mesh* prev, const double* x, const double* y,
                 const rich_mesh_bufs* out, void* ws, size_t ws_bytes, void* stream) {
-  retess::Args a;
-  RtLayout L;
-  const int rc = make_args(prev, x, y, out, ws, ws_bytes, a, L);
-  if (rc) return rc;
-  const int64_t n = prev->n_cells;
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  const int gc = (int)((n + retess::kThreads - 1) / retess::kThreads);
-  const bool periodic = a.bc == (int)RICH_BOUNDARY_PERIODIC;
-  launch_all<false>(a, retess::Batch{}, gc, L.nb, 1, !periodic, periodic,
-                    a.nb != nullptr && n >= retess::kTieredMin, st);
-  return hipGetLastError() == hipSuccess ? RICH_OK : RICH_E_DEVICE;
+  return retess_one(prev, x, y, out, ws, ws_bytes, nullptr, nullptr,
+                    static_cast<hipStream_t>(stream));
 }
 
 int rich_retess_view(const rich_mesh_bufs* out, const double box[4], uint32_t bc,
@@ -1866,49 +1954,8 @@ int rich_retess_batch(int32_t n, const rich_mesh* const* prev, const double* con
                       const double* const* y, const rich_mesh_bufs* const* out,
                       void* const* ws, const size_t* ws_bytes, void* bws, size_t bws_bytes,
                       void* stream) {
-  if (n <= 0 || !prev || !x || !y || !out || !ws || !ws_bytes || !bws) return RICH_E_INVAL;
-  if (bws_bytes < batch_bytes(n) || (reinterpret_cast<uintptr_t>(bws) & 255)) return RICH_E_NOMEM;
-  std::vector<retess::Args> args((size_t)n);
-  std::vector<int32_t> starts(2 * ((size_t)n + 1));
-  int64_t gc = 0, gs = 0;
-  for (int32_t r = 0; r < n; ++r) {
-    RtLayout L;
-    const int rc = make_args(prev[r], x[r], y[r], out[r], ws[r], ws_bytes[r], args[r], L);
-    if (rc) return rc;
-    for (int32_t q = 0; q < r; ++q)
-      if (ws[q] == ws[r]) return RICH_E_INVAL;   // runs need workspaces of their own
-    starts[r] = (int32_t)gc;
-    starts[n + 1 + r] = (int32_t)gs;
-    gc += (prev[r]->n_cells + retess::kThreads - 1) / retess::kThreads;
-    gs += L.nb;
-    if (gc >= INT32_MAX / 2 || gs >= INT32_MAX / 2) return RICH_E_INVAL;
-  }
-  starts[n] = (int32_t)gc;
-  starts[2 * (size_t)n + 1] = (int32_t)gs;
-  char* b = static_cast<char*>(bws);
-  const size_t o_start = rt_align(sizeof(retess::Args) * (size_t)n);
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  // the host arrays die with this call: they go through the pinned staging
-  // ring, whose copies are enqueued on the stream (no wait)
-  const int up = rich_host::upload2(b, args.data(), sizeof(retess::Args) * (size_t)n,
-                                    b + o_start, starts.data(), starts.size() * sizeof(int32_t),
-                                    st);
-  if (up != RICH_OK) return up;
-  retess::Batch bt;
-  bt.descs = reinterpret_cast<const retess::Args*>(b);
-  bt.cstart = reinterpret_cast<const int32_t*>(b + o_start);
-  bt.sstart = bt.cstart + n + 1;
-  bt.hdr_out = reinterpret_cast<retess::Hdr*>(b + batch_hdr_offset(n));
-  bt.flags_out = reinterpret_cast<int32_t*>(b + batch_flags_offset(n));
-  bt.n_runs = n;
-  bool walls = false, periodic = false, tiered = gc >= retess::kTieredMin / retess::kThreads;
-  for (const retess::Args& r : args) {
-    tiered = tiered && r.nb != nullptr;
-    walls = walls || r.bc != (int)RICH_BOUNDARY_PERIODIC;
-    periodic = periodic || r.bc == (int)RICH_BOUNDARY_PERIODIC;
-  }
-  launch_all<true>(args[0], bt, (int)gc, (int)gs, n, walls, periodic, tiered, st);
-  return hipGetLastError() == hipSuccess ? RICH_OK : RICH_E_DEVICE;
+  return retess_many(n, prev, x, y, out, ws, ws_bytes, nullptr, nullptr, bws, bws_bytes,
+                     static_cast<hipStream_t>(stream));
 }
 
 int rich_retess_batch_result(int32_t n, void* bws, void* stream, rich_retess_info* info,
@@ -1916,9 +1963,10 @@ int rich_retess_batch_result(int32_t n, void* bws, void* stream, rich_retess_inf
   if (n <= 0 || !bws || !info || !status) return RICH_E_INVAL;
   const size_t o_hdr = batch_hdr_offset(n);
   std::vector<retess::Hdr> h((size_t)n);
-  if (hipStreamSynchronize(static_cast<hipStream_t>(stream)) != hipSuccess ||
-      hipMemcpy(h.data(), static_cast<char*>(bws) + o_hdr, sizeof(retess::Hdr) * (size_t)n,
-                hipMemcpyDeviceToHost) != hipSuccess)
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  if (hipMemcpyAsync(h.data(), static_cast<char*>(bws) + o_hdr, sizeof(retess::Hdr) * (size_t)n,
+                     hipMemcpyDeviceToHost, st) != hipSuccess ||
+      hipStreamSynchronize(st) != hipSuccess)
     return RICH_E_DEVICE;
   for (int32_t r = 0; r < n; ++r) {
     info[r].flags = h[r].flags;
@@ -1944,9 +1992,11 @@ int rich_retess_batch_flags_async(int32_t n, void* bws, void* stream, int32_t* h
 
 int rich_retess_result(void* ws, void* stream, rich_retess_info* info) {
   if (!ws || !info) return RICH_E_INVAL;
-  if (hipStreamSynchronize(static_cast<hipStream_t>(stream)) != hipSuccess) return RICH_E_DEVICE;
+  hipStream_t st = static_cast<hipStream_t>(stream);
   retess::Hdr h;
-  if (hipMemcpy(&h, ws, sizeof(h), hipMemcpyDeviceToHost) != hipSuccess) return RICH_E_DEVICE;
+  if (hipMemcpyAsync(&h, ws, sizeof(h), hipMemcpyDeviceToHost, st) != hipSuccess ||
+      hipStreamSynchronize(st) != hipSuccess)
+    return RICH_E_DEVICE;
   info->flags = h.flags;
   info->sticky = h.sticky;
   info->n_edges = h.n_edges;

@@ -137,6 +137,7 @@ def lib():
         L.rich_stage_accel.argtypes = [mp, sp, sp, sp, C.c_double, pp, _vp, _vp, _vp, C.c_size_t,
                                        _vp]
         L.rich_cfl_dt.argtypes = [mp, sp, pp, _dp, _vp, C.c_size_t, _vp]
+        L.rich_cfl_dt_batch.argtypes = [C.c_int32, _vp, _vp, _vp, _dp, _vp, C.c_size_t, _vp]
         L.rich_area_rate.argtypes = [mp, sp, pp, _vp, _vp, C.c_size_t, _vp]
         L.rich_stage_courant.argtypes = [mp, sp, sp, sp, C.c_double, pp, _vp, C.c_size_t, _vp]
         L.rich_stage_dt_of.argtypes = [mp, sp, sp, sp, C.c_double, _vp, pp, _vp, C.c_size_t,
@@ -162,7 +163,7 @@ def lib():
         L.rich_profile_enable.argtypes = [C.c_int]
         L.rich_profile_read.argtypes = [C.c_char_p, _dp, C.POINTER(C.c_int64)]
         for f in ("rich_workspace_size", "rich_stage", "rich_stage_flags", "rich_cfl_dt",
-                  "rich_stage_courant", "rich_stage_dt_of", "rich_stage_dt", "rich_area_rate",
+                  "rich_cfl_dt_batch", "rich_stage_courant", "rich_stage_dt_of", "rich_stage_dt", "rich_area_rate",
                   "rich_retess_capacity", "rich_retess_workspace_size", "rich_retess",
                   "rich_retess_view", "rich_retess_result", "rich_retess_batch_workspace_size",
                   "rich_retess_batch", "rich_retess_batch_result",
@@ -446,6 +447,22 @@ def rich_cfl_dt(mesh: DeviceMesh, state: DeviceState, params: Params, ws, stream
                            _stream_ptr(stream))
     _check(st, "rich_cfl_dt")
     return dt.value
+
+
+def rich_cfl_dt_batch(meshes, states, params, ws, stream=None):
+    """rich_cfl_dt of len(meshes) runs at once (ws: a batch workspace of runs of
+    these sizes); returns the list of their steps."""
+    n = len(meshes)
+    ad = C.addressof
+    mp = (_vp * n)(*[ad(m.c()) for m in meshes])
+    sp = (_vp * n)(*[ad(x.c()) for x in states])
+    pc = [p.c() for p in params]
+    pp = (_vp * n)(*[ad(x) for x in pc])
+    dt = (C.c_double * n)()
+    st = lib().rich_cfl_dt_batch(n, mp, sp, pp, dt, C.c_void_p(ws.data_ptr()), ws.numel(),
+                                 _stream_ptr(stream))
+    _check(st, "rich_cfl_dt_batch")
+    return list(dt)
 
 
 def rich_area_rate(mesh: DeviceMesh, state: DeviceState, params: Params, ws, stream=None):

@@ -51,7 +51,6 @@ class Sweep:
             self.params.append(R.Params(gamma=P.gamma, chi=chi, eta=eta, motion=1))
         n = m.n_cells
         self.ws = R.batch_workspace([n] * len(self.grid))
-        self.ws_cfl = R.workspace(n)
         self.t = np.zeros(len(self.grid))
         self.steps = np.zeros(len(self.grid), dtype=int)
         self.status = [0] * len(self.grid)
@@ -71,9 +70,11 @@ class Sweep:
             return []
         if dts is None:
             dts = [0.0] * len(self.grid)
-            for r in live:
-                dts[r] = R.rich_cfl_dt(self.ctxs[r].mesh(), self.states[r], self.params[r],
-                                       self.ws_cfl)
+            got = R.rich_cfl_dt_batch([self.ctxs[r].mesh() for r in live],
+                                      [self.states[r] for r in live],
+                                      [self.params[r] for r in live], self.ws)
+            for r, dt in zip(live, got):
+                dts[r] = dt
         dts = list(dts)
         if t_end is not None:
             for r in live:
