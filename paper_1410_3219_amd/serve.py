@@ -160,6 +160,7 @@ class Server:
         self._tpl_index = {id(t): k for k, t in enumerate(templates)}
         self.cells_done = 0
         self.stream = torch.cuda.current_stream()
+        self.poll = None           # submits what has arrived by now (optional)
 
     # -- sessions ---------------------------------------------------------
     @staticmethod
@@ -240,7 +241,8 @@ class Server:
             return
         self.queue.append(req)
 
-    def _launch(self):
+    def _ready(self):
+        """The requests a launch can take now."""
         items = []
         seen = set()
         for req in self.queue:
@@ -249,8 +251,16 @@ class Server:
                 continue
             seen.add(req.sid)     # a session's requests run in order
             items.append(req)
-        if not items:
+        return items
+
+    def _launch(self):
+        if not self._ready():
             return False
+        ev = self.torch.cuda.Event()
+        if self.poll is not None:   # what has arrived meanwhile shares the launch
+            self.poll()
+            self._admit()
+        items = self._ready()
         ss = [self.sessions[r.sid] for r in items]
         meshes = [s.tpl.mesh for s in ss]
         ps = [s.tpl.params for s in ss]
@@ -286,7 +296,6 @@ class Server:
         flags = self.torch.empty((2, len(items)), dtype=self.torch.int32, pin_memory=True)
         R.rich_batch_flags_async(len(items), ws1, flags[0], self.stream)
         R.rich_batch_flags_async(len(items), ws2, flags[1], self.stream)
-        ev = self.torch.cuda.Event()
         ev.record(self.stream)
         for r in items:
             r.phase = 1
@@ -393,7 +402,9 @@ def run(templates, rate=2000.0, duration=2.0, steps_per_session=8, seed=9,
     t0 = time.perf_counter()
     now = lambda: time.perf_counter() - t0   # noqa: E731
     k = 0
-    while k < n_req or srv.queue or srv.inflight:
+
+    def poll():
+        nonlocal k
         t = now()
         while k < n_req and arrivals[k] <= t:
             sid = k // steps_per_session
@@ -403,6 +414,10 @@ def run(templates, rate=2000.0, duration=2.0, steps_per_session=8, seed=9,
                 srv.open_session(sid, ti, min(steps_per_session, n_req - k))
             srv.submit(k, sid, arrivals[k])
             k += 1
+
+    srv.poll = poll
+    while k < n_req or srv.queue or srv.inflight:
+        poll()
         srv.tick(now)
         if now() > duration * 50 + 120:
             raise RuntimeError("serving run did not finish")
