@@ -218,7 +218,7 @@ int rich_cfl_dt(const rich_mesh* m, const rich_state* s, const rich_params* p,
  * rich_cfl_dt of n runs at once: dt[r] for each (host array).  ws is a batch
  * workspace of runs of these sizes (rich_batch_workspace_size); plans prepared
  * on it are stale afterwards.  Synchronises `stream`.  RICH_E_DOMAIN when some
- * run's step is not a positive number.  At most 65535 runs.
+ * run's step is not a positive number.
  */
 int rich_cfl_dt_batch(int32_t n, const rich_mesh* const* meshes,
                       const rich_state* const* states, const rich_params* const* params,
@@ -323,7 +323,8 @@ typedef struct rich_batch_plan {
   int32_t n_group[2];       /* number of HLLC runs, of exact-solver runs        */
   int32_t grid_cell;        /* blocks of the cell kernel (one per tile)        */
   int32_t grid_flux[2];     /* blocks of the two flux kernels (one per tile)   */
-  int32_t flux_tile;        /* cells per flux tile (edge-tile shape)           */
+  int32_t flux_tile;        /* edge-tile shape: cells per flux tile (256 also
+                               where the default splits each tile in four)     */
   int32_t courant;          /* 1: the stage computes each run's step          */
   int64_t serial;           /* identifies the prepare that made the plan       */
   int64_t table_offset;     /* bytes from ws to the tile -> run tables         */
@@ -335,7 +336,8 @@ int rich_stage_batch_prepare(int32_t n, const rich_mesh* const* meshes,
                              void* stream, rich_batch_plan* plan);
 int rich_stage_batch_launch(const rich_batch_plan* plan, void* ws, void* stream);
 /* As rich_stage_batch_prepare, with flux tiles of `tile` cells (128, 256 or
- * 512; rich_stage_batch_prepare takes 256).  A tile is a group of
+ * 512; rich_stage_batch_prepare takes 256, split into tiles of 64 where the
+ * batch has fewer than 81 920 cells in all).  A tile is a group of
  * consecutive cells whose owned edges one workgroup solves; the results do
  * not depend on it, bit for bit (each edge's flux is computed with the same
  * arithmetic wherever it is computed, and each cell sums its edges in CSR

@@ -1269,26 +1269,32 @@ int upload_staged(std::initializer_list<std::pair<void*, std::pair<const void*, 
 // The last plan prepared on each batch workspace: a launch runs only the plan
 // whose descriptors the workspace holds (a later prepare on the same
 // workspace overwrites them, and kernels launched with another plan's sizes
-// would read them out of step).
+// would read them out of step), with flux tiles of the size that its tables
+// were built for.
+struct PlanEntry {
+  int64_t serial;
+  int32_t tile;
+};
 std::mutex& plan_lock() {
   static std::mutex m;
   return m;
 }
-std::unordered_map<const void*, int64_t>& plan_registry() {
-  static std::unordered_map<const void*, int64_t> r;
+std::unordered_map<const void*, PlanEntry>& plan_registry() {
+  static std::unordered_map<const void*, PlanEntry> r;
   return r;
 }
-int64_t register_plan(const void* ws) {
+int64_t register_plan(const void* ws, int32_t tile = 0) {
   static int64_t serial = 0;
   std::lock_guard<std::mutex> g(plan_lock());
   const int64_t s = ++serial;
-  plan_registry()[ws] = s;
+  plan_registry()[ws] = PlanEntry{s, tile};
   return s;
 }
-bool plan_is_current(const void* ws, int64_t s) {
+// The flux tile of plan s if it is the workspace's last one, else 0.
+int32_t current_plan_tile(const void* ws, int64_t s) {
   std::lock_guard<std::mutex> g(plan_lock());
   auto it = plan_registry().find(ws);
-  return it != plan_registry().end() && it->second == s;
+  return it != plan_registry().end() && it->second.serial == s ? it->second.tile : 0;
 }
 
 // The batched flux kernel of solver k (0 HLLC, 1 exact) with tiles of `tile` cells.
@@ -1792,7 +1798,7 @@ int rich_cfl_dt(const rich_mesh* m, const rich_state* s, const rich_params* p, d
 int rich_cfl_dt_batch(int32_t n, const rich_mesh* const* meshes, const rich_state* const* states,
                       const rich_params* const* params, double* dt, void* ws, size_t ws_bytes,
                       void* stream) {
-  if (n <= 0 || n > 65535 || !meshes || !states || !params || !dt || !ws) return RICH_E_INVAL;
+  if (n <= 0 || !meshes || !states || !params || !dt || !ws) return RICH_E_INVAL;
   std::vector<int64_t> nc(n);
   int64_t most = 0;
   for (int32_t r = 0; r < n; ++r) {
@@ -1820,8 +1826,11 @@ int rich_cfl_dt_batch(int32_t n, const rich_mesh* const* meshes, const rich_stat
   double* minima = reinterpret_cast<double*>(w + L.rec);
   double* out = reinterpret_cast<double*>(w + L.cfl);
   static_assert(rich::kRecDoubles >= 16 && rich::kCflThreads >= 256, "room for the minima");
-  hipLaunchKernelGGL(rich::k_cfl_runs, dim3(nb, n), dim3(rich::kCflThreads), 0, st,
-                     reinterpret_cast<const RunDesc*>(w + L.desc), minima);
+  constexpr int32_t kGridY = 65535;   // runs a launch can index
+  for (int32_t r = 0; r < n; r += std::min(kGridY, n - r))
+    hipLaunchKernelGGL(rich::k_cfl_runs, dim3(nb, std::min(kGridY, n - r)),
+                       dim3(rich::kCflThreads), 0, st,
+                       reinterpret_cast<const RunDesc*>(w + L.desc) + r, minima + (size_t)r * nb);
   hipLaunchKernelGGL(rich::k_cfl_runs_final, dim3(n), dim3(64), 0, st, (const double*)minima, nb,
                      out);
   if (hipGetLastError() != hipSuccess) return RICH_E_DEVICE;
@@ -1845,6 +1854,7 @@ int rich_batch_workspace_size(int32_t n, const int64_t* n_cells, size_t* bytes) 
 
 namespace {
 constexpr int32_t kTileByCells = 0;   // the flux tile that suits the batch's cells
+bool offered_tile(int32_t tile) { return tile == 128 || tile == 256 || tile == 512; }
 int batch_prepare(int32_t n, const rich_mesh* const* meshes, const rich_state* const* src,
                   const rich_state* const* base, rich_state* const* out, const double* h,
                   const rich_params* const* params, const double* const* ax,
@@ -1884,7 +1894,6 @@ int batch_prepare(int32_t n, const rich_mesh* const* meshes, const rich_state* c
   if (ax)
     for (int32_t r = 0; r < n; ++r)
       if ((ax[r] == nullptr) != (ay[r] == nullptr)) return RICH_E_INVAL;
-  if (tile != kTileByCells && tile != 128 && tile != 256 && tile != 512) return RICH_E_INVAL;
   std::memset(plan, 0, sizeof(*plan));
   std::vector<int64_t> nc(n);
   int64_t cells = 0;
@@ -1984,14 +1993,14 @@ int batch_prepare(int32_t n, const rich_mesh* const* meshes, const rich_state* c
                                st);
   if (up) return up;
   plan->table_offset = (int64_t)L.tab;
-  plan->serial = register_plan(ws);
+  plan->serial = register_plan(ws, tile);
 
   // One block per tile: the hardware dispatcher then balances tiles of
   // uneven cost (shocks, walls) across the CUs as blocks finish, which a
   // persistent grid of resident blocks with a fixed share each does not
   // (2.20 -> 2.11 ms per step for 256 shock tubes of 4.0M cells in all).
   // The kernels still loop over tiles, so any grid is correct.
-  plan->flux_tile = tile;
+  plan->flux_tile = tile == rich::kSmallTile ? rich::kTile : tile;   // (kTile split in four)
   plan->courant = courant == 1 ? 1 : 0;
   plan->n_runs = n;
   plan->n_cell_tiles = (int32_t)tc;
@@ -2012,6 +2021,7 @@ int rich_stage_batch_prepare_tile(int32_t n, const rich_mesh* const* meshes,
                                   rich_state* const* out, const double* h,
                                   const rich_params* const* params, int32_t tile, void* ws,
                                   size_t ws_bytes, void* stream, rich_batch_plan* plan) {
+  if (!offered_tile(tile)) return RICH_E_INVAL;
   return batch_prepare(n, meshes, src, base, out, h, params, nullptr, nullptr, tile, ws,
                        ws_bytes, stream, plan);
 }
@@ -2022,6 +2032,7 @@ int rich_stage_batch_prepare_courant(int32_t n, const rich_mesh* const* meshes,
                                      const double* factor, const rich_params* const* params,
                                      int32_t tile, const void* dt_ws, void* ws, size_t ws_bytes,
                                      void* stream, rich_batch_plan* plan) {
+  if (!offered_tile(tile)) return RICH_E_INVAL;
   return batch_prepare(n, meshes, src, base, out, factor, params, nullptr, nullptr, tile, ws,
                        ws_bytes, stream, plan, dt_ws ? 2 : 1, dt_ws);
 }
@@ -2042,7 +2053,8 @@ int rich_stage_batch_launch(const rich_batch_plan* plan, void* ws, void* stream)
   if (!plan || !ws || plan->n_runs <= 0 || plan->n_cell_tiles <= 0 || plan->grid_cell <= 0)
     return RICH_E_INVAL;
   if (reinterpret_cast<uintptr_t>(ws) & 255) return RICH_E_NOMEM;
-  if (!plan_is_current(ws, plan->serial)) return RICH_E_INVAL;
+  const int32_t tile = current_plan_tile(ws, plan->serial);
+  if (!tile) return RICH_E_INVAL;
   const int32_t n = plan->n_runs;
   std::vector<int64_t> one(n, 1);
   const BatchLayout L = batch_layout(n, one.data());   // descriptor and plan offsets
@@ -2066,7 +2078,7 @@ int rich_stage_batch_launch(const rich_batch_plan* plan, void* ws, void* stream)
   const int2* ftab = tab + plan->n_cell_tiles;   // flux tiles of group 0, then of group 1
   for (int k = 0; k < 2; ++k) {
     if (plan->n_group[k] > 0 && plan->grid_flux[k] > 0)
-      launch_flux_batch(k, plan->flux_tile, plan->grid_flux[k], st, dummy, dd, ftab,
+      launch_flux_batch(k, tile, plan->grid_flux[k], st, dummy, dd, ftab,
                         plan->n_flux_tiles[k]);
     ftab += plan->n_flux_tiles[k];
   }

@@ -58,3 +58,22 @@ def test_small_and_large_tiles_agree_bitwise(name, nx, ny, shuffled, riemann):
     torch.cuda.synchronize()
     for o in (one, two):
         assert torch.equal(o.Q, big.Q) and torch.equal(o.X, big.X)
+
+
+def test_plan_reports_and_takes_the_offered_shapes_only():
+    """A small batch's default plan reports a shape that the explicit call takes
+    back; the shapes that are not offered are refused by both explicit calls."""
+    from paper_1410_3219_amd import rich as R
+    P, m, Q, X = _mesh("sod", 8, 8, 0)
+    dm, s = R.DeviceMesh.from_host(m), R.DeviceState.from_host(Q, X)
+    out = R.DeviceState.empty_like(s)
+    a = [dm], [s], [s], [out], [1e-3], [R.Params(gamma=P.gamma)]
+    wb = R.batch_workspace([m.n_cells])
+    tile = R.rich_stage_batch_prepare(*a, wb).flux_tile
+    assert R.rich_stage_batch_prepare_tile(*a, tile, wb).flux_tile == tile
+    for bad in (-1, 0, 64, 96):
+        for call in (lambda: R.rich_stage_batch_prepare_tile(*a, bad, wb),
+                     lambda: R.rich_stage_batch_prepare_courant(*a, wb, tile=bad)):
+            with pytest.raises(R.RichError) as e:
+                call()
+            assert e.value.status == R.RICH_E_INVAL
