@@ -625,6 +625,7 @@ __device__ void clip_cell(const Args& a, int i, ClipSlots<kSlots + (WALLS ? 4 : 
     }
     bad = group_or(bad);
     constexpr int CH = 8;   // candidates of a lane whose loads are in flight together
+    constexpr int QD = 4;   // ... that one read of a slot or a vertex is tried on
     for (; group_bits(k < k1) != 0u && !bad; k += CH) {
       uint32_t may = 0;   // the chunk's candidates for the full trial
       {
@@ -643,17 +644,33 @@ __device__ void clip_cell(const Args& a, int i, ClipSlots<kSlots + (WALLS ? 4 : 
           cp[t] = a.xy[cc[t] < 0 ? 0 : cc[t]];
         }
 #pragma unroll
-        for (int t = 0; t < CH; ++t) {
-          double dx, dy;
-          const int32_t id = displacement<WALLS>(a, xi, yi, cc[t], cp[t].x, cp[t].y, dx, dy);
-          const double d2 = dx * dx + dy * dy, hu = 0.5 * d2;
-          if (cc[t] < 0 || 4.0 * reach2 <= d2) continue;
-          bool known = false;
-          for (int v = base; v < nv; ++v) known = known || S.id[v] == id;
-          if (known) continue;
-          double q = -INFINITY;   // the largest projection of a vertex on the candidate
-          for (int v = 0; v < corners; ++v) q = dmax(q, S.v[v].x * dx + S.v[v].y * dy);
-          if (!(hu - q > kVertexMargin * hu + mr)) may |= 1u << t;
+        for (int g = 0; g < CH; g += QD) {
+          double dx[QD], dy[QD], q[QD];   // q: the largest projection of a vertex
+          int32_t id[QD];
+          bool on[QD], any = false;
+#pragma unroll
+          for (int t = 0; t < QD; ++t) {
+            id[t] = displacement<WALLS>(a, xi, yi, cc[g + t], cp[g + t].x, cp[g + t].y, dx[t], dy[t]);
+            on[t] = cc[g + t] >= 0 && !(4.0 * reach2 <= dx[t] * dx[t] + dy[t] * dy[t]);
+            q[t] = -INFINITY;
+            any = any || on[t];
+          }
+          if (!any) continue;
+          for (int v = base; v < nv; ++v) {
+            const int32_t idv = S.id[v];
+#pragma unroll
+            for (int t = 0; t < QD; ++t) on[t] = on[t] && idv != id[t];
+          }
+          for (int v = 0; v < corners; ++v) {
+            const double2 pv = S.v[v];
+#pragma unroll
+            for (int t = 0; t < QD; ++t) q[t] = dmax(q[t], pv.x * dx[t] + pv.y * dy[t]);
+          }
+#pragma unroll
+          for (int t = 0; t < QD; ++t) {
+            const double hu = 0.5 * (dx[t] * dx[t] + dy[t] * dy[t]);
+            if (on[t] && !(hu - q[t] > kVertexMargin * hu + mr)) may |= 1u << (g + t);
+          }
         }
       }
       for (; group_bits(may != 0u) != 0u && !bad; may &= may - 1u) {
