@@ -628,59 +628,71 @@ __device__ void clip_cell(const Args& a, int i, ClipSlots<kSlots + (WALLS ? 4 : 
     constexpr int QD = 4;   // ... that one read of a slot or a vertex is tried on
     for (; group_bits(k < k1) != 0u && !bad; k += CH) {
       uint32_t may = 0;   // the chunk's candidates for the full trial
-      {
-        int cc[CH];
-        double2 cp[CH];
+      int cc[CH];
+      double2 cp[CH];
+      const int tried = nv;   // slots that they are compared with here
 #pragma unroll
-        for (int t = 0; t < CH; ++t)
-          cc[t] = k + t < k1 ? (TIERED ? a.nb[k + t] : a.p_idx[k + t]) : -1;
-        if (!TIERED) {
+      for (int t = 0; t < CH; ++t)
+        cc[t] = k + t < k1 ? (TIERED ? a.nb[k + t] : a.p_idx[k + t]) : -1;
+      if (!TIERED) {
 #pragma unroll
-          for (int t = 0; t < CH; ++t) cc[t] = entry_cell(a, cc[t]);
+        for (int t = 0; t < CH; ++t) cc[t] = entry_cell(a, cc[t]);
+      }
+#pragma unroll
+      for (int t = 0; t < CH; ++t) {
+        if (cc[t] >= a.n || cc[t] == i) cc[t] = -1;
+        cp[t] = a.xy[cc[t] < 0 ? 0 : cc[t]];
+      }
+#pragma unroll
+      for (int g = 0; g < CH; g += QD) {
+        double dx[QD], dy[QD], q[QD];   // q: the largest projection of a vertex
+        int32_t id[QD];
+        bool on[QD], any = false;
+#pragma unroll
+        for (int t = 0; t < QD; ++t) {
+          id[t] = displacement<WALLS>(a, xi, yi, cc[g + t], cp[g + t].x, cp[g + t].y, dx[t], dy[t]);
+          on[t] = cc[g + t] >= 0 && !(4.0 * reach2 <= dx[t] * dx[t] + dy[t] * dy[t]);
+          q[t] = -INFINITY;
+          any = any || on[t];
+        }
+        if (!any) continue;
+        for (int v = base; v < nv; ++v) {
+          const int32_t idv = S.id[v];
+#pragma unroll
+          for (int t = 0; t < QD; ++t) on[t] = on[t] && idv != id[t];
+        }
+        for (int v = 0; v < corners; ++v) {
+          const double2 pv = S.v[v];
+#pragma unroll
+          for (int t = 0; t < QD; ++t) q[t] = dmax(q[t], pv.x * dx[t] + pv.y * dy[t]);
         }
 #pragma unroll
-        for (int t = 0; t < CH; ++t) {
-          if (cc[t] >= a.n || cc[t] == i) cc[t] = -1;
-          cp[t] = a.xy[cc[t] < 0 ? 0 : cc[t]];
-        }
-#pragma unroll
-        for (int g = 0; g < CH; g += QD) {
-          double dx[QD], dy[QD], q[QD];   // q: the largest projection of a vertex
-          int32_t id[QD];
-          bool on[QD], any = false;
-#pragma unroll
-          for (int t = 0; t < QD; ++t) {
-            id[t] = displacement<WALLS>(a, xi, yi, cc[g + t], cp[g + t].x, cp[g + t].y, dx[t], dy[t]);
-            on[t] = cc[g + t] >= 0 && !(4.0 * reach2 <= dx[t] * dx[t] + dy[t] * dy[t]);
-            q[t] = -INFINITY;
-            any = any || on[t];
-          }
-          if (!any) continue;
-          for (int v = base; v < nv; ++v) {
-            const int32_t idv = S.id[v];
-#pragma unroll
-            for (int t = 0; t < QD; ++t) on[t] = on[t] && idv != id[t];
-          }
-          for (int v = 0; v < corners; ++v) {
-            const double2 pv = S.v[v];
-#pragma unroll
-            for (int t = 0; t < QD; ++t) q[t] = dmax(q[t], pv.x * dx[t] + pv.y * dy[t]);
-          }
-#pragma unroll
-          for (int t = 0; t < QD; ++t) {
-            const double hu = 0.5 * (dx[t] * dx[t] + dy[t] * dy[t]);
-            if (on[t] && !(hu - q[t] > kVertexMargin * hu + mr)) may |= 1u << (g + t);
-          }
+        for (int t = 0; t < QD; ++t) {
+          const double hu = 0.5 * (dx[t] * dx[t] + dy[t] * dy[t]);
+          if (on[t] && !(hu - q[t] > kVertexMargin * hu + mr)) may |= 1u << (g + t);
         }
       }
       for (; group_bits(may != 0u) != 0u && !bad; may &= may - 1u) {
         bool on = may != 0u;
-        const int kk = on ? k + __ffs(may) - 1 : 0;
-        const int cj = on ? (TIERED ? a.nb[kk] : prev_neighbour(a, kk)) : i;   // (in range: tried)
-        const double2 pj = a.xy[cj];
+        const int tt = on ? __ffs(may) - 1 : 0;
+        int cj = i;
+        double2 pj = make_double2(xi, yi);
+        if (TIERED) {   // (kept in registers, they would cost a wave per SIMD)
+          if (on) cj = a.nb[k + tt];   // (in range: tried)
+          pj = a.xy[cj];
+        } else {
+#pragma unroll
+          for (int t = 0; t < CH; ++t) {
+            if (on && t == tt) {
+              cj = cc[t];
+              pj = cp[t];
+            }
+          }
+        }
         double dx, dy;
         const int32_t id = displacement<WALLS>(a, xi, yi, cj, pj.x, pj.y, dx, dy);
-        for (int v = base; v < nv; ++v) on = on && S.id[v] != id;
+        // those that entered since (in a full list they may have any place)
+        for (int v = nv < NS ? tried : base; v < nv; ++v) on = on && S.id[v] != id;
         if (group_bits(on) == 0u) continue;
         Part p(dx, dy);
 #pragma unroll 2
