@@ -81,9 +81,10 @@ constexpr int kSegStride = 32;      // int32 counters 128 bytes apart
 // From this many cells (of a call, a batch's runs together) the ring check and
 // the check of the neighbours' neighbours are launches of their own, which
 // loads less; below it one launch does both, and is the faster for it (a
-// rebuild after moves of 0.02 spacings, one launch against two: 61.5 and 63.2
-// us at 64 x 64 cells, 89 and 88 at 256 x 256, 962 and 922 at 1024 x 1024).
-constexpr int kTieredMin = 65536;
+// rebuild after moves of 0.02 spacings, one launch against two: 55 and 71 us at
+// 64 x 64 cells, 71 and 83 at 256 x 256, 115 and 107 at 362 x 362, 188 and 155
+// at 512 x 512, 668 and 477 at 1024 x 1024).
+constexpr int kTieredMin = 98304;
 constexpr int kRingMax = 64;   // CSR entries read per cell of the previous mesh
 constexpr int kThreads = 64;
 constexpr int kScanThreads = 1024;
@@ -437,13 +438,14 @@ __device__ __forceinline__ int32_t& slot_nb(const Args& a, int i, int q) {
 // serial chain of hundreds of operations and loads for one lane, run side by
 // side, and lane l goes through the row of ring member l.  A neighbour's
 // neighbour is first tried against the vertices of the polygon that the ring
-// gives (three operations a vertex); only the few that may cut it meet the
-// trial against every candidate.  A small mesh queues a wave or two of cells,
-// and the chain on an otherwise idle chip is its time: one lane per cell took
-// 143 us for 600 cells of a 64 x 64 tube, 16 lanes 33, this 25; of 60 113 cells
-// of a 511 x 511 one 205, 111 and 66 us; of 370 000 cells (2048 x 2048 wave),
-// where the vector ALU is the bound, 16 lanes without that first trial took
-// 465 us (2000 instructions for 4 cells), this 308.
+// gives (three operations a vertex, four candidates at a time); only the few
+// that may cut it meet the trial against every candidate.  A small mesh queues
+// a wave or two of cells, and the chain on an otherwise idle chip is its time:
+// one lane per cell took 143 us for 600 cells of a 64 x 64 tube, 16 lanes 33,
+// this 20; of 60 113 cells of a 511 x 511 one 205, 111 and 51 us; of 370 000
+// cells (2048 x 2048 wave), where the vector ALU is the bound, 16 lanes without
+// that first trial took 465 us (2000 instructions for 4 cells), this 247.  (One
+// candidate at a time: 25, 66 and 305 us.)
 constexpr int kClipThreads = 256;
 constexpr int kClipCells = kClipThreads / kGroup;   // cells of a block at a time
 constexpr int kClipMaxBlocks = kSeg * 32;           // of one run: the blocks stride
@@ -929,8 +931,9 @@ __global__ __launch_bounds__(kClipThreads) void k_rt_clip(Args one, Batch bt) {
 // The areas and the match of the edges certify the mesh in any case.)
 // The group's loads and stores are contiguous.  (One lane per cell and all candidates at once took
 // 1648 us on the 2048 x 2048 wave, bound by the gathers and their address
-// arithmetic; the two passes take 666, of which 1.1 GB written and 0.43 GB
-// read are 360 at the rate of a large copy, and 309 us.  64 x 64 tube: a
+// arithmetic; the two passes take 375, vector instructions for 260 of them, and
+// 287 us, most of it the gathers of the cells beside a failed one: 61 us where
+// none failed.  64 x 64 tube: a
 // chain of 24 dependent loads, 38 -> 10 us in one launch.)
 
 // Lane l of a cell's group: ring entry l, its displacement from r_i, and the

@@ -1,8 +1,8 @@
 """The two ways the device re-tessellation proves a cell whose neighbours
 stayed: in one launch (small calls), or the ring first and the neighbours'
-neighbours only of cells with a failed neighbour (calls of 65 536 cells and
+neighbours only of cells with a failed neighbour (calls of 98 304 cells and
 more).  A run rebuilt alone takes the first, the same run beside a filler of
-65 536 cells the second; both must give the same bytes (or refuse with the same
+102 400 cells the second; both must give the same bytes (or refuse with the same
 counts), whatever the mesh and however far its points moved."""
 import math
 
@@ -52,7 +52,7 @@ def _bytes(b, info):
 def test_both_paths_give_the_same_mesh(name, k, move):
     import torch
     from paper_1410_3219_amd import rich as R
-    hosts = [_mesh(name, k), _mesh("wave", 256)]
+    hosts = [_mesh(name, k), _mesh("wave", 320)]
     Xs = [torch.from_numpy(_moved(m, move)).cuda() for m in hosts]
     prevs = [R.DeviceMesh.from_host(m) for m in hosts]
 
