@@ -2365,6 +2365,7 @@ int step_impl(rich_ctx* ctx, rich_state* state, double dt, const rich_params* p,
   rich_state next = state_view(ctx->Qn, ctx->Xn, n);
   rich_mesh m;
   ctx->cur.view(&m);
+  if (!valid_mesh(&m)) return RICH_E_INVAL;   // (step_enqueued launches its stages unchecked)
   rich_mesh mh = m;
   int rc;
   if (!p->motion || ctx->device_tess) {
