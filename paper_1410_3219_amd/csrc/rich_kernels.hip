@@ -976,9 +976,10 @@ __global__ __launch_bounds__(256) void k_commit_runs(const Commit* __restrict__ 
 // ===========================================================================
 using rich::RunDesc;
 
-// (rich_retess.hip) a rebuild that also leaves its flags and its counts where
-// later launches read them
+// (rich_retess.hip) whether the rebuild takes a mesh of this kind and size; a
+// rebuild that also leaves its flags and its counts where later launches read them
 namespace rich_host {
+bool retess_takes(const rich_mesh* prev);
 int retess_reported(const rich_mesh* prev, const double* x, const double* y,
                     const rich_mesh_bufs* out, void* ws, size_t ws_bytes, int32_t* flags,
                     rich_retess_info* info, hipStream_t st);
@@ -2368,7 +2369,7 @@ int step_impl(rich_ctx* ctx, rich_state* state, double dt, const rich_params* p,
   if (!valid_mesh(&m)) return RICH_E_INVAL;   // (step_enqueued launches its stages unchecked)
   rich_mesh mh = m;
   int rc;
-  if (!p->motion || ctx->device_tess) {
+  if (!p->motion || (ctx->device_tess && rich_host::retess_takes(&m))) {
     rc = step_enqueued(ctx, state, dt, p, ax, ay, m, half, next, st);
     if (rc == RICH_OK || rc == RICH_E_DEVICE) return rc;
   }
@@ -2609,16 +2610,21 @@ int step_batch_impl(int32_t n, rich_ctx* const* ctxs, rich_state* const* states,
   if (rc) return fail_all(rc);
   if (ws_bytes < need) return fail_all(RICH_E_NOMEM);
 
-  // the runs that can be enqueued whole; those that succeed so are done
+  // the runs that can be enqueued whole; those that succeed so are done (a
+  // run whose rebuild would be refused stays out: it would fail them all)
   {
     std::vector<int32_t> of;
-    for (int32_t r = 0; r < n; ++r)
-      if (!status[r] && params[r]->integrator == 0 && (!params[r]->motion || ctxs[r]->device_tess))
+    for (int32_t r = 0; r < n; ++r) {
+      if (status[r] || params[r]->integrator != 0) continue;
+      rich_mesh m;
+      ctxs[r]->cur.view(&m);
+      if (!params[r]->motion || (ctxs[r]->device_tess && rich_host::retess_takes(&m)))
         of.push_back(r);
+    }
     if (!of.empty() && of.size() <= 65535) {
       rc = step_batch_enqueued(of, ctxs, states, dt, params, ax, ay, done.data(), ws, ws_bytes,
                                st);
-      // (anything else, as a run the device rebuild does not take: none is done)
+      // (anything else: none is done)
       if (rc == RICH_E_DEVICE) return fail_all(rc);
     }
     std::vector<int32_t> left;

@@ -1807,28 +1807,32 @@ RtLayout rt_layout(int64_t n) {
   return L;
 }
 
+// Whether a rebuild takes this previous mesh at all: its counts, arrays and box
+// (periodic: at least 16 cells).
+bool takes_mesh(const rich_mesh* m) {
+  if (!m || m->n_cells <= 0 || m->n_cells > (int64_t)retess::kMask) return false;
+  if (!m->off || !m->eoff || (m->n_csr > 0 && !m->idx) || (m->n_edges > 0 && !m->edges) ||
+      m->n_csr < 0 || m->n_edges < 0 || m->n_csr >= (int64_t)INT32_MAX ||
+      m->n_edges >= (int64_t)INT32_MAX)
+    return false;
+  if (!(m->box[2] > m->box[0]) || !(m->box[3] > m->box[1]) || !std::isfinite(m->box[0]) ||
+      !std::isfinite(m->box[1]) || !std::isfinite(m->box[2]) || !std::isfinite(m->box[3]))
+    return false;
+  return m->bc == RICH_BOUNDARY_WALLS || (m->bc == RICH_BOUNDARY_PERIODIC && m->n_cells >= 16);
+}
+
 // Checks one run's arguments and fills its descriptor; RICH_OK or the status.
 int make_args(const rich_mesh* prev, const double* x, const double* y,
               const rich_mesh_bufs* out, void* ws, size_t ws_bytes, retess::Args& a,
               RtLayout& L) {
-  if (!prev || !x || !y || !out || !ws) return RICH_E_INVAL;
+  if (!x || !y || !out || !ws || !takes_mesh(prev)) return RICH_E_INVAL;
   const int64_t n = prev->n_cells;
-  if (n <= 0 || n > (int64_t)retess::kMask || out->n_cells != n) return RICH_E_INVAL;
-  if (!prev->off || !prev->eoff || (prev->n_csr > 0 && !prev->idx) ||
-      (prev->n_edges > 0 && !prev->edges) || prev->n_csr < 0 || prev->n_edges < 0 ||
-      prev->n_csr >= (int64_t)INT32_MAX || prev->n_edges >= (int64_t)INT32_MAX)
-    return RICH_E_INVAL;
+  if (out->n_cells != n) return RICH_E_INVAL;
   if (!out->cells || !out->edges || !out->off || !out->idx || !out->eoff ||
       (reinterpret_cast<uintptr_t>(out->cells) & 15) ||
       (reinterpret_cast<uintptr_t>(out->edges) & 15) || out->cap_edges <= 0 ||
       out->cap_csr <= 0 || out->cap_csr >= (int64_t)INT32_MAX)
     return RICH_E_INVAL;
-  if (!(prev->box[2] > prev->box[0]) || !(prev->box[3] > prev->box[1]) ||
-      !std::isfinite(prev->box[0]) || !std::isfinite(prev->box[1]) ||
-      !std::isfinite(prev->box[2]) || !std::isfinite(prev->box[3]))
-    return RICH_E_INVAL;
-  if (prev->bc != RICH_BOUNDARY_WALLS && prev->bc != RICH_BOUNDARY_PERIODIC) return RICH_E_INVAL;
-  if (prev->bc == RICH_BOUNDARY_PERIODIC && n < 16) return RICH_E_INVAL;
   L = rt_layout(n);
   if (ws_bytes < L.total || (reinterpret_cast<uintptr_t>(ws) & 255)) return RICH_E_NOMEM;
 
@@ -2004,6 +2008,7 @@ int retess_many(int32_t n, const rich_mesh* const* prev, const double* const* x,
 }  // namespace
 
 namespace rich_host {
+bool retess_takes(const rich_mesh* prev) { return takes_mesh(prev); }
 int retess_reported(const rich_mesh* prev, const double* x, const double* y,
                     const rich_mesh_bufs* out, void* ws, size_t ws_bytes, int32_t* flags,
                     rich_retess_info* info, hipStream_t st) {

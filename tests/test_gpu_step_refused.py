@@ -1,4 +1,7 @@
-"""Calls that the step drivers refuse: what a stage refuses, both of them do."""
+"""Calls that the step drivers refuse: what a stage refuses, both of them do; and
+runs whose meshes the device rebuild does not take (a periodic box of under 16
+cells): their meshes come from the host stage, and the other runs of a batch are
+as if alone."""
 import copy
 
 import numpy as np
@@ -44,3 +47,27 @@ def test_both_drivers_refuse_what_a_stage_refuses(fault):
     assert R.rich_step_batch([ctx], [s], [1e-4], [p], ws) == [R.RICH_E_INVAL]
     assert np.array_equal(s.numpy()[0], Q)
     assert np.array_equal(s.numpy()[1], np.stack([m.px, m.py]))
+
+
+def _steps_equal(R, cases, dts, n_steps):
+    """Steps of the cases as one batch and each alone: the same bits; the
+    counts of device-built and host-built meshes of the batch and alone."""
+    batch, alone = ([_run(R, c) for c in cases] for _ in range(2))
+    ps = [R.Params(gamma=c[0].gamma) for c in cases]
+    ws = R.batch_workspace([c[1].n_cells for c in cases])
+    for _ in range(n_steps):
+        st = R.rich_step_batch([b[0] for b in batch], [b[1] for b in batch], dts, ps, ws)
+        assert st == [R.RICH_OK] * len(cases)
+        for a, dt, p in zip(alone, dts, ps):
+            a[0].step(a[1], dt, p)
+    for a, b in zip(alone, batch):
+        for u, v in zip(a[1].numpy(), b[1].numpy()):
+            assert np.array_equal(u, v)
+    return [b[0].tess_counts() for b in batch], [a[0].tess_counts() for a in alone]
+
+
+def test_a_run_the_rebuild_does_not_take_leaves_the_others_alone():
+    from paper_1410_3219_amd import rich as R
+    cases = [_problem("sod", 20), _problem("wave", 3), _problem("gresho", 24)]
+    batch, alone = _steps_equal(R, cases, [1e-3] * 3, 2)
+    assert batch == alone == [(4, 0), (0, 4), (4, 0)]
