@@ -2697,16 +2697,18 @@ int step_batch_impl(int32_t n, rich_ctx* const* ctxs, rich_state* const* states,
   std::vector<rich_host_mesh_view> hv(n);
   auto retessellate = [&](const std::vector<rich_state>& xs, bool half_step) -> int {
     std::vector<int32_t> todo, dev;
-    for (int32_t r = 0; r < n; ++r)
-      if (pending(r) && params[r]->motion && !(half_step && params[r]->integrator == 1))
-        (ctxs[r]->device_tess ? dev : todo).push_back(r);
+    for (int32_t r = 0; r < n; ++r) {
+      if (!pending(r) || !params[r]->motion || (half_step && params[r]->integrator == 1)) continue;
+      const bool device = ctxs[r]->device_tess && rich_host::retess_takes(&mesh[r]);
+      if (ctxs[r]->device_tess && !device) ++ctxs[r]->n_fallback;
+      (device ? dev : todo).push_back(r);
+    }
     auto dst_of = [&](int32_t r) -> DevMesh& {
       return half_step ? ctxs[r]->spare : ctxs[r]->third;
     };
     if (!dev.empty()) {
-      // one batched rebuild of every device run; runs whose arguments the
-      // device path does not take (a periodic box of under 16 cells) and
-      // uncertified meshes go to the host stage
+      // one batched rebuild of every device run; uncertified meshes go to the
+      // host stage
       const size_t m = dev.size();
       std::vector<rich_mesh_bufs> ob(m);
       std::vector<const rich_mesh*> pp(m);
