@@ -1,7 +1,7 @@
 """Calls that the step drivers refuse: what a stage refuses, both of them do; and
 runs whose meshes the device rebuild does not take (a periodic box of under 16
-cells): their meshes come from the host stage, and the other runs of a batch are
-as if alone."""
+cells) or does not certify (a cell of more neighbours than it holds): their
+meshes come from the host stage, and the other runs of a batch are as if alone."""
 import copy
 
 import numpy as np
@@ -73,3 +73,22 @@ def test_a_run_the_rebuild_does_not_take_leaves_the_others_alone(integrator):
     batch, alone = _steps_equal(R, cases, [1e-3] * 3, 2, integrator)
     k = 2 * (2 - integrator)
     assert batch == alone == [(k, 0), (0, k), (k, 0)]
+
+
+def _hub(petals=20):
+    """A point at rest inside a ring of 20: more neighbours than the device
+    rebuild holds, before and after every step."""
+    P = I.sod(k=20, seed=4)
+    keep = np.hypot(P.px - 0.5, P.py - 0.5) > 0.1
+    a = 2 * np.pi * np.arange(petals) / petals
+    m = T.rich_tess_build(np.concatenate([P.px[keep], [0.5], 0.5 + 0.06 * np.cos(a)]),
+                          np.concatenate([P.py[keep], [0.5], 0.5 + 0.06 * np.sin(a)]), P.box, P.bc)
+    assert np.diff(m.off).max() == petals
+    return P, m, I.conserved(1.0, 0.0, 0.0, 1.0, m.area, P.gamma)
+
+
+def test_a_run_whose_rebuild_fails_leaves_the_others_alone():
+    from paper_1410_3219_amd import rich as R
+    cases = [_problem("sod", 20), _hub(), _problem("gresho", 24)]
+    batch, alone = _steps_equal(R, cases, [1e-3, 1e-5, 1e-3], 3)
+    assert batch == alone == [(6, 0), (0, 6), (6, 0)]
