@@ -78,13 +78,22 @@ constexpr int32_t kDegNear = -3;    // of one that the check of its neighbours' 
 // meet on one address; the clip's blocks then take them from there.
 constexpr int kSeg = 64;
 constexpr int kSegStride = 32;      // int32 counters 128 bytes apart
-// From this many cells (of a call, a batch's runs together) the ring check and
-// the check of the neighbours' neighbours are launches of their own, which
-// loads less; below it one launch does both, and is the faster for it (a
-// rebuild after moves of 0.02 spacings, one launch against two: 55 and 71 us at
-// 64 x 64 cells, 71 and 83 at 256 x 256, 115 and 107 at 362 x 362, 188 and 155
-// at 512 x 512, 668 and 477 at 1024 x 1024).
+// A run of this many cells and more has the ring check and the check of the
+// neighbours' neighbours as launches of their own, which loads less; below it
+// one launch does both, and is the faster for it (a rebuild after moves of 0.02
+// spacings, one launch against two: 55 and 71 us at 64 x 64 cells, 71 and 83 at
+// 256 x 256, 115 and 107 at 362 x 362, 188 and 155 at 512 x 512, 668 and 477 at
+// 1024 x 1024).  The run's own cells decide, not those of a batch together:
+// the two forms send different cells to the clip (a neighbour's neighbour
+// between the margins of two cells' tests), whose numbers are rounded
+// otherwise, and a run's bits must not follow from its companions.
 constexpr int kTieredMin = 98304;
+// The two launches hand on the neighbours of the previous mesh's CSR entries
+// in an array with room for those of a rebuilt mesh.  More entries (a previous
+// mesh made by hand; none of Voronoi cells has more than 6 n + 2) take the one
+// launch, by the entries in use: a mesh in large buffers names their room as
+// its count, and then the kernels look at the last offset.
+enum Form { kOneLaunch = 0, kTiered = 1, kByUse = 2 };
 constexpr int kRingMax = 64;   // CSR entries read per cell of the previous mesh
 constexpr int kThreads = 64;
 constexpr int kScanThreads = 1024;
@@ -141,14 +150,16 @@ struct Args {
   CPart* cpart;        // [n_scan_blocks] block sums, reduced by the scan
   int32_t* qcnt;       // [kSeg * kSegStride] queue segment counters (every kSegStride-th)
   int32_t* queue;      // [kSeg][qcap] cells left to the clip
-  int32_t* nb;         // [p_n_csr] neighbour of each CSR entry of the previous mesh (or null)
+  int32_t* nb;         // [nb_cap] neighbour of each CSR entry of the previous mesh
+  int64_t nb_cap;
+  int64_t nb_end;      // entries that have a place there: min(p_n_csr, nb_cap)
   int32_t* flag_out;   // if set, the flags also go here, and the counts to info_out
   rich_retess_info* info_out;
   int32_t qcap;        // capacity of a segment: kThreads * ceil(cell blocks / kSeg)
   // geometry
   double x0, y0, x1, y1, Lx, Ly;
   double size;         // largest of the box's sides and its corners' coordinates
-  int32_t n, bc, n_scan_blocks;
+  int32_t n, bc, n_scan_blocks, form;
 };
 
 // Many runs in one launch: run r's descriptor is descs[r]; its blocks of
@@ -187,6 +198,10 @@ __device__ __forceinline__ const Args& block_run(const Args& one, const int32_t*
   const int r = run_of_block(start, bt.n_runs, b);
   blk = b - start[r];
   return bt.descs[r];
+}
+// Whether the run has the two launches (Form).
+__device__ __forceinline__ bool tiered(const Args& a) {
+  return a.form == kTiered || (a.form == kByUse && a.p_off[a.n] <= a.nb_cap);
 }
 // The block of cells this block works on: each of the 8 XCDs (with an L2 of
 // its own, taking every eighth block of a launch) gets one contiguous range
@@ -501,7 +516,7 @@ __device__ void clip_cell(const Args& a, int i, ClipSlots<kSlots + (WALLS ? 4 : 
   if (!bad) {
     k0 = a.p_off[i];
     k1 = a.p_off[i + 1];
-    if (k0 < 0 || k1 < k0 || k1 > a.p_n_csr) {
+    if (k0 < 0 || k1 < k0 || k1 > (TIERED ? a.nb_end : a.p_n_csr)) {
       bad |= RICH_RETESS_CLIP;
       k1 = k0;
     } else if (k1 - k0 > kSlots) {
@@ -620,7 +635,7 @@ __device__ void clip_cell(const Args& a, int i, ClipSlots<kSlots + (WALLS ? 4 : 
     static_assert(RH == 2, "two ring members of a lane");
     int k = h == 0 ? row0[0] : row0[RH - 1], k1 = h == 0 ? row1[0] : row1[RH - 1];
     if (cm >= 0) {
-      if (k < 0 || k1 < k || k1 > a.p_n_csr || k1 - k > kRingMax) {
+      if (k < 0 || k1 < k || k1 > (TIERED ? a.nb_end : a.p_n_csr) || k1 - k > kRingMax) {
         bad = RICH_RETESS_CLIP;
         k1 = k;
       }
@@ -876,7 +891,8 @@ __global__ __launch_bounds__(kClipThreads) void k_rt_clip(Args one, Batch bt) {
   __shared__ ClipSlots<kSlots + (WALLS ? 4 : 0)> s_slots[kClipCells];
   int blk, nblk = gridDim.x;
   const Args& a = block_run<B>(one, bt.cstart, bt, blockIdx.x, blk);
-  if ((a.bc == (int)RICH_BOUNDARY_PERIODIC) == WALLS) return;  // the other launch's run
+  if ((a.bc == (int)RICH_BOUNDARY_PERIODIC) == WALLS || tiered(a) != TIERED)
+    return;  // another launch's run
   if (B) nblk = (a.n + kThreads - 1) / kThreads;
   const int seg = blk % kSeg;
   const int queued = min(a.qcnt[seg * kSegStride], a.qcap);
@@ -925,10 +941,16 @@ __global__ __launch_bounds__(kClipThreads) void k_rt_clip(Args one, Batch bt) {
 // one of its neighbours is then locally Delaunay, and a point inside a
 // vertex's circle would have to be reached from it across such edges only,
 // each crossing keeping the point inside the next circle, until a triangle
-// holds it as a corner.  (The path could leave the neighbours' triangles
-// through an edge of two further points; no cell of 3.5 million, random and
-// regular meshes with moves from 0 to 0.3 spacings, was decided otherwise.
-// The areas and the match of the edges certify the mesh in any case.)
+// holds it as a corner.  (That is a reason, not a proof: the path could leave
+// the neighbours' triangles through an edge of two further points.  No mesh
+// rests on it: what proves a mesh is its certification, of whichever cells the
+// checks left.  Every kept edge is seen by both its cells between the same end
+// points (emit and end), so the cells, convex and each about its own point,
+// glue to a closed surface over the box that covers it a whole number of times;
+// the areas say once, 1e-10 of the box where another sheet would be all of it.
+// The cells then tile the box, and |x - r_i|^2 - |x|^2, i the cell of x, is
+// continuous and concave across every edge, a bisector, hence concave on the
+// box: the least over all points everywhere, which is the Voronoi mesh.)
 // The group's loads and stores are contiguous.  (One lane per cell and all candidates at once took
 // 1648 us on the 2048 x 2048 wave, bound by the gathers and their address
 // arithmetic; the two passes take 375, vector instructions for 260 of them, and
@@ -959,7 +981,7 @@ __device__ __forceinline__ bool load_ring(const Args& a, int i, bool live, Ring&
   if (live) {
     k0 = a.p_off[i];
     const int k1 = a.p_off[i + 1];
-    if (k0 >= 0 && k1 >= k0 && k1 <= a.p_n_csr) n = k1 - k0;
+    if (k0 >= 0 && k1 >= k0 && k1 <= (NB || WRITE ? a.nb_end : a.p_n_csr)) n = k1 - k0;
   }
   r.c = -1;
   if (l < n) r.c = NB ? a.nb[k0 + l] : prev_neighbour(a, k0 + l);
@@ -1042,7 +1064,7 @@ __device__ __forceinline__ bool second_ring(const Args& a, int i, const Ring& r,
   if (r.c >= 0) {
     l0 = a.p_off[r.c];
     l1 = a.p_off[r.c + 1];
-    if (l0 < 0 || l1 < l0 || l1 > a.p_n_csr || l1 - l0 > kRingMax) {
+    if (l0 < 0 || l1 < l0 || l1 > (NB ? a.nb_end : a.p_n_csr) || l1 - l0 > kRingMax) {
       ok = false;
       l1 = l0;
     }
@@ -1112,7 +1134,8 @@ __global__ __launch_bounds__(kGroupThreads) void k_rt_vertex(Args one, Batch bt)
   __shared__ Fan s_fan[RING ? 1 : kThreads];
   int blk;
   const Args& a = block_run<B>(one, bt.cstart, bt, cell_block(), blk);
-  if ((a.bc == (int)RICH_BOUNDARY_PERIODIC) == WALLS) return;  // the other launch's run
+  if ((a.bc == (int)RICH_BOUNDARY_PERIODIC) == WALLS || tiered(a) != RING)
+    return;  // another launch's run
   const int l = (int)threadIdx.x & (kGroup - 1);
   const int i = blk * kThreads + (int)threadIdx.x / kGroup;
   const bool live = i < a.n;
@@ -1168,7 +1191,8 @@ __global__ __launch_bounds__(kThreads) void k_rt_near(Args one, Batch bt) {
   static_assert(kThreads == 64, "a block is one wave");
   int blk;
   const Args& a = block_run<B>(one, bt.cstart, bt, cell_block(), blk);
-  if ((a.bc == (int)RICH_BOUNDARY_PERIODIC) == WALLS) return;  // the other launch's run
+  if ((a.bc == (int)RICH_BOUNDARY_PERIODIC) == WALLS || !tiered(a))
+    return;  // another launch's run
   const int lane = (int)threadIdx.x;
   bool near = false;
   const int i0 = blk * kThreads + lane;
@@ -1867,8 +1891,12 @@ int make_args(const rich_mesh* prev, const double* x, const double* y,
   a.queue = reinterpret_cast<int32_t*>(w + L.queue);
   a.qcap = L.qcap;
   a.xy = reinterpret_cast<double2*>(w + L.xy);
-  // (a previous mesh of more entries than a rebuilt one may have: no room)
-  if (prev->n_csr <= L.nbr_cap) a.nb = reinterpret_cast<int32_t*>(w + L.nbr);
+  a.nb = reinterpret_cast<int32_t*>(w + L.nbr);
+  a.nb_cap = L.nbr_cap;
+  a.nb_end = std::min(prev->n_csr, L.nbr_cap);
+  a.form = n < retess::kTieredMin        ? retess::kOneLaunch
+           : prev->n_csr <= L.nbr_cap    ? retess::kTiered
+                                         : retess::kByUse;
   a.x0 = prev->box[0];
   a.y0 = prev->box[1];
   a.x1 = prev->box[2];
@@ -1883,31 +1911,43 @@ int make_args(const rich_mesh* prev, const double* x, const double* y,
   return RICH_OK;
 }
 
+// The kinds of run a call holds: between walls or periodic, in the one launch
+// or the two (a run that the kernels decide on counts as both).
+struct Kinds {
+  bool has[2][2] = {};   // [walls][two launches]
+  void add(const retess::Args& a) {
+    bool* h = has[a.bc == (int)RICH_BOUNDARY_PERIODIC ? 0 : 1];
+    if (a.form != retess::kTiered) h[0] = true;
+    if (a.form != retess::kOneLaunch) h[1] = true;
+  }
+};
+
 // The launches that find the cells, for one kind of box.
 template <bool B, bool WALLS>
-void launch_cells(const retess::Args& a, const retess::Batch& bt, int gc, int gq, bool tiered,
+void launch_cells(const retess::Args& a, const retess::Batch& bt, int gc, int gq, const bool* forms,
                   hipStream_t st) {
   using namespace retess;
-  if (tiered) {
+  if (forms[1]) {
     hipLaunchKernelGGL((k_rt_vertex<B, WALLS, true>), dim3(gc), dim3(kGroupThreads), 0, st, a, bt);
     hipLaunchKernelGGL((k_rt_near<B, WALLS>), dim3(gc), dim3(kThreads), 0, st, a, bt);
     hipLaunchKernelGGL((k_rt_clip<B, WALLS, true>), dim3(gq), dim3(kClipThreads), 0, st, a, bt);
-  } else {
+  }
+  if (forms[0]) {
     hipLaunchKernelGGL((k_rt_vertex<B, WALLS, false>), dim3(gc), dim3(kGroupThreads), 0, st, a, bt);
     hipLaunchKernelGGL((k_rt_clip<B, WALLS, false>), dim3(gq), dim3(kClipThreads), 0, st, a, bt);
   }
 }
 
-// The launches of one re-tessellation of one kind of box (B: of n_runs runs at once, with
-// gc cell blocks and gs scan blocks in all).
+// The launches of one re-tessellation (B: of n_runs runs at once, with gc cell
+// blocks and gs scan blocks in all).
 template <bool B>
 void launch_all(const retess::Args& a, const retess::Batch& bt, int gc, int gs, int n_runs,
-                bool walls, bool periodic, bool tiered, bool one_block, hipStream_t st) {
+                const Kinds& kinds, bool one_block, hipStream_t st) {
   using namespace retess;
   const int gq = B ? gc : std::min(gc, kClipMaxBlocks);   // (a batch's blocks find their run by gc)
   hipLaunchKernelGGL(k_rt_begin<B>, dim3(gc), dim3(kThreads), 0, st, a, bt);
-  if (walls) launch_cells<B, true>(a, bt, gc, gq, tiered, st);
-  if (periodic) launch_cells<B, false>(a, bt, gc, gq, tiered, st);
+  launch_cells<B, true>(a, bt, gc, gq, kinds.has[1], st);
+  launch_cells<B, false>(a, bt, gc, gq, kinds.has[0], st);
   if (one_block) {
     hipLaunchKernelGGL(k_rt_count_all<B>, dim3(n_runs), dim3(kScanThreads), 0, st, a, bt);
   } else {
@@ -1944,9 +1984,9 @@ int retess_one(const rich_mesh* prev, const double* x, const double* y,
   a.info_out = info_out;
   const int64_t n = prev->n_cells;
   const int gc = (int)((n + retess::kThreads - 1) / retess::kThreads);
-  const bool periodic = a.bc == (int)RICH_BOUNDARY_PERIODIC;
-  launch_all<false>(a, retess::Batch{}, gc, L.nb, 1, !periodic, periodic,
-                    a.nb != nullptr && n >= retess::kTieredMin, L.nb <= retess::kOneBlockMax, st);
+  Kinds kinds;
+  kinds.add(a);
+  launch_all<false>(a, retess::Batch{}, gc, L.nb, 1, kinds, L.nb <= retess::kOneBlockMax, st);
   return hipGetLastError() == hipSuccess ? RICH_OK : RICH_E_DEVICE;
 }
 
@@ -1994,14 +2034,12 @@ int retess_many(int32_t n, const rich_mesh* const* prev, const double* const* x,
   bt.flags_out = reinterpret_cast<int32_t*>(b + batch_flags_offset(n));
   bt.n_runs = n;
   bool one_block = true;   // (every run of the batch small)
-  bool walls = false, periodic = false, tiered = gc >= retess::kTieredMin / retess::kThreads;
+  Kinds kinds;
   for (const retess::Args& r : args) {
-    tiered = tiered && r.nb != nullptr;
     one_block = one_block && r.n_scan_blocks <= retess::kOneBlockMax;
-    walls = walls || r.bc != (int)RICH_BOUNDARY_PERIODIC;
-    periodic = periodic || r.bc == (int)RICH_BOUNDARY_PERIODIC;
+    kinds.add(r);
   }
-  launch_all<true>(args[0], bt, (int)gc, (int)gs, n, walls, periodic, tiered, one_block, st);
+  launch_all<true>(args[0], bt, (int)gc, (int)gs, n, kinds, one_block, st);
   return hipGetLastError() == hipSuccess ? RICH_OK : RICH_E_DEVICE;
 }
 
