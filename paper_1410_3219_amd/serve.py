@@ -241,26 +241,26 @@ class Server:
             return
         self.queue.append(req)
 
-    def _ready(self):
-        """The requests a launch can take now."""
-        items = []
-        seen = set()
-        for req in self.queue:
+    def _ready(self, start, items, seen):
+        """Adds to items what a launch can take of the queue from `start` on
+        (seen: the sessions it has a request of)."""
+        for req in self.queue[start:]:
             s = self.sessions[req.sid]
             if req.phase or not s.admitted or req.sid in self.busy or req.sid in seen:
                 continue
             seen.add(req.sid)     # a session's requests run in order
             items.append(req)
-        return items
 
     def _launch(self):
-        if not self._ready():
+        items, seen, looked = [], set(), len(self.queue)
+        self._ready(0, items, seen)
+        if not items:
             return False
         ev = self.torch.cuda.Event()
         if self.poll is not None:   # what has arrived meanwhile shares the launch
             self.poll()
-            self._admit()
-        items = self._ready()
+            self._admit()           # (at most sessions that have just opened)
+            self._ready(looked, items, seen)
         ss = [self.sessions[r.sid] for r in items]
         meshes = [s.tpl.mesh for s in ss]
         ps = [s.tpl.params for s in ss]
