@@ -1721,10 +1721,11 @@ __global__ __launch_bounds__(kScanThreads) void k_rt_end(Args one, Batch bt) {
   int blk;
   const int run = B ? run_of_block(bt.sstart, bt.n_runs, blockIdx.x) : 0;
   const Args& a = block_run<B>(one, bt.sstart, bt, blockIdx.x, blk);
+  const int blocks = B ? min(a.n_scan_blocks, kEndMaxBlocks) : gridDim.x;   // of this run
+  if (blk >= blocks) return;   // (the whole block)
   __shared__ int s_bad, s_flags;   // s_flags: of a finished rebuild, else 0
   if (threadIdx.x == 0) s_bad = s_flags = 0;
   __syncthreads();
-  const int blocks = B ? a.n_scan_blocks : gridDim.x;   // of this run
   for (int i = blk * kScanThreads + threadIdx.x; i < a.n; i += blocks * kScanThreads)
   for (uint32_t chk = a.chk[i]; chk != 0u; chk &= chk - 1u) {
     const int q = __ffs(chk) - 1;

@@ -200,3 +200,21 @@ def test_previous_mesh_of_more_entries_than_a_rebuilt_one():
     assert st2 == R.RICH_OK, info2
     G.compare_meshes(R.mesh_to_host(b2.mesh(), info2["n_edges"], info2["n_csr"]),
                      R.mesh_to_host(b.mesh(), info["n_edges"], info["n_csr"]), 1.0 / 320)
+
+
+def test_a_run_of_many_end_blocks_in_a_batch():
+    """270 400 cells: more blocks of cells (265) than count on one word."""
+    from paper_1410_3219_amd import rich as R
+    hosts = []
+    for name, k in (("wave", 520), ("sod", 20)):
+        P = {"wave": I.advected_wave, "sod": I.sod}[name](k=k, seed=3)
+        hosts.append(T.rich_tess_build(P.px, P.py, P.box, P.bc))
+    Xs = [_points(m, 0.05)[1] for m in hosts]
+    prevs = [R.DeviceMesh.from_host(m) for m in hosts]
+    bufs = [R.DeviceMeshBufs(m.n_cells, m.box, m.bc) for m in hosts]
+    bws = R.rich_retess_batch(prevs, Xs, bufs, [R.retess_workspace(m.n_cells) for m in hosts])
+    for (st, info), b, m, p, X in zip(R.rich_retess_batch_result(2, bws), bufs, hosts, prevs, Xs):
+        assert st == R.RICH_OK, info
+        alone = _rebuild(R, m, p, X)
+        assert (st, info) == alone[:2]
+        assert _bytes(b, info) == _bytes(alone[2], info)
