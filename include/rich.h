@@ -319,7 +319,8 @@ int rich_stage_batch_accel(int32_t n, const rich_mesh* const* meshes,
 typedef struct rich_batch_plan {
   int32_t n_runs;
   int32_t n_cell_tiles;     /* tiles of the cell kernel over all runs          */
-  int32_t n_flux_tiles[2];  /* flux tiles of the HLLC runs, of the exact runs  */
+  int32_t n_flux_tiles[2];  /* flux tiles of the HLLC runs, of the exact runs
+                               (those launched: the split ones, where split)  */
   int32_t n_group[2];       /* number of HLLC runs, of exact-solver runs        */
   int32_t grid_cell;        /* blocks of the cell kernel (one per tile)        */
   int32_t grid_flux[2];     /* blocks of the two flux kernels (one per tile)   */

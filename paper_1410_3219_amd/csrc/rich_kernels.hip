@@ -1658,7 +1658,7 @@ int rich_stage_noalloc(const rich_mesh* m, const rich_state* src, const rich_sta
   if (ws == nullptr) return RICH_E_DEVICE;
   hipStream_t st = static_cast<hipStream_t>(stream);
   RunDesc d = make_desc(m, src, base, out, h, p, ws);
-  const int rc = launch_stage(d, p->riemann, st);  // clears the flag word with a kernel
+  const int rc = launch_stage(d, p->riemann, st);  // (its cell pass clears the flag word)
   if (rc) return rc;
   if (flag_out) hipLaunchKernelGGL(rich::k_copy_flag, dim3(1), dim3(64), 0, st, d.flag, flag_out);
   return hip_status(hipGetLastError());

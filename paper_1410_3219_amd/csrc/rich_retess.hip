@@ -37,6 +37,7 @@
 //                 rules, scanned within blocks of cells
 //   k_rt_scan_blocks  the scan over the blocks, totals, the checks of areas
 //                 and capacities
+//   k_rt_count_all  (small runs) both of these in one launch
 //   k_rt_emit     off[], eoff[], edge records and the CSR entries of both
 //                 sides of each edge, found in the neighbour's slots
 //   k_rt_end      compares the few edges that emit cannot decide, folds the
@@ -86,7 +87,9 @@ constexpr int kSegStride = 32;      // int32 counters 128 bytes apart
 // 1024 x 1024).  The run's own cells decide, not those of a batch together:
 // the two forms send different cells to the clip (a neighbour's neighbour
 // between the margins of two cells' tests), whose numbers are rounded
-// otherwise, and a run's bits must not follow from its companions.
+// otherwise, and a run's bits must not follow from its companions.  (By the
+// cells of a whole batch 64 runs of 16 384 cells took 693 us, so 869; 6 of
+// 65 536 262 and 313; 16 of 10 000 156 and 173.)
 constexpr int kTieredMin = 98304;
 // The two launches hand on the neighbours of the previous mesh's CSR entries
 // in an array with room for those of a rebuilt mesh.  More entries (a previous
@@ -206,8 +209,9 @@ __device__ __forceinline__ bool tiered(const Args& a) {
 // The block of cells this block works on: each of the 8 XCDs (with an L2 of
 // its own, taking every eighth block of a launch) gets one contiguous range
 // of them, so that the neighbours' rows, points and offsets that a block
-// gathers are mostly in its XCD's L2 (2048 x 2048 wave: the ring check reads
-// 0.29 GB instead of 0.43 from beyond it; 511 x 511 tube, emit: 19.8 -> 18.6 us).
+// gathers are mostly in its XCD's L2 (2048 x 2048 wave, read from beyond it
+// with plain order and with this: ring check 0.87 and 0.60 GB, near check 0.37
+// and 0.18, emit 0.49 and 0.24; 511 x 511 tube, emit: 19.8 -> 18.6 us).
 __device__ __forceinline__ int cell_block() {
   constexpr int kNumXcd = 8;
   const int nb = gridDim.x, x = blockIdx.x % kNumXcd, rem = nb % kNumXcd;
@@ -941,7 +945,7 @@ __global__ __launch_bounds__(kClipThreads) void k_rt_clip(Args one, Batch bt) {
 //
 // The neighbours' neighbours (about 36 per cell, most of them several times
 // over) are most of the loads.  Large meshes therefore try only the ring at
-// first (TIER_RING), and a second pass (k_rt_near) tries the neighbours'
+// first (RING), and a second pass (k_rt_near) tries the neighbours'
 // neighbours of those cells that have a failed neighbour.  For the others
 // they cannot matter: every edge of the old triangulation at the point or at
 // one of its neighbours is then locally Delaunay, and a point inside a
@@ -959,10 +963,10 @@ __global__ __launch_bounds__(kClipThreads) void k_rt_clip(Args one, Batch bt) {
 // box: the least over all points everywhere, which is the Voronoi mesh.)
 // The group's loads and stores are contiguous.  (One lane per cell and all candidates at once took
 // 1648 us on the 2048 x 2048 wave, bound by the gathers and their address
-// arithmetic; the two passes take 375, vector instructions for 260 of them, and
-// 287 us, most of it the gathers of the cells beside a failed one: 61 us where
-// none failed.  64 x 64 tube: a
-// chain of 24 dependent loads, 38 -> 10 us in one launch.)
+// arithmetic; the two passes take 367, vector instructions for 260 of them, and
+// 205 us over a chain of steps, most of it the gathers of the cells beside a
+// failed one: 62 us where none failed.  64 x 64 tube: a chain of 24 dependent
+// loads, 38 -> 10 us in one launch.)
 
 // Lane l of a cell's group: ring entry l, its displacement from r_i, and the
 // vertex after it.
