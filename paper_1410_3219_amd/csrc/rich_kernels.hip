@@ -623,8 +623,16 @@ __global__ __launch_bounds__(THREADS, RIEMANN == 0 ? RICH_FLUX_WAVES : 1) void k
   // (about 3 per cell), of other edges the tile's cells need (its border),
   // and the classification of the tile's CSR entries (about 6 per cell)
   constexpr int kEdgeCap = TILE * 25 / 8, kMapCap = TILE * 9;
-  constexpr int kForCap = TILE == kSmallTile ? TILE * 3 / 2 : TILE * 3 / 4;
-  __shared__ double sF[4][kEdgeCap + kForCap];
+  // A small tile's border is a larger share, and most of its edges where the
+  // cells lie in no order (64 cells then have about 384): owned and border edges
+  // share one range of slots there.  An edge past it is computed where it is
+  // needed, by few threads one after another (with 96 border slots instead, a
+  // stage of 200 x 200 cells in random order took 55 us and 227 with the exact
+  // solver, so 48 and 84; 30 x 30 29 and 113, so 20 and 38; in order no change).
+  constexpr bool kShared = TILE == kSmallTile;
+  constexpr int kForCap = kShared ? TILE * 6 : TILE * 3 / 4;
+  constexpr int kSlotCap = kShared ? TILE * 7 : kEdgeCap + kForCap;
+  __shared__ double sF[4][kSlotCap];
   __shared__ int s_forE[kForCap];
   __shared__ short s_map[kMapCap];  // (flux slot << 1) | side, or -1
   __shared__ int s_off[TILE + 1];  // the tile's CSR offsets
@@ -641,6 +649,9 @@ __global__ __launch_bounds__(THREADS, RIEMANN == 0 ? RICH_FLUX_WAVES : 1) void k
     const int kb = d.off[c0];
     const int S = max(0, min(d.off[c1], d.n_csr) - kb);
     const int Sm = min(S, kMapCap);
+    // the border's first slot, and its capacity
+    const int f0 = kShared ? ne : kEdgeCap;
+    const int fcap = kShared ? min(kForCap, kSlotCap - ne) : kForCap;
     bool ok = true;
     if (tid == 0) s_nfor = 0;
     if (tid < TILE / kFlagCells && c0 + tid * kFlagCells < d.n && cells_bad(d, c0 + tid * kFlagCells))
@@ -667,18 +678,18 @@ __global__ __launch_bounds__(THREADS, RIEMANN == 0 ? RICH_FLUX_WAVES : 1) void k
         m = e - e0;
       } else if (e >= 0 && e < d.n_edges) {
         const int f = atomicAdd(&s_nfor, 1);
-        if (f < kForCap) {
+        if (f < fcap) {
           s_forE[f] = e;
-          m = kEdgeCap + f;
+          m = f0 + f;
         }
       }
       s_map[s] = (short)(m < 0 ? -1 : (m << 1) | (entry & 1));
     }
     __syncthreads();
-    const int nfor = min(s_nfor, kForCap);
+    const int nfor = min(s_nfor, fcap);
     for (int w = tid; w < ne + nfor; w += THREADS) {
       const int e = w < ne ? e0 + w : s_forE[w - ne];
-      const int pos = w < ne ? w : kEdgeCap + (w - ne);
+      const int pos = w < ne ? w : f0 + (w - ne);
       double LF[4];
       if (!flux_of_edge<RIEMANN>(d, e, LF)) ok = false;
 #pragma unroll
