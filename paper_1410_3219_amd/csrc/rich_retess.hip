@@ -129,6 +129,7 @@ struct CPart {
 struct Args {
   // previous mesh (candidates)
   const int32_t* p_off;
+  const int32_t* p_eoff;
   const int32_t* p_idx;
   const rich_edge* p_edges;
   int64_t p_n_csr, p_n_edges;
@@ -947,8 +948,8 @@ __global__ __launch_bounds__(kClipThreads) void k_rt_clip(Args one, Batch bt) {
 // over) are most of the loads.  Large meshes therefore try only the ring at
 // first (RING), and a second pass (k_rt_near) tries the neighbours'
 // neighbours of those cells that have a failed neighbour.  For the others
-// they cannot matter: every edge of the old triangulation at the point or at
-// one of its neighbours is then locally Delaunay, and a point inside a
+// they cannot matter where the old mesh is a triangulation (k_rt_near): every
+// edge of it at the point or at one of its neighbours is then locally Delaunay, and a point inside a
 // vertex's circle would have to be reached from it across such edges only,
 // each crossing keeping the point inside the next circle, until a triangle
 // holds it as a corner.  (That is a reason, not a proof: the path could leave
@@ -1189,7 +1190,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_rt_vertex(Args one, Batch bt)
 }
 
 // The neighbours' neighbours of the cells whose ring passed but that have a
-// neighbour whose ring did not.  Each wave lists such cells among its own 64
+// neighbour whose ring did not (or of all, below).  Each wave lists such cells among its own 64
 // (a lane per cell), goes through the list kThreads / kGroup cells at a time,
 // and queues those that fail for the clip with a mark of their own: the marks
 // that others look for stay those of the first pass.
@@ -1204,6 +1205,11 @@ __global__ __launch_bounds__(kThreads) void k_rt_near(Args one, Batch bt) {
   if ((a.bc == (int)RICH_BOUNDARY_PERIODIC) == WALLS || !tiered(a))
     return;  // another launch's run
   const int lane = (int)threadIdx.x;
+  // Three cells meet at every vertex of the previous mesh just when it has 3 n
+  // edges (one more between walls).  Where four meet (an exact lattice, whose
+  // diagonal edges of no length were dropped) the rings do not know of the
+  // point opposite: every cell is tried.
+  const bool whole = a.p_eoff[a.n] == 3 * a.n + (WALLS ? 1 : 0);
   bool near = false;
   const int i0 = blk * kThreads + lane;
   if (i0 < a.n && a.deg[i0] != kDegClip) {
@@ -1212,7 +1218,7 @@ __global__ __launch_bounds__(kThreads) void k_rt_near(Args one, Batch bt) {
 #pragma unroll
     for (int m = 0; m < kGroup; ++m) c[m] = m < n ? a.nb[k0 + m] : i0;
 #pragma unroll
-    for (int m = 0; m < kGroup; ++m) near = near || a.deg[c[m]] == kDegClip;
+    for (int m = 0; m < kGroup; ++m) near = near || !whole || a.deg[c[m]] == kDegClip;
   }
   const unsigned long long nears = __ballot(near);
   if (near) s_list[__popcll(nears & ((1ull << lane) - 1ull))] = i0;
@@ -1874,6 +1880,7 @@ int make_args(const rich_mesh* prev, const double* x, const double* y,
   char* w = static_cast<char*>(ws);
   std::memset(&a, 0, sizeof(a));
   a.p_off = prev->off;
+  a.p_eoff = prev->eoff;
   a.p_idx = prev->idx;
   a.p_edges = prev->edges;
   a.p_n_csr = prev->n_csr;

@@ -218,3 +218,35 @@ def test_a_run_of_many_end_blocks_in_a_batch():
         alone = _rebuild(R, m, p, X)
         assert (st, info) == alone[:2]
         assert _bytes(b, info) == _bytes(alone[2], info)
+
+
+@pytest.mark.parametrize("noise", [1e-8, 0.02])
+@pytest.mark.parametrize("name", ["sod", "wave"])
+def test_large_exact_lattice_moves(name, noise):
+    """An exact lattice of 102 400 cells whose points move by a part of the
+    spacing: four cells met at each vertex of the previous mesh, so every cell
+    gains neighbours that no ring holds.  The mesh is the input stage's (1e-12
+    of the cell size), but for edges as short as the cut for dropping them."""
+    import torch
+    from paper_1410_3219_amd import rich as R
+    P = {"wave": I.advected_wave, "sod": I.sod}[name](k=16, seed=3)
+    k = 320
+    c = (np.arange(k) + 0.5) / k
+    x, y = (v.ravel() for v in np.meshgrid(c, c, indexing="ij"))   # (a unit box)
+    assert tuple(P.box) == (0.0, 0.0, 1.0, 1.0)
+    o = T.rich_tess_hilbert_order(x, y, P.box)
+    m = T.rich_tess_build(x[o], y[o], P.box, P.bc)
+    X = np.stack([m.px, m.py]) + noise / k * np.random.default_rng(5).uniform(-1, 1, (2, k * k))
+    st, info, b = _rebuild(R, m, R.DeviceMesh.from_host(m), torch.from_numpy(X).cuda())
+    assert st == R.RICH_OK, info
+    dev = R.mesh_to_host(b.mesh(), info["n_edges"], info["n_csr"])
+    G.check_structure(dev)
+    ref = T.rich_tess_build(X[0], X[1], P.box, P.bc)
+    (kd, *gd), (kr, *gr) = G.edge_keys(dev), G.edge_keys(ref)
+    cut = 1e-12 / k / math.sqrt(math.pi)   # (edges of this length are kept or dropped by rounding)
+    assert np.isin(kd[gd[0] > 2 * cut], kr).all() and np.isin(kr[gr[0] > 2 * cut], kd).all()
+    both = np.intersect1d(kd, kr)
+    assert len(both) > 2.9 * k * k
+    for u, v in zip(gd, gr):   # lengths, midpoints
+        assert np.abs(u[np.isin(kd, both)] - v[np.isin(kr, both)]).max() <= 1e-12 / k
+    assert np.abs(dev.area - ref.area).max() <= 1e-12 / (k * k)
